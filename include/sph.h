@@ -129,8 +129,11 @@ sph_status sph_gemm_small(const sph_weights* w, const void* d_x, int64_t m, int6
 /* Y = X W^T for any batch 1 <= m <= 65536 (prefill and large batches): m <= 32 is sph_gemm_small;
  * larger batches run on the matrix cores (16x16x32 fp16 MFMA, fp32 accumulation) with the
  * factored exact-product arithmetic of sph_gemm_small's batches above 8, each weight's operands
- * rebuilt once per 64-row slice of X and per 128-column chunk of K. Same argument rules as
- * sph_gemm_small. When the
+ * rebuilt once per 64-row slice of X and per 128-column chunk of K; or, on large shapes, with the
+ * radius applied first and radius times direction split into two fp16 operands (23 bits), rebuilt
+ * once per 128-row slice, where the rounding error is no larger: that needs group offsets of 0 or of
+ * at least 2^-12 of the group's largest radius (found by sph_pack_weights and kept in the
+ * descriptor). Same argument rules as sph_gemm_small. When the
  * grid would not cover the chip, K is split and fp32 partial outputs go through the workspace
  * (sph_workspace_bytes(w, m); for m > 32 it needs no zero-fill) and are added in a fixed order,
  * so repeated calls give bitwise identical results. Asynchronous on `stream`. */
@@ -157,7 +160,8 @@ sph_status sph_gemm_small_noalloc(const sph_weights* w, const void* d_x, int64_t
  * workgroups: 64-bit words (fp32 sum and a valid flag), one per value of a tile over two
  * workgroups, one per workgroup and value of a tile over more, and one 32-bit arrival counter per
  * tile; where the prefill kernel runs (m above 16, and 9..16 on large matrices: see
- * sph_gemm_small) it holds fp32 partial outputs of a K split. It must be 256-byte
+ * sph_gemm_small) it holds fp32 partial outputs of a K split (a large batch with less workspace than
+ * this reports, but enough for the three-operand kernel, runs on that). It must be 256-byte
  * aligned and zero-filled before its first use, and every call leaves it zero-filled again (above
  * m = 32 it needs no initial contents, but is still left zero-filled). Calls that may run
  * concurrently must not share one. No call waits for another workgroup to make progress, so calls

@@ -14,3 +14,8 @@ void sph_host_pack(const sph_format* fmt, int64_t n, int64_t k, const uint8_t* s
                    const uint16_t* dir_idx, const uint8_t* radius_code, const uint16_t* gmin,
                    const uint16_t* gstep, const uint16_t* codebook, const uint64_t off[8],
                    uint8_t* blob);
+
+// Whether every weight's radius times direction fits two fp16 words at the precision of an fp32
+// product (SPH_FLAG_RADIUS_SPLIT): codes already checked by sph_host_check_codes.
+bool sph_host_radius_split(const sph_format* fmt, int64_t n, int64_t k, const uint16_t* gmin, const uint16_t* gstep,
+                           const uint16_t* codebook);

@@ -17,7 +17,8 @@
 //    A operands of v_mfma_f32_16x16x32_f16 (Eq. 7 factored over a group), activations form the
 //    B operand;
 //  - prefill (batch above 16, and 9..16 on large matrices): workgroups rebuild their tiles once
-//    per K-chunk and multiply them with activations staged in LDS on the same 16x16x32 MFMA;
+//    per K-chunk and multiply them with activations staged in LDS on the same 16x16x32 MFMA; large
+//    batches with the radius applied before the product (two MFMA operands instead of three);
 //  - 4-D and 16-D vectors: row-planar kernels, one wave per output row.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -1441,12 +1442,312 @@ __global__ void __launch_bounds__(PF_THREADS) k_gemm_prefill(KArgs a) {
   }
 }
 
+// ------------------------------------------------------------------------------------------
+// Wide prefill kernel (large batches on matrices whose radii allow it, see SPH_FLAG_RADIUS_SPLIT and
+// wide_plan): two MFMA operands per weight instead of three, 128 batch rows per workgroup.
+//
+// The matrix cores bound this path (2 m n k flop against 0.3-0.4 bytes per weight), and random
+// fp16 data runs them at about 1.75 PFLOP/s on this part (power; 16x16x32, measured in registers),
+// so the number of products counts. The kernel above multiplies t and the two halves of q * t (three
+// products and two sums per weight); here each weight's radius is applied before the product and
+// rho * t is split into two fp16 words, hi and lo, with rho = r * 2^e brought into fp16's upper range
+// by a power of two per (row, group): two products and one sum. One sum also leaves registers for
+// 128 batch rows, so each rebuilt weight meets twice as many columns.
+//
+// Precision. hi + lo holds rho * t to 23 bits (relative error of a sum about 3.3e-8), all sums are
+// fp32 and restart at every 128-column chunk, which is folded in once (the kernel above folds
+// twice). The matrix cores round each sum once per 8 products, so the lo products of a position
+// group are added before its hi products. wide_plan takes this kernel only where the modelled
+// rounding error is no larger than the three-product kernel's (see there).
+//
+// A workgroup of 8 waves owns T row tiles: 16 (two per wave) or 12 (two on waves 0-3, one on waves
+// 4-7, so three per SIMD), which lets 24576 rows x 256 fill 256 CUs once instead of 192 of them. X is staged
+// in LDS, 128 columns per buffer (64 beside the 128 KiB table of the 2^13 codebook, whose signs are
+// therefore applied by bit operations), 16-byte pieces swizzled against bank conflicts; codes and
+// parameters go straight to registers, half a chunk ahead, for no other wave needs them. The
+// weights of position group i + 1 are rebuilt between the lo and the hi products of group i.
+//
+// Measured (one box, HIP events, us; three-product kernel -> this one): W2 24576x4096 at 256 rows
+// 176 -> 116 (T = 12; T = 16 takes 134), W2 5120x5120 at 1024 217 -> 134, W3 4096x12288 at 2048
+// 550 -> 388, W3_cfg 9000x3072 at 700 146 -> 102. Three waves' VALU work per two matrix instructions
+// is what remains: a fold per half chunk cost 15%, fp16 conversions through fp32 products 10%,
+// v_fma_mixlo/hi_f16 (half rate) 8%, 32x32x16 products 20%, all more exact by under 4%.
+// ------------------------------------------------------------------------------------------
+constexpr int PW_MC = 128;   // batch rows per workgroup
+
+// The largest level of a format, for the scale (W2 with D = 6 has 4 or 3 radius bits: the larger).
+template <int KIND, int D>
+constexpr float PW_QMAX = KIND == SPH_KIND_NIB16Q8   ? 255.0f
+                          : KIND == SPH_KIND_CB13    ? 7.0f
+                          : KIND == SPH_KIND_NIB16   ? (float)((1 << (8 - (D < 8 ? D : 8))) - 1)
+                          : KIND == SPH_KIND_NIB16Q2 || (KIND == SPH_KIND_W2 && D == 7) ? 3.0f
+                                                                                         : 15.0f;
+
+template <int KIND, int D>
+struct PwCfg {
+  static constexpr bool SPLIT = IS_CB<KIND>;               // half a chunk of X per LDS buffer
+  static constexpr int KC = SPLIT ? 64 : 128;              // columns of X per buffer
+  static constexpr int XP = KC / 8;                        // 16-byte pieces per staged row
+  static constexpr int GPB = KC / 32;                      // position groups (4 positions) per buffer
+  static constexpr int NB = PW_MC / 16;
+  static constexpr int XPER = PW_MC * XP / PF_THREADS;     // pieces each thread stages
+  static constexpr uint32_t t_bytes = IS_CB<KIND> ? (16u << D) : (256u << D);
+  static constexpr uint32_t stage = PW_MC * KC * 2;
+  static constexpr uint32_t bytes = t_bytes + 2 * stage;
+  static constexpr bool B1 = KIND == SPH_KIND_W2 || KIND == SPH_KIND_NIB16Q2;
+  static constexpr int ADW = IS_CB<KIND> ? 4 : 8;
+  static constexpr int BDW = KIND == SPH_KIND_NIB16 ? 0 : B1 ? 1 : (KIND == SPH_KIND_NIB16Q8) ? 4 : 8;
+  static constexpr bool HAS_C = KIND == SPH_KIND_CB13Q4;
+  static_assert(bytes <= 160u * 1024u, "tables and two X buffers fit in LDS");
+  static_assert(PF_THREADS / XP % 16 == 0, "pieces of one thread share a swizzle");
+};
+
+// The signed direction and level of a row's vector.
+template <int KIND, int D>
+__device__ __forceinline__ uint4 pw_decode(uint32_t ra, uint32_t rb, uint32_t rc, const unsigned char* lds, int r, uint32_t& q) {
+  if constexpr (IS_CB<KIND>) {
+    uint32_t sg, z;
+    decode_cb13(ra, r % 4, rb, r & 1, sg, z, q);
+    if constexpr (KIND == SPH_KIND_CB13Q4) q |= ((rc >> r) & 1u) << 3;
+    const uint4 c = ((const uint4*)lds)[z];
+    const uint32_t u = sg | (sg << 15);   // sign of element 2i at bit 2i, of element 2i + 1 at bit 2i + 16
+    return make_uint4(c.x ^ ((u << 15) & 0x80008000u), c.y ^ ((u << 13) & 0x80008000u), c.z ^ ((u << 11) & 0x80008000u),
+                      c.w ^ ((u << 9) & 0x80008000u));
+  } else {
+    uint32_t l, hh, qx = 0;
+    if constexpr (KIND == SPH_KIND_W2) qx = (rb >> (4 * (r / 2))) & 15u;
+    if constexpr (KIND == SPH_KIND_NIB16Q2) qx = (rb >> (2 * r)) & 3u;
+    if constexpr (KIND == SPH_KIND_NIB16Q8) qx = (rb >> (8 * (r % 4))) & 0xFFu;
+    decode_nib<KIND, D>(ra, r & 1, qx, l, hh, q);
+    return signed_dir_nib<KIND, D>(lds, l, hh);
+  }
+}
+
+// rho * t for the 8 fp16 values of t as hi + lo: rho is split into two fp16 words (22 bits; the
+// levels and parameters leave it fewer), hi = fp16(rh t + fp16(rl t)) is the product rounded to
+// fp16, rh t - hi is exact (22 bits less their leading 11), and lo adds rl t to it with one
+// rounding, half an ulp of at most 2^-11 of the product.
+__device__ __forceinline__ void rt_split(uint4 t, float rho, uint4& hi, uint4& lo) {
+  const f16 rh = (f16)rho;
+  const f16 rl = (f16)(rho - (float)rh);
+  const f16x2 a = {rh, rh}, b = {rl, rl};
+  const uint32_t tw[4] = {t.x, t.y, t.z, t.w};
+  uint32_t h[4], l[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const f16x2 tv = as_h2(tw[i]);
+    const f16x2 p = __builtin_elementwise_fma(tv, a, tv * b);
+    const f16x2 d = __builtin_elementwise_fma(tv, a, -p);
+    h[i] = __builtin_bit_cast(uint32_t, p);
+    l[i] = __builtin_bit_cast(uint32_t, __builtin_elementwise_fma(tv, b, d));
+  }
+  hi = make_uint4(h[0], h[1], h[2], h[3]);
+  lo = make_uint4(l[0], l[1], l[2], l[3]);
+}
+
+// One wave's TPW tiles from tile tw0 over the chunks [c0, c1). Every wave of the workgroup runs the
+// same number of barriers whatever its TPW.
+template <int KIND, int D, int TPW>
+__device__ __forceinline__ void pw_wave(const KArgs& a, unsigned char* lds, int tw0, int mc0, int c0, int c1) {
+  using C = PwCfg<KIND, D>;
+  constexpr int NB = C::NB;
+  const int lane = threadIdx.x & 63;
+  const int r = lane & 15, j = lane >> 4;
+  unsigned char* xs = lds + C::t_bytes;
+  // this thread's pieces of X: byte offsets from the first batch row's chunk (rows past the batch
+  // repeat the last one; the launch keeps 127 row strides within 32 bits), and its place in LDS
+  uint32_t xg[C::XPER];
+  const int xrow0 = (int)threadIdx.x / C::XP, xpos = (int)threadIdx.x % C::XP;
+#pragma unroll
+  for (int p = 0; p < C::XPER; ++p)
+    xg[p] = (uint32_t)(min(mc0 + xrow0 + p * (PF_THREADS / C::XP), a.m - 1) - mc0) * (uint32_t)(2 * a.ldx) + (uint32_t)xpos * 16u;
+  const uint32_t xo = (uint32_t)(xrow0 * (C::KC * 2) + ((xpos ^ (xrow0 & (C::XP - 1))) * 16));
+  const char* xb = (const char*)(a.x + (int64_t)mc0 * a.ldx + (int64_t)c0 * 128);
+  // wave-uniform stream positions and the lane's offsets in a position group
+  const char *pa[TPW], *pb[TPW], *pc[TPW], *pp[TPW];
+#pragma unroll
+  for (int u = 0; u < TPW; ++u) {
+    const int64_t t = min(tw0 + u, a.nt - 1);   // tiles past the matrix repeat the last one, never stored
+    const int64_t rec = t * a.nv + (int64_t)c0 * 16;
+    pa[u] = (const char*)(a.A + rec * C::ADW);
+    pb[u] = (const char*)(a.B + rec * C::BDW);
+    pc[u] = (const char*)(a.C + rec);
+    pp[u] = (const char*)(a.P + (t * a.ng + c0) * 16);
+  }
+  const int adw = IS_CB<KIND> ? r / 4 : r / 2;
+  const int bdw = C::B1 ? 0 : (KIND == SPH_KIND_NIB16Q8) ? r / 4 : r / 2;
+  const uint32_t la = (uint32_t)(j * C::ADW + adw) * 4u, lb = (uint32_t)(j * C::BDW + bdw) * 4u, lc = (uint32_t)j * 2u,
+                 lp = (uint32_t)r * 4u;
+  uint32_t ra[TPW][4], rb[TPW][4], rc[TPW][4], pw[TPW];
+  // position groups 2h and 2h + 1 of the chunk at pa..pp, with h = 0 its parameters too
+  auto load_codes = [&](int h) {
+#pragma unroll
+    for (int u = 0; u < TPW; ++u) {
+#pragma unroll
+      for (int i = 2 * h; i < 2 * h + 2; ++i) {
+        ra[u][i] = *(const uint32_t*)(pa[u] + 16 * i * C::ADW + la);
+        rb[u][i] = C::BDW > 0 ? *(const uint32_t*)(pb[u] + 16 * i * C::BDW + lb) : 0u;
+        rc[u][i] = C::HAS_C ? *(const uint16_t*)(pc[u] + 8 * i + lc) : 0u;
+      }
+      if (h == 0) pw[u] = *(const uint32_t*)(pp[u] + lp);
+    }
+  };
+  uint4 xr[C::XPER];
+  auto fetch_x = [&]() {
+#pragma unroll
+    for (int p = 0; p < C::XPER; ++p) xr[p] = *(const uint4*)(xb + xg[p]);
+  };
+  auto put_x = [&](int buf) {
+#pragma unroll
+    for (int p = 0; p < C::XPER; ++p) *(uint4*)(xs + buf * C::stage + xo + p * (PF_THREADS / C::XP) * (C::KC * 2)) = xr[p];
+  };
+  fetch_x();
+  load_codes(0);
+  load_codes(1);
+  put_x(0);
+  f32x4 acc[TPW][NB];
+#pragma unroll
+  for (int u = 0; u < TPW; ++u)
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) acc[u][nb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  __syncthreads();   // the tables and the first X buffer
+  const uint32_t xrow = (uint32_t)(r * (C::KC * 2)), xsw = (uint32_t)(r & (C::XP - 1));
+  int buf = 0;
+  for (int c = c0; c < c1; ++c) {
+    const int adv = c + 1 < c1 ? 1 : 0;   // the last chunk prefetches itself
+    // per row, the power of two that brings the group's largest possible radius into [2^13, 2^14)
+    // (directions reach 2, so rho * t stays below fp16's 65504), and its inverse
+    float off[TPW], st[TPW], dn[TPW];
+#pragma unroll
+    for (int u = 0; u < TPW; ++u) {
+      const float o = f16lo(pw[u]), s = f16hi(pw[u]);
+      const uint32_t e = max(__builtin_bit_cast(uint32_t, fmaf(PW_QMAX<KIND, D>, s, fabsf(o))) & 0x7F800000u, 100u << 23);
+      const float up = __builtin_bit_cast(float, (267u << 23) - e);   // 2^(13 - exponent)
+      dn[u] = __builtin_bit_cast(float, e - (13u << 23));
+      off[u] = o * up;
+      st[u] = s * up;
+    }
+    auto rebuild = [&](int i, uint4 (&hi)[TPW], uint4 (&lo)[TPW]) {
+#pragma unroll
+      for (int u = 0; u < TPW; ++u) {
+        uint32_t q;
+        const uint4 t = pw_decode<KIND, D>(ra[u][i], rb[u][i], rc[u][i], lds, r, q);
+        rt_split(t, fmaf((float)q, st[u], off[u]), hi[u], lo[u]);
+      }
+    };
+    auto xfrag = [&](int i, int nb) {
+      const uint32_t p = (uint32_t)(4 * (i % C::GPB) + j);
+      return *(const f16x8*)(xs + buf * C::stage + xrow + nb * (16 * C::KC * 2) + ((p ^ xsw) * 16));
+    };
+    f32x4 s[TPW][NB];
+    uint4 hi[2][TPW], lo[2][TPW];
+    rebuild(0, hi[0], lo[0]);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (i % C::GPB == 0) {   // the next buffer's X, in flight during this one's products
+        xb += i + C::GPB < 4 ? 2 * C::KC : adv * 2 * C::KC;
+        fetch_x();
+      }
+      if (i == 2) {   // the first half's codes have been used: the next chunk's take their place
+#pragma unroll
+        for (int u = 0; u < TPW; ++u) {
+          pa[u] += adv * 64 * C::ADW;
+          pb[u] += adv * 64 * C::BDW;
+          pc[u] += adv * 32;
+          pp[u] += adv * 64;
+        }
+        load_codes(0);
+      }
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        const f16x8 x = xfrag(i, nb);
+#pragma unroll
+        for (int u = 0; u < TPW; ++u)
+          s[u][nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, lo[i & 1][u]), x,
+                                                            i == 0 ? f32x4{0.0f, 0.0f, 0.0f, 0.0f} : s[u][nb], 0, 0, 0);
+      }
+      if (i + 1 < 4) rebuild(i + 1, hi[(i + 1) & 1], lo[(i + 1) & 1]);
+      else load_codes(1);
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb) {
+        const f16x8 x = xfrag(i, nb);
+#pragma unroll
+        for (int u = 0; u < TPW; ++u)
+          s[u][nb] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, hi[i & 1][u]), x, s[u][nb], 0, 0, 0);
+      }
+      if (i == 3) {   // fold the chunk's sums in, with the scales of rows 4 * (lane / 16) + e
+#pragma unroll
+        for (int u = 0; u < TPW; ++u) {
+          float sc[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+            sc[e] = __builtin_bit_cast(float, __builtin_amdgcn_ds_bpermute((4 * j + e) * 4, __builtin_bit_cast(int, dn[u])));
+#pragma unroll
+          for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc[u][nb][e] = fmaf(sc[e], s[u][nb][e], acc[u][nb][e]);
+        }
+      }
+      if ((i + 1) % C::GPB == 0) {
+        // the other buffer's readers passed the previous barrier; this one makes it visible
+        put_x(buf ^ 1);
+        __syncthreads();
+        buf ^= 1;
+      }
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < TPW; ++u) {
+    const int tile = tw0 + u;
+    if (tile >= a.nt) continue;
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+      const int b = mc0 + 16 * nb + r;
+      if (b >= a.m) continue;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int row = tile * 16 + 4 * j + e;
+        if (a.ks > 1) a.ws_part[((int64_t)blockIdx.z * a.m + b) * ((int64_t)a.nt * 16) + row] = acc[u][nb][e];
+        else if (row < a.n) store_y(a, b, row, acc[u][nb][e]);
+      }
+    }
+  }
+}
+
+template <int KIND, int D, int T>
+__global__ void __launch_bounds__(PF_THREADS) k_gemm_wide(KArgs a) {
+  using C = PwCfg<KIND, D>;
+  static_assert(T == 16 || T == 12, "two tiles per wave, or two and one");
+  __shared__ __align__(16) unsigned char lds[C::bytes];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  // the tables in batches of up to 8 loads per thread, each batch one round trip
+  constexpr int n16 = (int)(C::t_bytes / 16u), TPER = (n16 + PF_THREADS - 1) / PF_THREADS, TB = TPER < 8 ? TPER : 8;
+#pragma unroll
+  for (int p0 = 0; p0 < TPER; p0 += TB) {
+    uint4 tv[TB];
+#pragma unroll
+    for (int p = 0; p < TB; ++p) tv[p] = a.T[min((int)threadIdx.x + PF_THREADS * (p0 + p), n16 - 1)];
+#pragma unroll
+    for (int p = 0; p < TB; ++p) {
+      const int t = (int)threadIdx.x + PF_THREADS * (p0 + p);
+      if (t < n16) ((uint4*)lds)[t] = tv[p];
+    }
+  }
+  const int c0 = (int)((int64_t)a.ng * blockIdx.z / a.ks), c1 = (int)((int64_t)a.ng * (blockIdx.z + 1) / a.ks);
+  const int t0 = (int)blockIdx.x * T, mc0 = (int)blockIdx.y * PW_MC;
+  if (T == 16 || wave < PF_WAVES / 2) pw_wave<KIND, D, 2>(a, lds, t0 + 2 * wave, mc0, c0, c1);
+  else pw_wave<KIND, D, 1>(a, lds, t0 + PF_WAVES / 2 + wave, mc0, c0, c1);
+}
+
 // y[b][row] = sum over the K ranges, in range order, of the prefill partials, which are cleared.
+// S: the type of the sum, fp32 for the three-product kernel, fp64 for the two-product one (its
+// ranges then add no rounding of their own; 0.4 us of the 5 us a small launch's pass takes).
 // Four consecutive rows per thread, so that every access to the partials is 16 bytes wide (the
 // rows are padded to whole tiles, and a range's partials start on a 64-byte boundary). All of a
 // thread's partials are read before any is cleared: read-add-clear per range made each read wait
 // for the previous range's store (the compiler cannot tell the addresses apart), one memory round
 // trip per range.
+template <typename S>
 __global__ void __launch_bounds__(256) k_prefill_reduce(KArgs a) {
   const int64_t npad = (int64_t)a.nt * 16, nq = npad / 4;
   const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -1458,16 +1759,18 @@ __global__ void __launch_bounds__(256) k_prefill_reduce(KArgs a) {
 #pragma unroll
   for (int z = 0; z < PF_KS_MAX; ++z)
     if (z < 2 || z < a.ks) v[z] = p0[z * zs];
-  f32x4 s = v[0];
+  S s[4] = {v[0][0], v[0][1], v[0][2], v[0][3]};
 #pragma unroll
   for (int z = 1; z < PF_KS_MAX; ++z)
-    if (z < 2 || z < a.ks) s += v[z];
+    if (z < 2 || z < a.ks)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s[e] += (S)v[z][e];
 #pragma unroll
   for (int z = 0; z < PF_KS_MAX; ++z)
     if (z < 2 || z < a.ks) p0[z * zs] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};   // left zero-filled, as every call promises
 #pragma unroll
   for (int e = 0; e < 4; ++e)
-    if (row + e < a.n) store_y(a, b, row + e, s[e]);
+    if (row + e < a.n) store_y(a, b, row + e, (float)s[e]);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -1685,8 +1988,12 @@ const void* pick(int D, int V, int M) {
   return nullptr;
 }
 
+// The prefill kernel of a plan: `wide` its tiles per workgroup on the two-product kernel, or 0 for
+// the three-product kernel with `mc` batch rows per workgroup.
 template <int KIND, int D>
-const void* prefill_fn_mc(int mc) {
+const void* prefill_fn_mc(int mc, int wide) {
+  if (wide == 16) return (const void*)k_gemm_wide<KIND, D, 16>;
+  if (wide == 12) return (const void*)k_gemm_wide<KIND, D, 12>;
   if (mc == 16) return (const void*)k_gemm_prefill<KIND, D, 16>;
   if (mc == 32) return (const void*)k_gemm_prefill<KIND, D, 32>;
   return (const void*)k_gemm_prefill<KIND, D, 64>;
@@ -1709,17 +2016,17 @@ bool small_on_prefill(const sph_weights* w, int64_t m) {
   return (int64_t)w->n * w->k >= 120ll << 20;
 }
 
-const void* prefill_fn(int D, int V, int mc) {
+const void* prefill_fn(int D, int V, int mc, int wide) {
   switch (sph_kind_of(D, V)) {
-    case SPH_KIND_W2: return D == 7 ? prefill_fn_mc<SPH_KIND_W2, 7>(mc) : prefill_fn_mc<SPH_KIND_W2, 6>(mc);
+    case SPH_KIND_W2: return D == 7 ? prefill_fn_mc<SPH_KIND_W2, 7>(mc, wide) : prefill_fn_mc<SPH_KIND_W2, 6>(mc, wide);
     case SPH_KIND_NIB16:
-      if (D == 4) return prefill_fn_mc<SPH_KIND_NIB16, 4>(mc);
-      if (D == 5) return prefill_fn_mc<SPH_KIND_NIB16, 5>(mc);
-      return prefill_fn_mc<SPH_KIND_NIB16, 6>(mc);
-    case SPH_KIND_NIB16Q8: return prefill_fn_mc<SPH_KIND_NIB16Q8, 8>(mc);
-    case SPH_KIND_NIB16Q2: return prefill_fn_mc<SPH_KIND_NIB16Q2, 8>(mc);
-    case SPH_KIND_CB13: return prefill_fn_mc<SPH_KIND_CB13, 13>(mc);
-    case SPH_KIND_CB13Q4: return prefill_fn_mc<SPH_KIND_CB13Q4, 13>(mc);
+      if (D == 4) return prefill_fn_mc<SPH_KIND_NIB16, 4>(mc, wide);
+      if (D == 5) return prefill_fn_mc<SPH_KIND_NIB16, 5>(mc, wide);
+      return prefill_fn_mc<SPH_KIND_NIB16, 6>(mc, wide);
+    case SPH_KIND_NIB16Q8: return prefill_fn_mc<SPH_KIND_NIB16Q8, 8>(mc, wide);
+    case SPH_KIND_NIB16Q2: return prefill_fn_mc<SPH_KIND_NIB16Q2, 8>(mc, wide);
+    case SPH_KIND_CB13: return prefill_fn_mc<SPH_KIND_CB13, 13>(mc, wide);
+    case SPH_KIND_CB13Q4: return prefill_fn_mc<SPH_KIND_CB13Q4, 13>(mc, wide);
   }
   return nullptr;
 }
@@ -1774,10 +2081,15 @@ int num_cus() {
 
 // Prefill plan: workgroups of PF_WAVES * PF_TPW tiles by MC batch rows; K is split only while the
 // split grid still fits in one round on the CUs (each split adds a pass over fp32 partial outputs).
+// wide: tiles per workgroup on the two-product kernel (12 or 16, 128 batch rows), or 0.
 struct PrefillPlan {
-  int gx, gy, ks, mc;
+  int gx, gy, ks, mc, wide;
   size_t ws_bytes;
 };
+
+size_t partial_bytes(const sph_weights* w, int64_t m, int64_t ks) {
+  return ks > 1 ? (size_t)(ks * m * ((w->n + 15) / 16) * 16) * sizeof(float) : 0;
+}
 
 PrefillPlan prefill_plan(const sph_weights* w, int64_t m) {
   PrefillPlan P{};
@@ -1791,9 +2103,51 @@ PrefillPlan prefill_plan(const sph_weights* w, int64_t m) {
   // least one chunk): a small grid otherwise leaves CUs idle (4096x12288 at 32 batch rows ran on
   // half of them with splits limited to powers of two up to 8, 17-18% slower)
   P.ks = (int)std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(cus / g, ng), PF_KS_MAX));
-  P.ws_bytes = P.ks > 1 ? (size_t)P.ks * m * nt * 16 * sizeof(float) : 0;
+  P.ws_bytes = partial_bytes(w, m, P.ks);
   return P;
 }
+
+// The plan of a batch above 32 on the two-product kernel, where it applies and pays; otherwise
+// wide = 0. It applies to matrices flagged at pack time, and where its rounding error is no larger
+// than the three-product kernel's under plan `old`. In units of the variance of one rounding at
+// the size of the result, with C chunks per K range: C / 2 for the folds, 14.5 for the roundings of
+// a chunk's sums and 2.2 for the operands here, against C for two folds, 6 and, before its partials
+// were added in fp64, ks / 2 there (measured on fp32 outputs against fp64: 1.22e-7 against 1.25e-7
+// for W2 6144x4096 at 256 rows, where the two sides are 20 and 23). It pays by a cost in ns fitted to
+// the launches named at the kernel and at 14 other shapes (within 15%): 4.0 us per chunk and round
+// of workgroups with 16 tiles, 3.2 with 12, 3.2 on the three-product kernel; split-K partials 4 us
+// and 1 us per megabyte.
+PrefillPlan wide_plan(const sph_weights* w, int64_t m, const PrefillPlan& old) {
+  PrefillPlan best{};
+  if (m <= 64 || !(w->off[SPH_OFF_FLAGS] & SPH_FLAG_RADIUS_SPLIT)) return best;
+  const int64_t nt = (w->n + 15) / 16, ng = w->k / 128, cus = num_cus();
+  auto cost = [&](int64_t wgs, int64_t ks, int64_t per_chunk) {
+    const int64_t c = (wgs * ks + cus - 1) / cus * ((ng + ks - 1) / ks) * per_chunk;
+    return ks > 1 ? c + 4000 + (int64_t)(partial_bytes(w, m, ks) / 1000) : c;
+  };
+  int64_t least = cost((int64_t)old.gx * old.gy, old.ks, 3200);
+  const double old_err = (double)ng / old.ks + 6.0 + (old.ks > 1 ? old.ks / 2.0 : 0.0);
+  for (const int T : {16, 12}) {
+    const int64_t gx = (nt + T - 1) / T, gy = (m + PW_MC - 1) / PW_MC;
+    const int64_t most = std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(cus / (gx * gy), ng), PF_KS_MAX));
+    for (int64_t ks = 1; ks <= most; ++ks) {
+      if (ng / (2.0 * ks) + 16.7 > old_err) continue;
+      const int64_t c = cost(gx * gy, ks, T == 16 ? 4000 : 3200);
+      if (c >= least) continue;
+      least = c;
+      best.gx = (int)gx;
+      best.gy = (int)gy;
+      best.ks = (int)ks;
+      best.mc = PW_MC;
+      best.wide = T;
+      best.ws_bytes = partial_bytes(w, m, ks);
+    }
+  }
+  return best;
+}
+
+// Row strides of X up to which 127 rows stay within the wide kernel's 32-bit byte offsets.
+constexpr int64_t PW_MAX_LDX = 1ll << 23;
 
 // m and k of udiv_by for a divisor 1 <= d < 2^31.
 void div_magic(int d, uint32_t& m, int& k) {
@@ -1867,8 +2221,12 @@ Launch plan(const sph_weights* w, int m) {
 // The prefill kernel (and its split-K reduction) for a validated call.
 sph_status launch_prefill(const sph_weights* w, const void* d_x, int64_t m, int64_t ldx, void* d_y, int64_t ldy,
                           sph_dtype y_dtype, void* d_ws, size_t ws_bytes, hipStream_t s) {
-  const PrefillPlan P = prefill_plan(w, m);
-  const void* fn = prefill_fn(w->fmt.dir_bits, w->fmt.radius_bits, P.mc);
+  PrefillPlan P = prefill_plan(w, m);
+  // the two-product kernel, unless the row stride or the workspace is beyond what it takes: then
+  // the three-product kernel runs, with the workspace it needs
+  const PrefillPlan W = wide_plan(w, m, P);
+  if (W.wide && ldx <= PW_MAX_LDX && (W.ws_bytes == 0 || (d_ws && ws_bytes >= W.ws_bytes && (uintptr_t)d_ws % 256 == 0))) P = W;
+  const void* fn = prefill_fn(w->fmt.dir_bits, w->fmt.radius_bits, P.mc, P.wide);
   if (!fn) return SPH_ERR_UNSUPPORTED_FORMAT;
   if (P.ws_bytes > 0) {
     if (!d_ws) return SPH_ERR_NULL;
@@ -1889,7 +2247,8 @@ sph_status launch_prefill(const sph_weights* w, const void* d_x, int64_t m, int6
   if (hipGetLastError() != hipSuccess) return SPH_ERR_HIP;
   if (P.ks > 1) {
     const int64_t total = (int64_t)m * ((w->n + 15) / 16) * 4;   // four rows per thread
-    if (hipLaunchKernel((const void*)k_prefill_reduce, dim3((unsigned)((total + 255) / 256)), dim3(256), kargs, 0, s) !=
+    const void* rf = P.wide ? (const void*)k_prefill_reduce<double> : (const void*)k_prefill_reduce<float>;
+    if (hipLaunchKernel(rf, dim3((unsigned)((total + 255) / 256)), dim3(256), kargs, 0, s) !=
         hipSuccess)
       return SPH_ERR_HIP;
     if (hipGetLastError() != hipSuccess) return SPH_ERR_HIP;
@@ -1903,8 +2262,8 @@ bool valid_desc(const sph_weights* w) {
   uint64_t off[8], total = 0;
   if (sph_host_layout(&w->fmt, w->n, w->k, off, &total) != SPH_OK || total > w->bytes) return false;
   for (int i = 0; i < 8; ++i)
-    if (off[i] != w->off[i]) return false;
-  return true;
+    if (i != SPH_OFF_FLAGS && off[i] != w->off[i]) return false;
+  return (w->off[SPH_OFF_FLAGS] & ~(uint64_t)SPH_FLAG_RADIUS_SPLIT) == 0;
 }
 
 sph_status launch(const Launch& L, const KArgs& a, hipStream_t s) {
@@ -2031,6 +2390,7 @@ sph_status sph_pack_weights(const sph_format* fmt, int64_t n, int64_t k, const u
   w.d_base = d_buf;
   w.bytes = (size_t)total;
   for (int i = 0; i < 8; ++i) w.off[i] = off[i];
+  w.off[SPH_OFF_FLAGS] = sph_host_radius_split(fmt, n, k, group_min, group_step, codebook) ? SPH_FLAG_RADIUS_SPLIT : 0;
   w.layout_version = SPH_LAYOUT_VERSION;
   w.magic = SPH_MAGIC;
   *out = w;
@@ -2045,7 +2405,13 @@ sph_status sph_workspace_bytes(const sph_weights* w, int64_t m, size_t* bytes) {
     *bytes = 0;
     return SPH_OK;
   }
-  *bytes = small_on_prefill(w, m) ? prefill_plan(w, m).ws_bytes : plan(w, (int)m).ws_bytes;
+  if (!small_on_prefill(w, m)) {
+    *bytes = plan(w, (int)m).ws_bytes;
+    return SPH_OK;
+  }
+  // enough for whichever prefill kernel the call takes
+  const PrefillPlan P = prefill_plan(w, m);
+  *bytes = std::max(P.ws_bytes, wide_plan(w, m, P).ws_bytes);
   return SPH_OK;
 }
 

@@ -62,8 +62,16 @@ enum sph_kind {
 
 // Offsets inside the device blob (sph_weights.off[]).
 enum sph_off {
-  SPH_OFF_A = 0, SPH_OFF_B = 1, SPH_OFF_PARAMS = 2, SPH_OFF_TABLES = 3, SPH_OFF_CODEBOOK = 4, SPH_OFF_C = 5
+  SPH_OFF_A = 0, SPH_OFF_B = 1, SPH_OFF_PARAMS = 2, SPH_OFF_TABLES = 3, SPH_OFF_CODEBOOK = 4, SPH_OFF_C = 5,
+  SPH_OFF_FLAGS = 7   // not an offset: properties of the codes found at pack time, 0 where not known
 };
+
+// A group's radii, scaled by one power of two, times the directions fit two fp16 words with an error
+// of at most 2^-25 of the vector's length (or one fp32 rounding, if that is larger): in every group
+// the offset is 0 or at least 2^-12 of the largest radius |offset| + (2^V - 1) step (so it stays
+// above 1 when at most twice that radius is brought to 2^13, where fp16's smallest step is 2^-24), and every
+// codebook entry is 0 or has a coordinate of at least 1/4.
+#define SPH_FLAG_RADIUS_SPLIT 1u
 
 static inline int sph_kind_of(int dir_bits, int radius_bits) {
   if ((dir_bits == 6 && (radius_bits == 4 || radius_bits == 3)) || (dir_bits == 7 && radius_bits == 2))

@@ -95,6 +95,34 @@ int sph_host_check_codes(const sph_format* fmt, int64_t n, int64_t k, const uint
   return SPH_OK;
 }
 
+// Value of a finite, non-negative fp16 bit pattern.
+static float f16_value(uint16_t h) {
+  const int e = (h >> 10) & 31, m = h & 1023;
+  return e ? std::ldexp((float)(1024 + m), e - 25) : std::ldexp((float)m, -24);
+}
+
+bool sph_host_radius_split(const sph_format* fmt, int64_t n, int64_t k, const uint16_t* gmin, const uint16_t* gstep,
+                           const uint16_t* codebook) {
+  if (fmt->vec_dim != SPH_VEC) return false;
+  const int64_t ngrp = n * (k / SPH_GROUP);
+  const float top = (float)((1 << fmt->radius_bits) - 1);
+  std::vector<float> val(0x7C00);   // values of all finite magnitudes
+  for (int h = 0; h < 0x7C00; ++h) val[h] = f16_value((uint16_t)h);
+  for (int64_t i = 0; i < ngrp; ++i) {
+    const float o = val[gmin[i] & 0x7FFF], s = val[gstep[i] & 0x7FFF];
+    if (o != 0.0f && o * 4096.0f < o + top * s) return false;
+  }
+  for (int64_t z = 0; z < (int64_t(1) << fmt->dir_bits); ++z) {
+    uint16_t most = 0;   // entries are non-negative, so their bit patterns order them
+    for (int j = 0; j < SPH_VEC; ++j) {
+      const uint16_t c = codebook[z * SPH_VEC + j] & 0x7FFF;
+      if (c > most) most = c;
+    }
+    if (most != 0 && val[most] < 0.25f) return false;
+  }
+  return true;
+}
+
 // Row-planar packing of the 4-D and 16-D formats (see sph_layout.h). For 16-D vectors the sign
 // array holds one little-endian uint16 per vector.
 static void pack_rowvec(const sph_format* fmt, int kind, int64_t n, int64_t k, const uint8_t* signs,
