@@ -1,22 +1,24 @@
 // Spherical encoder and codebook initialisation on the device (Sec. 3.1, Eq. 3 and 5-7;
 // Sec. 4.1 for the k-means settings).
 //
-// All arithmetic is fp64 on the vector ALUs, from fp32 weights, so that each integer decision (a
-// direction index, a radius level, a sampled vector) is taken in the same precision as in a plain
-// fp64 implementation of the equations. Sums whose order fixes the bits of a stored value (the
-// squared radius, the least-squares radius of Eq. 6, the norm of a k-means centre) use the
-// pairwise order ((p0+p1)+(p2+p3))+((p4+p5)+(p6+p7)) with the products rounded first, never
-// fused. Every reduction runs in a fixed order, so repeated calls give bitwise identical results.
+// Every decision is the fp64 one, from fp32 weights, so that each integer (a direction index, a radius
+// level, a sampled vector) is the one a plain fp64 implementation of the equations takes. Sums whose
+// order fixes the bits of a stored value (the squared radius, the least-squares radius of Eq. 6, the
+// norm of a k-means centre) use the pairwise order ((p0+p1)+(p2+p3))+((p4+p5)+(p6+p7)) with the
+// products rounded first, never fused. Every reduction runs in a fixed order or on integers, so
+// repeated calls give bitwise identical results.
 //
 // Work layout:
-//   encoder      one thread per 8-D vector (four per thread), 16 neighbouring lanes form one
-//                128-weight group; the codebook is staged in LDS as fp64 in 512-entry chunks and
-//                read by broadcast.
+//   Eq. 5 search a wave takes 64 vectors (or samples); the matrix cores score them against all
+//                entries within a known error, and only entries within that error of the best are
+//                compared in fp64 (see scan_entries and nearest_of).
+//   encoder      16 neighbouring lanes form one 128-weight group; the fp16 codebook sits in LDS.
 //   k-means      squared radii and their running sum (three-pass scan), inverse-CDF sampling by
 //                binary search, then per iteration: assignment (the centre range split over
-//                workgroups, splits combined in ascending order), exact fixed-point centre sums
-//                (integer LDS atomics per block, integer sums across blocks, so the order of
-//                arrival does not matter), renormalisation.
+//                workgroups, splits combined in ascending order) and a count per centre, the
+//                samples listed by centre, and one workgroup per centre that adds its samples in
+//                exact fixed point (integers, so the order of the list does not matter) and
+//                renormalises.
 #include <hip/hip_runtime.h>
 #include <limits.h>
 #include <math.h>
@@ -32,11 +34,8 @@ namespace {
 
 constexpr double kEps = 1e-12;  // Eq. 3's guard against a zero radius
 constexpr int kThreads = 256;
-constexpr int kVpt = 4;          // vectors (or samples) per thread in the assignment kernels
-constexpr int kChunk = 512;      // codebook entries per LDS pass: 32 KiB of fp64
 constexpr int kScanItems = 8;    // vectors per thread in the radius scan
 constexpr int kScanBlock = kThreads * kScanItems;
-constexpr int kTargetBlocks = 1024;  // workgroups the k-means launches aim for (256 CUs)
 
 // Pairwise sum of the eight rounded products a[j] * b[j].
 __device__ __forceinline__ double dot8_pairwise(const double* a, const double* b) {
@@ -45,6 +44,16 @@ __device__ __forceinline__ double dot8_pairwise(const double* a, const double* b
 #pragma unroll
   for (int j = 0; j < 8; ++j) p[j] = a[j] * b[j];
   return ((p[0] + p[1]) + (p[2] + p[3])) + ((p[4] + p[5]) + (p[6] + p[7]));
+}
+
+// Eq. 3's unit direction a / max(||a||, eps) of magnitudes a. Returns the radius.
+__device__ __forceinline__ double unit_direction(const double a[8], double d[8]) {
+#pragma clang fp contract(off)
+  const double r = sqrt(dot8_pairwise(a, a));
+  const double rr = r < kEps ? kEps : r;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) d[j] = a[j] / rr;
+  return r;
 }
 
 // Eq. 3 on one fp32 vector: magnitudes |w_j| (w_+), sign bits (set where w_j < 0) and the
@@ -62,53 +71,335 @@ __device__ __forceinline__ double decompose(const float* __restrict__ w, int64_t
     neg |= (f[j] < 0.0f ? 1u : 0u) << j;
     a[j] = fabs((double)f[j]);
   }
-  const double r = sqrt(dot8_pairwise(a, a));
-  const double rr = r < kEps ? kEps : r;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) d[j] = a[j] / rr;
-  return r;
+  return unit_direction(a, d);
 }
 
-// Eq. 5 over entries [base, base + cnt) of a codebook held in LDS (fp64, 8 per entry): strict
-// comparison in ascending index order keeps the lowest index among equal cosines.
-__device__ __forceinline__ void argmax_chunk(const double* __restrict__ cl, int cnt, int base,
-                                             const double (&d)[kVpt][8], double (&best)[kVpt],
-                                             int (&bz)[kVpt]) {
-  for (int e = 0; e < cnt; ++e) {
-    const double2* ce2 = reinterpret_cast<const double2*>(cl + e * 8);
-    const double2 c01 = ce2[0], c23 = ce2[1], c45 = ce2[2], c67 = ce2[3];
-    const double c[8] = {c01.x, c01.y, c23.x, c23.y, c45.x, c45.y, c67.x, c67.y};
+// ------------------------------------------------------------------------------------ Eq. 5
+
+typedef _Float16 h2v __attribute__((ext_vector_type(2)));
+typedef _Float16 h8v __attribute__((ext_vector_type(8)));
+typedef float f16v __attribute__((ext_vector_type(16)));
+
+// A unit direction as two fp16 words per pair of coordinates, d = hi + lo up to 2^-22 of it.
+struct DirWords {
+  uint32_t hi[4], lo[4];
+};
+
+__device__ __forceinline__ DirWords split_dir(const float (&d)[8]) {
+  DirWords w;
 #pragma unroll
-    for (int u = 0; u < kVpt; ++u) {
-      double s = d[u][0] * c[0];
+  for (int i = 0; i < 4; ++i) {
+    // taken as they are: folded into the product that made them, the two uses of hi could be
+    // rounded differently (once from the product, or by way of fp32)
+    float x = d[2 * i], y = d[2 * i + 1];
+    asm("" : "+v"(x), "+v"(y));
+    h2v h, l;
+    h[0] = (_Float16)x;
+    h[1] = (_Float16)y;
+    l[0] = (_Float16)(x - (float)h[0]);
+    l[1] = (_Float16)(y - (float)h[1]);
+    w.hi[i] = __builtin_bit_cast(uint32_t, h);
+    w.lo[i] = __builtin_bit_cast(uint32_t, l);
+  }
+  return w;
+}
+
+// (x, y) of the wave -> x = {lower half of x, lower half of y}, y = {upper half of x, upper half of y}.
+__device__ __forceinline__ void swap_halves(uint32_t& x, uint32_t& y) {
+  const bool low = (threadIdx.x & 32) == 0;
+  const uint32_t o = __shfl_xor(low ? y : x, 32, 64);
+  if (low) y = o;
+  else x = o;
+}
+
+// Scores are compared through their bit patterns as signed integers: for non-negative floats the
+// order is the same, and integer max needs no NaN canonicalisation.
+__device__ __forceinline__ int fbits(float x) { return __builtin_bit_cast(int, x); }
+__device__ __forceinline__ int max3i(int a, int b, int c) { return max(max(a, b), c); }
+__device__ __forceinline__ int med3i(int a, int b, int c) { return max(min(a, b), min(max(a, b), c)); }
+
+// The three best keys among a lane's entries, largest first. A key is the best score of a block of
+// entries with its low bits replaced by the block's number.
+struct Top3 {
+  int k[3];
+};
+
+// Screening by the matrix cores. Entry c (fp16, in LDS; LO: fp64 centres as two fp16 words, a second
+// array) against direction d: one v_mfma_f32_32x32x16_f16 forms c . d_hi + c . d_lo for 32 entries and
+// 32 vectors (K = 16, the lower lanes' operand d_hi, the upper ones' d_lo, the same entry for both),
+// with LO a second one adds c_lo . (d_hi + d_lo). Products are exact and the fp32 sums of up to 32
+// non-negative terms err by less than 2e-6 of the score, d's split by 2^-22 of it (and by 2^-25 a
+// coordinate where fp16 ends). A lane holds 16 of each 32 entries (rows 8 (i / 4) + 4 (lane / 32) + i % 4)
+// for vector lane % 32 of two blocks of 32, block b = 0 the wave's vectors 0..31. It keeps the three
+// best keys of blocks of GR * 32 entries. The scan is bound by the vector ALU's maxima
+// (a v_max3_i32 per two scores, 4 cycles; 20 instructions per 64 entries and 32 vectors) on top of the
+// products (64 cycles), which overlap with them only in part: issuing the next block's products
+// first gained 2%. GR = 2 spares the key's four instructions on every second product where one
+// product covers 32 entries; GR = 1 where two do halves the entries looked at again.
+template <int GR, bool LO>
+__device__ __forceinline__ void scan_entries(const uint4* cb, const uint4* cl, int nblk, const DirWords& w, Top3& p, Top3& q) {
+  const int lane = threadIdx.x & 63;
+  constexpr int kMask = GR == 2 ? 127 : 63;   // block numbers: up to 128 blocks of 64, 64 of 32
+  uint32_t b0[4], b1[4];
 #pragma unroll
-      for (int j = 1; j < 8; ++j) s = fma(d[u][j], c[j], s);
-      if (s > best[u]) {
-        best[u] = s;
-        bz[u] = base + e;
+  for (int i = 0; i < 4; ++i) {
+    b0[i] = w.hi[i];
+    b1[i] = w.lo[i];
+    swap_halves(b0[i], b1[i]);
+  }
+  const h8v bop[2] = {__builtin_bit_cast(h8v, make_uint4(b0[0], b0[1], b0[2], b0[3])),
+                      __builtin_bit_cast(h8v, make_uint4(b1[0], b1[1], b1[2], b1[3]))};
+  int k[2][3];
+#pragma unroll
+  for (int b = 0; b < 2; ++b) k[b][0] = k[b][1] = k[b][2] = INT_MIN;
+  const uint4* ca = cb + (lane & 31);
+  const uint4* cla = LO ? cl + (lane & 31) : nullptr;
+  f16v zero;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) zero[i] = 0.0f;
+  for (int blk = 0; blk < nblk; ++blk) {
+    f16v d[2][GR];
+#pragma unroll
+    for (int g = 0; g < GR; ++g) {
+      const h8v aop = __builtin_bit_cast(h8v, ca[(blk * GR + g) * 32]);
+#pragma unroll
+      for (int b = 0; b < 2; ++b) d[b][g] = __builtin_amdgcn_mfma_f32_32x32x16_f16(aop, bop[b], zero, 0, 0, 0);
+      if constexpr (LO) {
+        const h8v alo = __builtin_bit_cast(h8v, cla[(blk * GR + g) * 32]);
+#pragma unroll
+        for (int b = 0; b < 2; ++b) d[b][g] = __builtin_amdgcn_mfma_f32_32x32x16_f16(alo, bop[b], d[b][g], 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      int m = INT_MIN;
+#pragma unroll
+      for (int g = 0; g < GR; ++g)
+#pragma unroll
+        for (int i = 0; i < 16; i += 2) m = max3i(m, fbits(d[b][g][i]), fbits(d[b][g][i + 1]));
+      m = (m & ~kMask) | blk;
+      k[b][2] = med3i(k[b][1], k[b][2], m);
+      k[b][1] = med3i(k[b][0], k[b][1], m);
+      k[b][0] = max(k[b][0], m);
+    }
+  }
+  // both halves' keys of the lane's own vector: p from the rows of the lower lanes, q of the upper ones
+#pragma unroll
+  for (int t = 0; t < 3; ++t) {
+    uint32_t x = (uint32_t)k[0][t], y = (uint32_t)k[1][t];
+    swap_halves(x, y);
+    p.k[t] = (int)x;
+    q.k[t] = (int)y;
+  }
+}
+
+__device__ __forceinline__ float dot2(uint32_t a, uint32_t b, float c) {
+  return __builtin_amdgcn_fdot2(__builtin_bit_cast(h2v, a), __builtin_bit_cast(h2v, b), c, false);
+}
+
+// The score of one entry on the vector ALU, with the matrix cores' error bound.
+template <bool LO>
+__device__ __forceinline__ float score_of(const uint4* cb, const uint4* cl, int e, const DirWords& w) {
+  const uint4 c = cb[e];
+  const uint32_t cw[4] = {c.x, c.y, c.z, c.w};
+  float s = 0.0f;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) s = dot2(cw[i], w.lo[i], s);
+  if constexpr (LO) {
+    const uint4 l = cl[e];
+    const uint32_t lw[4] = {l.x, l.y, l.z, l.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) s = dot2(lw[i], w.hi[i], s);
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) s = dot2(cw[i], w.hi[i], s);
+  return s;
+}
+
+__device__ __forceinline__ double cosine(const double (&d)[8], const double (&c)[8]) {
+  double s = d[0] * c[0];
+#pragma unroll
+  for (int t = 1; t < 8; ++t) s = fma(d[t], c[t], s);
+  return s;
+}
+
+// The entry of [0, cnt) with the largest fp64 cosine to the direction of lane src, the lowest index among
+// equals, by the whole wave: each lane compares the entries scoring at least thr of its share. d: the
+// lanes' fp64 directions. 0 without a result (non-finite weights).
+template <bool LO, class EntF>
+__device__ __forceinline__ int wave_scan(const uint4* cb, const uint4* cl, int cnt, const DirWords& w, const double (&d)[8],
+                                         float thr, int src, EntF entry) {
+  const int lane = threadIdx.x & 63;
+  DirWords v;
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    v.hi[i] = __shfl(w.hi[i], src, 64);
+    v.lo[i] = __shfl(w.lo[i], src, 64);
+  }
+  double dv[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) dv[i] = __shfl(d[i], src, 64);
+  const float tv = __shfl(thr, src, 64);
+  double bs = -INFINITY;
+  int be = INT_MAX;
+  for (int e = lane; e < cnt; e += 64)
+    if (score_of<LO>(cb, cl, e, v) >= tv) {
+      double c[8];
+      entry(e, c);
+      const double sc = cosine(dv, c);
+      if (sc > bs) {
+        bs = sc;
+        be = e;
+      }
+    }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+    const double os = __shfl_xor(bs, o, 64);
+    const int oe = __shfl_xor(be, o, 64);
+    if (os > bs || (os == bs && oe < be)) {
+      bs = os;
+      be = oe;
+    }
+  }
+  return be < cnt ? be : 0;
+}
+
+// The entry of [0, cnt) with the largest fp64 cosine (an FMA chain in coordinate order), the lowest
+// index among equals, for the lane's vector. `active` lanes hold a non-zero direction in w; dir(d)
+// gives it in fp64 and entry(e, c) an entry in fp64. Every entry whose fp64 cosine could be the
+// largest scores within `slack` of the best key: twice the score's error (4e-6 of it), the key's
+// cut-off bits (2^-16 of it) and a margin. One survivor needs no fp64 at all; two are compared;
+// more, or more candidate blocks than were kept, go to a scan of all entries by the whole wave. Lanes
+// without a result (non-finite weights) get 0. The LDS holds nblk whole blocks.
+template <int GR, bool LO, class DirF, class EntF>
+__device__ __forceinline__ int nearest_of(const uint4* cb, const uint4* cl, int cnt, int nblk, const DirWords& w, bool active,
+                                          DirF dir, EntF entry) {
+  constexpr int kMask = GR == 2 ? 127 : 63;
+  Top3 p, q;
+  scan_entries<GR, LO>(cb, cl, nblk, w, p, q);
+  const float best = __builtin_bit_cast(float, max(p.k[0], q.k[0]) & ~kMask);
+  const float thr = best - (1e-5f + 3e-5f * best);
+  const int thr_i = thr < 0.0f ? INT_MIN : fbits(thr);
+  int e1 = 0, e2 = 0, n = 0;
+  // the candidate blocks: each lane's best first, then (rarely) the others
+  const int first = max(p.k[0], q.k[0]), first_half = p.k[0] >= q.k[0] ? 0 : 1;
+  const int second = min(p.k[0], q.k[0]);
+#pragma unroll 1
+  for (int t = 0; t < 4; ++t) {
+    const int key = t == 0 ? first : t == 1 ? second : t == 2 ? p.k[1] : q.k[1];
+    const int half = t == 0 ? first_half : t == 1 ? first_half ^ 1 : t - 2;
+    const bool on = active && key >= thr_i;
+    if (!__any(on)) continue;
+    const int base = (key & kMask) * (32 * GR) + 4 * half;
+    // four entries at a time, their LDS reads and dot products independent of each other (lanes
+    // that are not `on` read some block as well)
+#pragma unroll 2
+    for (int g = 0; g < 4 * GR; ++g) {
+      uint4 c[4], l[4];
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        c[x] = cb[base + 8 * g + x];
+        if constexpr (LO) l[x] = cl[base + 8 * g + x];
+      }
+      float a[4] = {0.0f, 0.0f, 0.0f, 0.0f}, b[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+          const uint32_t cw = i == 0 ? c[x].x : i == 1 ? c[x].y : i == 2 ? c[x].z : c[x].w;
+          a[x] = dot2(cw, w.hi[i], a[x]);
+          b[x] = dot2(cw, w.lo[i], b[x]);
+          if constexpr (LO) b[x] = dot2(i == 0 ? l[x].x : i == 1 ? l[x].y : i == 2 ? l[x].z : l[x].w, w.hi[i], b[x]);
+        }
+#pragma unroll
+      for (int x = 0; x < 4; ++x) {
+        const int e = base + 8 * g + x;
+        const bool hit = on && e < cnt && a[x] + b[x] >= thr;
+        e2 = hit && n == 1 ? e : e2;
+        e1 = hit && n == 0 ? e : e1;
+        n += hit ? 1 : 0;
       }
     }
   }
+  const bool wide = active && (p.k[2] >= thr_i || q.k[2] >= thr_i || n == 0 || n > 2);
+  if (__any(wide || (active && n == 2))) {
+    double d[8];
+    dir(d);
+    if (active && n == 2) {
+      double c1[8], c2[8];
+      entry(e1, c1);
+      entry(e2, c2);
+      const double s1 = cosine(d, c1), s2 = cosine(d, c2);
+      if (s2 > s1 || (s2 == s1 && e2 < e1)) e1 = e2;
+    }
+    for (uint64_t todo = __ballot(wide); todo; todo &= todo - 1) {
+      const int src = (int)__builtin_ctzll(todo);
+      const int e = wave_scan<LO>(cb, cl, cnt, w, d, thr, src, entry);
+      if ((int)(threadIdx.x & 63) == src) e1 = e;
+    }
+  }
+  return active ? e1 : 0;
 }
 
-// Stage entries [c0, c1) of the codebook chunk by chunk into LDS and run the argmax over them.
-// The source is either the fp16 codebook or fp64 centres. Every thread of the block must call this.
-template <typename T>
-__device__ __forceinline__ void argmax_codebook(const T* __restrict__ src, int c0, int c1, double* cl,
-                                                const double (&d)[kVpt][8], double (&best)[kVpt],
-                                                int (&bz)[kVpt]) {
-  for (int base = c0; base < c1; base += kChunk) {
-    const int cnt = min(kChunk, c1 - base);
-    __syncthreads();
-    for (int t = threadIdx.x; t < cnt * 8; t += kThreads) {
-      if constexpr (sizeof(T) == 2)
-        cl[t] = h2d(src[(int64_t)base * 8 + t]);
-      else
-        cl[t] = src[(int64_t)base * 8 + t];
-    }
-    __syncthreads();
-    argmax_chunk(cl, cnt, base, d, best, bz);
+// The same for a small codebook (at most 256 entries): keys carry the entry itself, so the best key
+// names the entry, and where the second best lies outside the slack nothing is left to decide (all
+// but about one vector in a thousand at 64 entries). Three instructions per score instead of half of one, but
+// no second look at a block of entries, which would cost more than the scan.
+template <class DirF, class EntF>
+__device__ __forceinline__ int nearest_small(const uint4* cb, int cnt, const DirWords& w, bool active, DirF dir, EntF entry) {
+  const int lane = threadIdx.x & 63;
+  const int mask = max(cnt, 32) - 1;   // cnt is a power of two
+  uint32_t b0[4], b1[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    b0[i] = w.hi[i];
+    b1[i] = w.lo[i];
+    swap_halves(b0[i], b1[i]);
   }
+  const h8v bop[2] = {__builtin_bit_cast(h8v, make_uint4(b0[0], b0[1], b0[2], b0[3])),
+                      __builtin_bit_cast(h8v, make_uint4(b1[0], b1[1], b1[2], b1[3]))};
+  f16v zero;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) zero[i] = 0.0f;
+  int k[2][2] = {{INT_MIN, INT_MIN}, {INT_MIN, INT_MIN}};
+  for (int e0 = 0; e0 < cnt; e0 += 32) {
+    const h8v aop = __builtin_bit_cast(h8v, cb[e0 + (lane & 31)]);
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const f16v d = __builtin_amdgcn_mfma_f32_32x32x16_f16(aop, bop[b], zero, 0, 0, 0);
+      int m1 = INT_MIN, m2 = INT_MIN;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int key = (fbits(d[i]) & ~mask) | (8 * (i / 4) + i % 4);
+        m2 = med3i(m1, m2, key);
+        m1 = max(m1, key);
+      }
+      m1 |= e0;
+      m2 |= e0;
+      k[b][1] = max(med3i(k[b][0], k[b][1], m1), m2);
+      k[b][0] = max(k[b][0], m1);
+    }
+  }
+  uint32_t x1 = (uint32_t)k[0][0], y1 = (uint32_t)k[1][0], x2 = (uint32_t)k[0][1], y2 = (uint32_t)k[1][1];
+  swap_halves(x1, y1);
+  swap_halves(x2, y2);
+  const int p1 = (int)x1, q1 = (int)y1 | 4, p2 = (int)x2, q2 = (int)y2 | 4;   // bit 2: the rows' half
+  const int k1 = max(p1, q1), k2 = max(min(p1, q1), max(p2, q2));
+  const float best = __builtin_bit_cast(float, k1 & ~mask);
+  const float thr = best - (1e-5f + best * (1e-5f + (float)(mask + 1) * 0x1p-23f));
+  const int thr_i = thr < 0.0f ? INT_MIN : fbits(thr);
+  int e1 = k1 & mask;
+  const bool wide = active && !(k2 < thr_i && e1 < cnt);
+  if (__any(wide)) {
+    double d[8];
+    dir(d);
+    for (uint64_t todo = __ballot(wide); todo; todo &= todo - 1) {
+      const int src = (int)__builtin_ctzll(todo);
+      const int e = wave_scan<false>(cb, nullptr, cnt, w, d, thr, src, entry);
+      if (lane == src) e1 = e;
+    }
+  }
+  return active ? e1 : 0;
 }
 
 // ------------------------------------------------------------------------------------ encoder
@@ -116,6 +407,8 @@ __device__ __forceinline__ void argmax_codebook(const T* __restrict__ src, int c
 struct EncArgs {
   const float* w;
   int64_t ldw, nv, nvec;
+  uint32_t nv_m;   // division by nv below 2^31, as (x * nv_m) >> nv_k; 0 for more vectors
+  int nv_k;
   const uint16_t* cb;
   int ncb, vmax;
   uint8_t* signs;
@@ -125,233 +418,127 @@ struct EncArgs {
   uint16_t* gstep;
 };
 
-// Eq. 3, 5, 6 and 7 for kVpt * 256 consecutive vectors. Groups of 16 vectors never straddle a
-// row (k is a multiple of 128) and start at multiples of 16 in the flat vector index, so each
-// group is 16 aligned lanes of one wave, all inside or all outside [0, nvec).
-__global__ __launch_bounds__(kThreads) void k_encode(EncArgs a) {
-  __shared__ double cl[kChunk * 8];
-  const int64_t blk = (int64_t)blockIdx.x * kThreads * kVpt;
-  double d[kVpt][8], best[kVpt];
-  int bz[kVpt];
-#pragma unroll
-  for (int u = 0; u < kVpt; ++u) {
-    const int64_t i = blk + u * kThreads + threadIdx.x;
-    best[u] = -INFINITY;
-    bz[u] = 0;
-    double av[8];
-    uint32_t neg;
-    if (i < a.nvec) {
-      decompose(a.w, a.ldw, a.nv, i, av, d[u], neg);
-    } else {
-#pragma unroll
-      for (int j = 0; j < 8; ++j) d[u][j] = 0.0;
+typedef uint32_t u4a2 __attribute__((ext_vector_type(4), aligned(2)));   // codebooks are 2-byte aligned
+
+// Minimum and maximum over 16-lane rows by DPP rotations.
+template <int CTRL>
+__device__ __forceinline__ double row_ror(double v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xF, 0xF, false);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xF, 0xF, false);
+  return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ void row_min_max(double& lo, double& hi) {
+  lo = fmin(lo, row_ror<0x128>(lo));
+  hi = fmax(hi, row_ror<0x128>(hi));
+  lo = fmin(lo, row_ror<0x124>(lo));
+  hi = fmax(hi, row_ror<0x124>(hi));
+  lo = fmin(lo, row_ror<0x122>(lo));
+  hi = fmax(hi, row_ror<0x122>(hi));
+  lo = fmin(lo, row_ror<0x121>(lo));
+  hi = fmax(hi, row_ror<0x121>(hi));
+}
+
+// Eq. 3, 5, 6 and 7: a wave encodes 64 consecutive vectors at a time, with the codebook (at most
+// MAXE entries) in LDS, rows past it zero. Groups of 16 vectors never straddle a row (k is a multiple of 128) and start at multiples of 16 in the flat
+// vector index, so each is 16 aligned lanes, all inside or all outside [0, nvec).
+//
+// The direction is normalised in fp32 for the screening, after scaling by a power of two so that no
+// square leaves its range: a common factor of d's coordinates (the rounded norm, Eq. 3's floor of
+// the radius) does not change which entry is nearest, and fp64 decides among survivors with Eq. 3's own.
+//
+// Measured (MI355X): 12288x4096 W2 (64 entries) 235 -> 107 us, of which the bytes take 45, the rest
+// vector-ALU work (about 2700 cycles per 64 vectors: a third the search, the rest Eq. 3, 6 and 7);
+// 4096x4096 W3 (8192 entries) 2.61 -> 0.61 ms, the scan. Before, every vector was compared with
+// every entry in fp64 (W2), or scored twice on 16x16x16 products with fp64 on the candidates (W3).
+template <int MAXE, int WAVES>
+__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(4))) void k_encode(EncArgs a, int64_t units) {
+  constexpr bool SMALL = MAXE <= 256;
+  static_assert(MAXE % 64 == 0, "whole blocks of entries");
+  __shared__ uint4 cbl[MAXE];
+  const int nthreads = (int)blockDim.x;
+  for (int t = threadIdx.x; t < MAXE; t += nthreads) {
+    uint4 c = make_uint4(0, 0, 0, 0);
+    if (t < a.ncb) {
+      const u4a2 v = *(const u4a2*)(a.cb + (int64_t)t * 8);
+      c = make_uint4(v[0], v[1], v[2], v[3]);
     }
+    cbl[t] = c;
   }
-  argmax_codebook(a.cb, 0, a.ncb, cl, d, best, bz);
+  __syncthreads();
+  const int lane = threadIdx.x & 63;
+  const int wpb = nthreads >> 6;
+  auto entry = [&](int e, double (&c)[8]) {
+    const uint4 v = cbl[e];
+    const uint32_t cw[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-  for (int u = 0; u < kVpt; ++u) {
-    const int64_t i = blk + u * kThreads + threadIdx.x;
-    // the magnitudes and signs are read again rather than kept live across the argmax
-    double av[8] = {0, 0, 0, 0, 0, 0, 0, 0}, dd[8];
+    for (int t = 0; t < 8; ++t) c[t] = h2d((uint16_t)(cw[t / 2] >> (16 * (t & 1))));
+  };
+  for (int64_t unit = (int64_t)blockIdx.x * wpb + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); unit < units; unit += (int64_t)gridDim.x * wpb) {
+    // the wave's first row and vector by one scalar division, the lanes' from there
+    const int64_t i0 = unit * 64, i = i0 + lane;
+    const bool ok = i < a.nvec;
+    int64_t row = a.nv_m ? (int64_t)(((uint64_t)(uint32_t)i0 * a.nv_m) >> a.nv_k) : i0 / a.nv;
+    int v = (int)(i0 - row * a.nv) + lane;
+    const int nv = (int)a.nv;
+    if (v >= nv) {
+      const int more = nv >= 64 ? 1 : v / nv;
+      row += more;
+      v -= more * nv;
+    }
+    float f[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    if (ok) {
+      const float4* p = reinterpret_cast<const float4*>(a.w + row * a.ldw + (int64_t)v * 8);
+      const float4 x0 = p[0], x1 = p[1];
+      f[0] = x0.x; f[1] = x0.y; f[2] = x0.z; f[3] = x0.w; f[4] = x1.x; f[5] = x1.y; f[6] = x1.z; f[7] = x1.w;
+    }
     uint32_t neg = 0;
-    if (i < a.nvec) decompose(a.w, a.ldw, a.nv, i, av, dd, neg);
-    double c[8];
+    float most = 0.0f;
 #pragma unroll
-    for (int j = 0; j < 8; ++j) c[j] = h2d(a.cb[(int64_t)bz[u] * 8 + j]);
+    for (int j = 0; j < 8; ++j) {
+      neg |= (f[j] < 0.0f ? 1u : 0u) << j;
+      f[j] = fabsf(f[j]);
+      most = fmaxf(most, f[j]);
+    }
+    const bool active = ok && most > 0.0f;   // a zero vector's cosines are all 0: the first entry
+    float d[8], ss = 0.0f;
+    const int ex = -__builtin_amdgcn_frexp_expf(most);
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      d[j] = ldexpf(f[j], ex);
+      ss = fmaf(d[j], d[j], ss);
+    }
+    const float inv = active ? __builtin_amdgcn_rsqf(ss) : 0.0f;   // ss is in [1/4, 8)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) d[j] *= inv;
+    const DirWords w = split_dir(d);
+    auto dir = [&](double (&dd)[8]) {
+      double av[8];
+#pragma unroll
+      for (int j = 0; j < 8; ++j) av[j] = (double)f[j];
+      unit_direction(av, dd);
+    };
+    int bz;
+    if constexpr (SMALL) bz = nearest_small(cbl, a.ncb, w, active, dir, entry);
+    else bz = nearest_of<2, false>(cbl, nullptr, a.ncb, (a.ncb + 63) / 64, w, active, dir, entry);
+    double av[8], c[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) av[j] = (double)f[j];
+    entry(bz, c);
     const double rt = dot8_pairwise(av, c);  // Eq. 6
     double lo = rt, hi = rt;
-#pragma unroll
-    for (int o = 1; o < 16; o <<= 1) {
-      lo = fmin(lo, __shfl_xor(lo, o, 16));
-      hi = fmax(hi, __shfl_xor(hi, o, 16));
-    }
+    row_min_max(lo, hi);
     const uint16_t lo16 = d2h(lo), st16 = d2h((hi - lo) / (double)a.vmax);
     const double lod = h2d(lo16), std_ = h2d(st16);
     int q = 0;
-    if (std_ > 0.0) {
-      const double t = rint((rt - lod) / std_);
-      q = (int)fmin(fmax(t, 0.0), (double)a.vmax);
-    }
-    if (i < a.nvec) {
+    if (std_ > 0.0) q = (int)fmin(fmax(rint((rt - lod) / std_), 0.0), (double)a.vmax);
+    if (ok) {
       a.signs[i] = (uint8_t)neg;
-      a.dir[i] = (uint16_t)bz[u];
+      a.dir[i] = (uint16_t)bz;
       a.q[i] = (uint8_t)q;
-      if ((threadIdx.x & 15) == 0) {
+      if ((lane & 15) == 0) {
         a.gmin[i >> 4] = lo16;
         a.gstep[i >> 4] = st16;
-      }
-    }
-  }
-}
-
-// Matrix-core direction search for the 2^13-entry codebook (exact in fp16). A unit direction d is
-// split as d_hi = fp16(d), d_lo = fp16(d - d_hi); with K = 16 = (c, c) . (d_hi, d_lo) one
-// v_mfma_f32_16x16x16_f16 scores 16 entries against 16 vectors with exact products and fp32
-// sums. |score - c.d| <= 2^-22 + 8 * 2^-24 (the split) + 16 * 2^-24 * 2 (fp32 sums) < delta =
-// 3e-6 (the matrix cores keep fp16 subnormal inputs, which the split produces for coordinates
-// below 2^-14). The fp64 argmax e* then has score >= s(e*) - delta >= best score - 2 delta:
-// every entry within kMxSlack (> 2 delta, with margin) of the best score is a candidate. Pass 1 finds each vector's best score; pass 2 rescores, and evaluates the fp64
-// cosine (the same FMA chain as the vector-ALU search, in ascending entry order) only for the
-// candidates. The result equals the full fp64 scan's. Lane layout: vector j = lane % 16 of each 16-vector block
-// (one radius group), entries 4 * (lane / 16) + e of each 16-entry block; the four lanes of a
-// vector are combined at the end (larger cosine, then lower index).
-constexpr int kMxWaves = 8;
-constexpr int kMxNB = 4;                                   // 16-vector blocks per wave
-constexpr int kMxVecPerWg = kMxWaves * kMxNB * 16;         // 512
-constexpr int kMxMaxEntries = 8192;
-constexpr float kMxSlack = 2e-5f;
-
-typedef _Float16 h4v __attribute__((ext_vector_type(4)));
-typedef float f4v __attribute__((ext_vector_type(4)));
-
-// A operand of lane (j, qd) for entry block e0: coordinates 4 * (qd & 1) .. + 3 of entry e0 + j
-// (k 8..15 repeat k 0..7), one 8-byte LDS read.
-__device__ __forceinline__ h4v mx_a_operand(const uint4* cbl, int e0, int j, int qd) {
-  return __builtin_bit_cast(h4v, ((const uint2*)cbl)[(e0 + j) * 2 + (qd & 1)]);
-}
-
-// Scores of non-negative vectors are compared through their bit patterns as signed integers:
-// for non-negative floats the order is the same, and integer max needs no NaN canonicalisation.
-__device__ __forceinline__ int fbits(float x) { return __builtin_bit_cast(int, x); }
-__device__ __forceinline__ int max4bits(const f4v acc) {
-  return max(max(fbits(acc[0]), fbits(acc[1])), max(fbits(acc[2]), fbits(acc[3])));
-}
-
-__global__ __launch_bounds__(64 * kMxWaves) void k_encode_mx(EncArgs a, int64_t nchunks) {
-  __shared__ uint4 cbl[kMxMaxEntries];   // the fp16 codebook, 16 bytes per entry (2^13 entries)
-  for (int t = threadIdx.x; t < kMxMaxEntries; t += 64 * kMxWaves) cbl[t] = ((const uint4*)a.cb)[t];
-  __syncthreads();
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int j = lane & 15, qd = lane >> 4;
-  for (int64_t ch = blockIdx.x; ch < nchunks; ch += gridDim.x) {
-    const int64_t v0 = ch * kMxVecPerWg + (int64_t)wave * (kMxNB * 16);
-    double d[kMxNB][8];
-    h4v bop[kMxNB];
-    bool ok[kMxNB];
-#pragma unroll
-    for (int nb = 0; nb < kMxNB; ++nb) {
-      const int64_t i = v0 + nb * 16 + j;
-      ok[nb] = i < a.nvec;
-      double av[8];
-      uint32_t neg;
-      if (ok[nb]) {
-        decompose(a.w, a.ldw, a.nv, i, av, d[nb], neg);
-      } else {
-#pragma unroll
-        for (int t = 0; t < 8; ++t) d[nb][t] = 0.0;
-      }
-#pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        // both halves pass through an empty asm so that the select stays a register select
-        // (an indexed read would put d in scratch memory)
-        double x0 = d[nb][t], x1 = d[nb][4 + t];
-        asm volatile("" : "+v"(x0), "+v"(x1));
-        const double x = (qd & 1) ? x1 : x0;
-        const _Float16 hi = (_Float16)(float)x;
-        bop[nb][t] = qd < 2 ? hi : (_Float16)(float)(x - (double)hi);
-      }
-    }
-    // pass 1: the best matrix-core score of every vector (scores of the non-negative entries and
-    // directions are >= 0 up to rounding; only a zero vector has its best at 0)
-    int mx[kMxNB];
-#pragma unroll
-    for (int nb = 0; nb < kMxNB; ++nb) mx[nb] = INT_MIN;
-#pragma unroll 4
-    for (int e0 = 0; e0 < kMxMaxEntries; e0 += 16) {
-      const h4v aop = mx_a_operand(cbl, e0, j, qd);
-#pragma unroll
-      for (int nb = 0; nb < kMxNB; ++nb) {
-        const f4v acc = __builtin_amdgcn_mfma_f32_16x16x16f16(aop, bop[nb], f4v{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
-        mx[nb] = max(mx[nb], max4bits(acc));
-      }
-    }
-    int thr[kMxNB];
-#pragma unroll
-    for (int nb = 0; nb < kMxNB; ++nb) {
-      int v = max(mx[nb], __shfl_xor(mx[nb], 16, 64));
-      v = max(v, __shfl_xor(v, 32, 64));
-      const float t = __builtin_bit_cast(float, v) - kMxSlack;
-      // a threshold below 0 (a zero vector) takes every entry; vectors past the end take none
-      thr[nb] = !ok[nb] ? INT_MAX : t < 0.0f ? INT_MIN : fbits(t);
-    }
-    // pass 2: fp64 cosines of the candidates, ascending entry order per lane
-    double best[kMxNB];
-    int bz[kMxNB];
-#pragma unroll
-    for (int nb = 0; nb < kMxNB; ++nb) {
-      best[nb] = -INFINITY;
-      bz[nb] = kMxMaxEntries;
-    }
-#pragma unroll 2
-    for (int e0 = 0; e0 < kMxMaxEntries; e0 += 16) {
-      const h4v aop = mx_a_operand(cbl, e0, j, qd);
-#pragma unroll
-      for (int nb = 0; nb < kMxNB; ++nb) {
-        const f4v acc = __builtin_amdgcn_mfma_f32_16x16x16f16(aop, bop[nb], f4v{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
-        if (max4bits(acc) >= thr[nb]) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            if (fbits(acc[e]) >= thr[nb]) {
-              const int ent = e0 + 4 * qd + e;
-              const uint4 ce = cbl[ent];
-              const uint32_t cw[4] = {ce.x, ce.y, ce.z, ce.w};
-              double c[8];
-#pragma unroll
-              for (int t = 0; t < 8; ++t) c[t] = h2d((uint16_t)(cw[t / 2] >> (16 * (t & 1))));
-              double sc = d[nb][0] * c[0];
-#pragma unroll
-              for (int t = 1; t < 8; ++t) sc = fma(d[nb][t], c[t], sc);
-              if (sc > best[nb]) {
-                best[nb] = sc;
-                bz[nb] = ent;
-              }
-            }
-          }
-        }
-      }
-    }
-#pragma unroll
-    for (int nb = 0; nb < kMxNB; ++nb) {
-#pragma unroll
-      for (int o = 16; o <= 32; o <<= 1) {
-        const double ob = __shfl_xor(best[nb], o, 64);
-        const int oz = __shfl_xor(bz[nb], o, 64);
-        if (ob > best[nb] || (ob == best[nb] && oz < bz[nb])) {
-          best[nb] = ob;
-          bz[nb] = oz;
-        }
-      }
-      if (bz[nb] >= a.ncb) bz[nb] = 0;   // no candidate (non-finite input): any valid index
-    }
-    // Eq. 6 and 7 as in k_encode; the four lanes of a vector agree, the first writes
-#pragma unroll
-    for (int nb = 0; nb < kMxNB; ++nb) {
-      const int64_t i = v0 + nb * 16 + j;
-      double av[8] = {0, 0, 0, 0, 0, 0, 0, 0}, dd[8];
-      uint32_t neg = 0;
-      if (ok[nb]) decompose(a.w, a.ldw, a.nv, i, av, dd, neg);
-      double c[8];
-#pragma unroll
-      for (int t = 0; t < 8; ++t) c[t] = h2d(a.cb[(int64_t)bz[nb] * 8 + t]);
-      const double rt = dot8_pairwise(av, c);
-      double lo = rt, hi = rt;
-#pragma unroll
-      for (int o = 1; o < 16; o <<= 1) {
-        lo = fmin(lo, __shfl_xor(lo, o, 16));
-        hi = fmax(hi, __shfl_xor(hi, o, 16));
-      }
-      const uint16_t lo16 = d2h(lo), st16 = d2h((hi - lo) / (double)a.vmax);
-      const double lod = h2d(lo16), std_ = h2d(st16);
-      int q = 0;
-      if (std_ > 0.0) q = (int)fmin(fmax(rint((rt - lod) / std_), 0.0), (double)a.vmax);
-      if (ok[nb] && qd == 0) {
-        a.signs[i] = (uint8_t)neg;
-        a.dir[i] = (uint16_t)bz[nb];
-        a.q[i] = (uint8_t)q;
-        if (j == 0) {
-          a.gmin[i >> 4] = lo16;
-          a.gstep[i >> 4] = st16;
-        }
       }
     }
   }
@@ -380,23 +567,33 @@ __device__ __forceinline__ double block_exclusive(double v, double* sh, double& 
   return woff + (incl - v);
 }
 
-// Squared radius r^2 of every vector (r from Eq. 3), stored in cdf[], and each block's total.
+// Squared radius r^2 of every vector (r from Eq. 3), stored in cdf[], and each block's total. The
+// vectors are read in order across the block (8 consecutive ones per thread, as they are summed, would
+// touch eight times the lines at once: 50 us for 4096x4096) and handed over through LDS.
 __global__ __launch_bounds__(kThreads) void k_r2(const float* __restrict__ w, int64_t ldw, int64_t nv,
                                                  int64_t nvec, double* __restrict__ cdf,
                                                  double* __restrict__ bsum) {
   __shared__ double sh[kThreads / 64];
-  const int64_t i0 = (int64_t)blockIdx.x * kScanBlock + (int64_t)threadIdx.x * kScanItems;
-  double s = 0.0;
+  __shared__ double val[kThreads * (kScanItems + 1)];   // one double of padding per thread's run
+  const int64_t b0 = (int64_t)blockIdx.x * kScanBlock;
+#pragma unroll
   for (int j = 0; j < kScanItems; ++j) {
-    const int64_t i = i0 + j;
-    if (i >= nvec) break;
-    double av[8], d[8];
-    uint32_t neg;
-    const double r = decompose(w, ldw, nv, i, av, d, neg);
-    const double r2 = r * r;
-    cdf[i] = r2;
-    s += r2;
+    const int o = j * kThreads + (int)threadIdx.x;
+    const int64_t i = b0 + o;
+    double r2 = 0.0;
+    if (i < nvec) {
+      double av[8], d[8];
+      uint32_t neg;
+      const double r = decompose(w, ldw, nv, i, av, d, neg);
+      r2 = r * r;
+      cdf[i] = r2;
+    }
+    val[o + o / kScanItems] = r2;
   }
+  __syncthreads();
+  double s = 0.0;
+#pragma unroll
+  for (int j = 0; j < kScanItems; ++j) s += val[threadIdx.x * (kScanItems + 1) + j];
   double total;
   block_exclusive(s, sh, total);
   if (threadIdx.x == 0) bsum[blockIdx.x] = total;
@@ -466,97 +663,234 @@ __global__ __launch_bounds__(kThreads) void k_sample(const float* __restrict__ w
   for (int c = 0; c < 8; ++c) ds[j * 8 + c] = d[c];
 }
 
+__device__ __forceinline__ void store_words(uint4* words, int ncb, int c, int e, double v);
+
 __global__ __launch_bounds__(kThreads) void k_init_centres(const uint16_t* __restrict__ init, int64_t count,
-                                                           double* __restrict__ cen) {
+                                                           double* __restrict__ cen, uint4* __restrict__ words) {
   const int64_t t = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (t < count) cen[t] = h2d(init[t]);
+  if (t >= count) return;
+  const double v = h2d(init[t]);
+  cen[t] = v;
+  store_words(words, (int)(count / 8), (int)(t / 8), (int)(t & 7), v);
 }
 
 // Eq. 5 for every sample against centres [split * per, (split + 1) * per): the best cosine and its
-// index per sample and split (blockIdx.y is the split).
-__global__ __launch_bounds__(kThreads) void k_assign_split(const double* __restrict__ ds, int64_t ns,
-                                                           const double* __restrict__ cen, int ncb, int per,
-                                                           double* __restrict__ sbest, int32_t* __restrict__ sidx) {
-  __shared__ double cl[kChunk * 8];
-  const int64_t blk = (int64_t)blockIdx.x * kThreads * kVpt;
+// index per sample and split (blockIdx.y is the split). The centres go through LDS kCentres at a
+// time as two fp16 words per coordinate (error 2^-22 of it, inside nearest_of's bound), kept beside the
+// fp64 ones by whoever moves a centre; a later chunk wins only with a strictly larger cosine. 65,536 samples, 8192 centres: 236 us
+// (fp64 against every centre) -> 44 us.
+constexpr int kCentres = 2048;   // 64 KiB of LDS
+
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(4))) void k_assign_split(const double* __restrict__ ds, int64_t ns,
+                                                             const double* __restrict__ cen, const uint4* __restrict__ words, int ncb,
+                                                             int per, double* __restrict__ sbest, int32_t* __restrict__ sidx) {
+  constexpr int MAXE = WAVES == 16 ? kCentres : 256;
+  __shared__ uint4 ch[MAXE], cl[MAXE];
+  const int lane = threadIdx.x & 63;
+  const int64_t j = ((int64_t)blockIdx.x * WAVES + (threadIdx.x >> 6)) * 64 + lane;
   const int c0 = blockIdx.y * per, c1 = min(ncb, c0 + per);
-  double d[kVpt][8], best[kVpt];
-  int bz[kVpt];
+  double d[8];
 #pragma unroll
-  for (int u = 0; u < kVpt; ++u) {
-    const int64_t j = blk + u * kThreads + threadIdx.x;
-    best[u] = -INFINITY;
-    bz[u] = c0;
+  for (int c = 0; c < 8; ++c) d[c] = j < ns ? ds[j * 8 + c] : 0.0;
+  float f[8], most = 0.0f;
 #pragma unroll
-    for (int c = 0; c < 8; ++c) d[u][c] = j < ns ? ds[j * 8 + c] : 0.0;
+  for (int c = 0; c < 8; ++c) {
+    f[c] = (float)d[c];
+    most = fmaxf(most, f[c]);
   }
-  argmax_codebook(cen, c0, c1, cl, d, best, bz);
-#pragma unroll
-  for (int u = 0; u < kVpt; ++u) {
-    const int64_t j = blk + u * kThreads + threadIdx.x;
-    if (j < ns) {
-      sbest[blockIdx.y * ns + j] = best[u];
-      sidx[blockIdx.y * ns + j] = bz[u];
+  const bool active = most > 0.0f;   // a zero vector's cosines are all 0: the first centre
+  const DirWords w = split_dir(f);
+  double best = -INFINITY;
+  int bz = c0;
+  for (int base = c0; base < c1; base += MAXE) {
+    const int cnt = min(MAXE, c1 - base), nblk = (cnt + 31) / 32;
+    __syncthreads();
+    for (int t = threadIdx.x; t < nblk * 32; t += 64 * WAVES) {
+      ch[t] = t < cnt ? words[base + t] : make_uint4(0, 0, 0, 0);
+      cl[t] = t < cnt ? words[ncb + base + t] : make_uint4(0, 0, 0, 0);
     }
+    __syncthreads();
+    auto entry = [&](int e, double (&c)[8]) {
+      const double2* p = reinterpret_cast<const double2*>(cen + (int64_t)(base + e) * 8);
+      const double2 x0 = p[0], x1 = p[1], x2 = p[2], x3 = p[3];
+      c[0] = x0.x; c[1] = x0.y; c[2] = x1.x; c[3] = x1.y; c[4] = x2.x; c[5] = x2.y; c[6] = x3.x; c[7] = x3.y;
+    };
+    const int z = nearest_of<1, true>(
+        ch, cl, cnt, nblk, w, active,
+        [&](double (&dd)[8]) {
+#pragma unroll
+          for (int c = 0; c < 8; ++c) dd[c] = d[c];
+        },
+        entry);
+    double c[8];
+    entry(z, c);
+    const double s = cosine(d, c);
+    if (s > best) {
+      best = s;
+      bz = base + z;
+    }
+  }
+  if (j < ns) {
+    sbest[blockIdx.y * ns + j] = best;
+    sidx[blockIdx.y * ns + j] = bz;
   }
 }
 
 // The splits combined in ascending order with a strict comparison (the same decision as one scan
-// over all centres); z[j] gets the nearest centre and each block writes the sum of its samples'
-// cosines to their centre (each summed in pairwise order, then in a fixed order over the block).
-__global__ __launch_bounds__(kThreads) void k_assign_final(const double* __restrict__ ds, int64_t ns,
-                                                           const double* __restrict__ cen, int nsplit,
-                                                           const double* __restrict__ sbest,
-                                                           const int32_t* __restrict__ sidx,
-                                                           int32_t* __restrict__ z, double* __restrict__ opart) {
-  __shared__ double sh[kThreads / 64];
-  const int64_t j = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  double v = 0.0;
-  if (j < ns) {
-    double best = sbest[j];
-    int bz = sidx[j];
-    for (int t = 1; t < nsplit; ++t) {
-      const double b = sbest[t * ns + j];
-      if (b > best) {
-        best = b;
-        bz = sidx[t * ns + j];
+// over all centres): z[j] gets the nearest centre, rank[j] its place among that centre's samples of this
+// block's chunk of ch samples (in whatever order they arrive), hist[block][centre] their number. Each
+// 256 samples' cosines to their centres are summed (each in pairwise order, then in a fixed order) into
+// opart. Counted in LDS: a few centres take thousands of samples each (weight vectors with an outlier),
+// and global atomics on them took 30 us. rank may be sidx's first split.
+constexpr int kFinalThreads = 1024;
+
+__global__ __launch_bounds__(kFinalThreads) void k_assign_final(const double* __restrict__ ds, int64_t ns, int64_t ch,
+                                                                const double* __restrict__ cen, int ncb, int nsplit,
+                                                                const double* __restrict__ sbest, const int32_t* sidx,
+                                                                int32_t* __restrict__ z, int32_t* rank,
+                                                                uint32_t* __restrict__ hist, double* __restrict__ opart) {
+  __shared__ uint32_t cnt[8192];
+  __shared__ double wsum[kFinalThreads / 64];
+  for (int t = threadIdx.x; t < ncb; t += kFinalThreads) cnt[t] = 0;
+  __syncthreads();
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int64_t j0 = blockIdx.x * ch, j1 = min(ns, j0 + ch);
+  for (int64_t base = j0; base < j1; base += kFinalThreads) {   // ch is a multiple of kFinalThreads
+    const int64_t j = base + threadIdx.x;
+    double v = 0.0;
+    if (j < j1) {
+      double best = sbest[j];
+      int bz = sidx[j];
+      for (int t = 1; t < nsplit; ++t) {
+        const double b = sbest[t * ns + j];
+        if (b > best) {
+          best = b;
+          bz = sidx[t * ns + j];
+        }
       }
-    }
-    z[j] = bz;
-    double d[8];
+      z[j] = bz;
+      rank[j] = (int32_t)atomicAdd(&cnt[bz], 1u);
+      double d[8];
 #pragma unroll
-    for (int c = 0; c < 8; ++c) d[c] = ds[j * 8 + c];
-    v = dot8_pairwise(d, cen + (int64_t)bz * 8);
+      for (int c = 0; c < 8; ++c) d[c] = ds[j * 8 + c];
+      v = dot8_pairwise(d, cen + (int64_t)bz * 8);
+    }
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const double t = __shfl_up(v, o, 64);
+      if (lane >= o) v += t;
+    }
+    __syncthreads();
+    if (lane == 63) wsum[wv] = v;
+    __syncthreads();
+    if (threadIdx.x < kFinalThreads / 256 && base + threadIdx.x * 256 < ns) {
+      double s = 0.0;
+#pragma unroll
+      for (int k = 0; k < 4; ++k) s += wsum[4 * threadIdx.x + k];
+      opart[base / 256 + threadIdx.x] = s;
+    }
   }
-  double total;
-  block_exclusive(v, sh, total);
-  if (threadIdx.x == 0) opart[blockIdx.x] = total;
+  __syncthreads();
+  for (int t = threadIdx.x; t < ncb; t += kFinalThreads) hist[(int64_t)blockIdx.x * ncb + t] = cnt[t];
 }
 
-// Objective of one assignment: the blocks' sums, lane-strided in block order and then combined
-// by a fixed lane tree.
-__global__ __launch_bounds__(64) void k_objective(const double* __restrict__ opart, int64_t nblk,
-                                                  double* __restrict__ out) {
-  double s = 0.0;
-  for (int64_t b = threadIdx.x; b < nblk; b += 64) s += opart[b];
+// Per centre, the running sum of the chunks' counts over the nch chunks, in place, and their total;
+// the last block adds up the objective of the assignment (if wanted) over its nblk partial sums,
+// lane-strided in block order and then by a fixed lane tree.
+__global__ __launch_bounds__(kThreads) void k_offsets(uint32_t* __restrict__ hist, int nch, int ncb, uint32_t* __restrict__ count,
+                                                      const double* __restrict__ opart, int64_t nblk, double* __restrict__ out) {
+  if (blockIdx.x + 1 == gridDim.x) {
+    if (!out || threadIdx.x >= 64) return;
+    double s = 0.0;
+    for (int64_t b = threadIdx.x; b < nblk; b += 64) s += opart[b];
 #pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o, 64);
-  if (threadIdx.x == 0) *out = s;
+    for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o, 64);
+    if (threadIdx.x == 0) *out = s;
+    return;
+  }
+  const int c = blockIdx.x * kThreads + threadIdx.x;
+  if (c >= ncb) return;
+  uint32_t run = 0;
+  for (int b0 = 0; b0 < nch; b0 += 16) {
+    uint32_t v[16];
+#pragma unroll
+    for (int t = 0; t < 16; ++t) v[t] = b0 + t < nch ? hist[(int64_t)(b0 + t) * ncb + c] : 0u;
+#pragma unroll
+    for (int t = 0; t < 16; ++t) {
+      if (b0 + t < nch) hist[(int64_t)(b0 + t) * ncb + c] = run;
+      run += v[t];
+    }
+  }
+  count[c] = run;
+}
+
+// The samples listed by centre, perm[start of the centre + the chunk's offset in it + rank] = sample,
+// the starts being the running sum of the counts, which every block forms for itself in LDS. Block 0
+// keeps them, and the list of centres with more than kBig samples.
+constexpr int kListThreads = 1024;
+constexpr int kBig = 256;          // samples up to which one wave adds up a centre
+constexpr int kMaxBig = 1024;      // big centres kept; more are left to their waves
+
+__global__ __launch_bounds__(kListThreads) void k_list(const int32_t* __restrict__ z, const int32_t* __restrict__ rank,
+                                                       int64_t ns, int64_t ch, const uint32_t* __restrict__ hist,
+                                                       const uint32_t* __restrict__ count, int ncb,
+                                                       uint32_t* __restrict__ start, uint32_t* __restrict__ big,
+                                                       int32_t* __restrict__ perm) {
+  __shared__ uint32_t at[8192];
+  __shared__ uint32_t wsum[kListThreads / 64];
+  __shared__ uint32_t nbig;
+  const int per = (ncb + kListThreads - 1) / kListThreads;   // 1..8 consecutive centres per thread
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int e0 = (int)threadIdx.x * per;
+  if (threadIdx.x == 0) nbig = 0;
+  uint32_t own[8], s = 0;
+#pragma unroll
+  for (int t = 0; t < 8; ++t) {
+    own[t] = t < per && e0 + t < ncb ? count[e0 + t] : 0u;
+    s += own[t];
+  }
+  uint32_t incl = s;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const uint32_t u = __shfl_up(incl, o, 64);
+    if (lane >= o) incl += u;
+  }
+  if (lane == 63) wsum[wv] = incl;
+  __syncthreads();
+  uint32_t run = incl - s;
+  for (int k = 0; k < wv; ++k) run += wsum[k];
+#pragma unroll
+  for (int t = 0; t < 8; ++t) {
+    if (t < per && e0 + t < ncb) {
+      at[e0 + t] = run;
+      if (blockIdx.x == 0) {
+        start[e0 + t] = run;
+        if (own[t] > kBig) {
+          const uint32_t b = atomicAdd(&nbig, 1u);
+          if (b < kMaxBig) big[1 + b] = (uint32_t)(e0 + t);
+        }
+      }
+    }
+    run += own[t];
+  }
+  __syncthreads();
+  if (blockIdx.x == 0 && threadIdx.x == 0) big[0] = nbig <= kMaxBig ? nbig : 0;
+  for (int64_t j = (int64_t)blockIdx.x * kListThreads + threadIdx.x; j < ns; j += (int64_t)gridDim.x * kListThreads) {
+    const int c = z[j];
+    perm[at[c] + hist[j / ch * ncb + c] + (uint32_t)rank[j]] = (int32_t)j;
+  }
 }
 
 // Centre sums by exact fixed-point accumulation. A direction component v in [0, 1 + 2^-52] is
-// truncated to T = floor(v * 2^100) and added as three 40-bit limbs in 64-bit integers. Integer
-// addition is associative, so the sums do not depend on the order in which samples are added,
-// and 2^24 samples cannot overflow a limb. The sum is exact up to the 2^-100 truncation of each
-// term. Block (r, p) adds the samples of chunk p whose centre lies in range r with LDS atomics
-// and stores its limbs; one wave per centre then adds the chunks' limbs.
+// truncated to T = floor(v * 2^100) in a 128-bit integer. Integer addition is associative, so the
+// sums do not depend on the order in which samples are listed, and 2^24 samples cannot overflow. The sum
+// is exact up to the 2^-100 truncation of each term.
 constexpr int kFixBits = 100;
 constexpr int kLimbBits = 40;
 constexpr uint64_t kLimbMask = (1ull << kLimbBits) - 1;
-constexpr int kLimbs = 8 * 3;       // limbs per centre
-constexpr int kAccRange = 512;      // centres per LDS accumulator: 96 KiB
 
-__device__ __forceinline__ void to_limbs(double v, uint64_t& l0, uint64_t& l1, uint64_t& l2) {
+__device__ __forceinline__ unsigned __int128 to_fixed(double v) {
   const uint64_t bits = __builtin_bit_cast(uint64_t, v);
   const int ex = (int)(bits >> 52);  // components are >= 0; 0 for zero and subnormals
   unsigned __int128 t = 0;
@@ -568,75 +902,75 @@ __device__ __forceinline__ void to_limbs(double v, uint64_t& l0, uint64_t& l1, u
     else if (sh > -64)
       t = m >> -sh;
   }
-  l0 = (uint64_t)t & kLimbMask;
-  l1 = (uint64_t)(t >> kLimbBits) & kLimbMask;
-  l2 = (uint64_t)(t >> (2 * kLimbBits));
+  return t;
 }
 
-__global__ __launch_bounds__(kThreads) void k_accumulate(const double* __restrict__ ds, int64_t ns,
-                                                         const int32_t* __restrict__ z, int ncb, int64_t ch,
-                                                         unsigned long long* __restrict__ part) {
-  __shared__ unsigned long long la[kAccRange * kLimbs];
-  const int c0 = blockIdx.x * kAccRange, c1 = min(ncb, c0 + kAccRange), nc = c1 - c0;
-  const int p = blockIdx.y;
-  for (int t = threadIdx.x; t < nc * kLimbs; t += kThreads) la[t] = 0;
-  __syncthreads();
-  const int64_t j0 = (int64_t)p * ch, j1 = min(ns, j0 + ch);
-  for (int64_t j = j0 + threadIdx.x; j < j1; j += kThreads) {
-    const int c = z[j];
-    if (c < c0 || c >= c1) continue;
-    unsigned long long* a = la + (c - c0) * kLimbs;
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      uint64_t l0, l1, l2;
-      to_limbs(ds[j * 8 + e], l0, l1, l2);
-      if (l0) atomicAdd(a + 3 * e, (unsigned long long)l0);
-      if (l1) atomicAdd(a + 3 * e + 1, (unsigned long long)l1);
-      if (l2) atomicAdd(a + 3 * e + 2, (unsigned long long)l2);
-    }
-  }
-  __syncthreads();
-  unsigned long long* out = part + ((int64_t)p * ncb + c0) * kLimbs;
-  for (int t = threadIdx.x; t < nc * kLimbs; t += kThreads) out[t] = la[t];
+// The fp16 words of centre c's coordinate e (lanes 0..7 of a wave hold the coordinates): the same split
+// as split_dir's, for k_assign_split.
+__device__ __forceinline__ void store_words(uint4* words, int ncb, int c, int e, double v) {
+  const float f = (float)v;
+  const _Float16 h = (_Float16)f, l = (_Float16)(f - (float)h);
+  ((_Float16*)(words + c))[e] = h;
+  ((_Float16*)(words + ncb + c))[e] = l;
 }
 
-// New centre c: the chunks' limbs added (integers, so in any order), converted to fp64 and the
-// sum normalised to unit length; a centre without directions keeps its position.
-__global__ __launch_bounds__(64) void k_update(const unsigned long long* __restrict__ part, int np, int ncb,
-                                               double* __restrict__ cen) {
+// New centres: eight lanes per sample, one for each component, add a centre's listed samples; the
+// sums are converted to fp64 and normalised to unit length; a centre without directions keeps its
+// position. One wave per centre of at most kBig samples (blocks of 16), and one block for each of the
+// big ones, which the last gridDim.x - (ncb + 15) / 16 blocks share. (65,536 samples, 8192 centres,
+// a few of them with thousands: 101 + 30 us with LDS atomics in passes over all samples per centre range,
+// 10 + 22 us with the list; 148 us with one wave per centre whatever its size.)
+__global__ __launch_bounds__(1024) void k_update(const double* __restrict__ ds, const int32_t* __restrict__ perm,
+                                                 const uint32_t* __restrict__ start, const uint32_t* __restrict__ count,
+                                                 const uint32_t* __restrict__ big, int ncb, double* __restrict__ cen,
+                                                 uint4* __restrict__ words) {
 #pragma clang fp contract(off)
-  const int c = blockIdx.x;
-  const int lane = threadIdx.x;
-  uint64_t l[kLimbs];
+  __shared__ uint64_t part[16][8][2];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, e = lane & 7;
+  const int small = (ncb + 15) / 16;
+  const bool one = (int)blockIdx.x < small;   // a wave per centre
+  const uint32_t nbig = big[0];
+  for (uint32_t b = one ? 0u : blockIdx.x - small; one || b < nbig; b += gridDim.x - small) {
+    const int c = one ? (int)blockIdx.x * 16 + wv : (int)big[1 + b];
+    const bool have = c < ncb && !(one && nbig > 0 && count[c] > kBig);   // wave-uniform
+    unsigned __int128 sum = 0;
+    if (have) {
+      const uint32_t len = count[c], first = start[c];
+      const uint32_t t0 = one ? lane >> 3 : threadIdx.x >> 3, step = one ? 8 : 128;
+#pragma unroll 4
+      for (uint32_t t = t0; t < len; t += step) sum += to_fixed(ds[(int64_t)perm[first + t] * 8 + e]);
 #pragma unroll
-  for (int t = 0; t < kLimbs; ++t) l[t] = 0;
-  for (int p = lane; p < np; p += 64) {
-    const unsigned long long* a = part + ((int64_t)p * ncb + c) * kLimbs;
+      for (int o = 8; o <= 32; o <<= 1) {
+        const uint64_t lo = __shfl_xor((uint64_t)sum, o, 64), hi = __shfl_xor((uint64_t)(sum >> 64), o, 64);
+        sum += ((unsigned __int128)hi << 64) | lo;
+      }
+    }
+    if (!one) {
+      if (lane < 8) {
+        part[wv][e][0] = (uint64_t)sum;
+        part[wv][e][1] = (uint64_t)(sum >> 64);
+      }
+      __syncthreads();
+      sum = 0;
+      for (int k = 0; k < 16; ++k) sum += ((unsigned __int128)part[k][e][1] << 64) | part[k][e][0];
+      __syncthreads();
+    }
+    if (have && (one || wv == 0)) {
+      // limbs of 40 bits convert exactly; two roundings combine them
+      const uint64_t l0 = (uint64_t)sum & kLimbMask, l1 = (uint64_t)(sum >> kLimbBits) & kLimbMask, l2 = (uint64_t)(sum >> (2 * kLimbBits));
+      const double hi = ((double)l2 * 0x1p40 + (double)l1) * 0x1p40;
+      const double mine = (hi + (double)l0) * 0x1p-100;
+      double s[8];
 #pragma unroll
-    for (int t = 0; t < kLimbs; ++t) l[t] += a[t];
-  }
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-#pragma unroll
-    for (int t = 0; t < kLimbs; ++t) l[t] += __shfl_xor(l[t], o, 64);
-  }
-  if (lane != 0) return;
-  double s[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    uint64_t l0 = l[3 * e], l1 = l[3 * e + 1], l2 = l[3 * e + 2];
-    l1 += l0 >> kLimbBits;
-    l0 &= kLimbMask;
-    l2 += l1 >> kLimbBits;
-    l1 &= kLimbMask;
-    // l2 < 2^53 and l1, l0 < 2^40 convert exactly; two roundings combine them
-    const double hi = ((double)l2 * 0x1p40 + (double)l1) * 0x1p40;
-    s[e] = (hi + (double)l0) * 0x1p-100;
-  }
-  const double norm = sqrt(dot8_pairwise(s, s));
-  if (norm > 0.0) {
-#pragma unroll
-    for (int e = 0; e < 8; ++e) cen[(int64_t)c * 8 + e] = s[e] / norm;
+      for (int t = 0; t < 8; ++t) s[t] = __shfl(mine, t, 64);
+      const double norm = sqrt(dot8_pairwise(s, s));
+      if (norm > 0.0 && lane < 8) {
+        const double v = mine / norm;
+        cen[(int64_t)c * 8 + e] = v;
+        store_words(words, ncb, c, e, v);
+      }
+    }
+    if (one) break;
   }
 }
 
@@ -651,29 +985,30 @@ __global__ __launch_bounds__(kThreads) void k_centres_to_f16(const double* __res
 inline uint64_t align256(uint64_t x) { return (x + 255) / 256 * 256; }
 
 struct KmPlan {
-  int64_t nvec, nb, nab, nfb, ch;
-  int ncb, nsplit, per, nr, np;
-  uint64_t off_cdf, off_bsum, off_ds, off_z, off_opart, off_cen, off_acc, off_sbest, off_sidx, total;
+  int64_t nvec, nb, nfb, ch;
+  int ncb, nsplit, per, waves, nch;
+  uint64_t off_cdf, off_bsum, off_ds, off_z, off_opart, off_cen, off_words, off_count, off_hist, off_sbest, off_sidx, total;
 };
 
 KmPlan km_plan(const sph_format* fmt, int64_t n, int64_t k, int64_t ns) {
   KmPlan P{};
   P.nvec = n * (k / SPH_VEC);
   P.nb = (P.nvec + kScanBlock - 1) / kScanBlock;
-  P.nab = (ns + kThreads * kVpt - 1) / (kThreads * kVpt);
   P.nfb = (ns + kThreads - 1) / kThreads;
   P.ncb = 1 << fmt->dir_bits;
-  // centre splits of the assignment: enough workgroups for the chip, at least 64 centres each
-  int64_t sp = (kTargetBlocks + P.nab - 1) / P.nab;
-  sp = std::min<int64_t>(sp, std::max(1, P.ncb / 64));
+  // Waves per workgroup of the assignment: 16 share the staged centres where there are many, 4 spread
+  // a small codebook's samples over more CUs. Centre splits: enough waves for four per SIMD, at
+  // least 256 centres each, and no more than 2^20 + ns split results altogether.
+  P.waves = P.ncb > 256 ? 16 : 4;
+  const int64_t units = (ns + 63) / 64;
+  int64_t sp = (4096 + units - 1) / units;
+  sp = std::min<int64_t>(sp, std::max(1, P.ncb / 256));
+  sp = std::max<int64_t>(1, std::min<int64_t>(sp, ((1 << 20) + ns) / ns));
   P.per = (int)((P.ncb + sp - 1) / sp);
   P.nsplit = (P.ncb + P.per - 1) / P.per;
-  // centre ranges x sample chunks of the accumulation: about 128 workgroups
-  P.nr = (P.ncb + kAccRange - 1) / kAccRange;
-  int64_t np = (128 + P.nr - 1) / P.nr;
-  np = std::min<int64_t>(np, (ns + kThreads - 1) / kThreads);
-  P.ch = (ns + np - 1) / np;
-  P.np = (int)((ns + P.ch - 1) / P.ch);
+  // sample chunks of the counting: whole rounds of kFinalThreads samples, at most 64 chunks
+  P.ch = ((ns + 63) / 64 + kFinalThreads - 1) / kFinalThreads * kFinalThreads;
+  P.nch = (int)((ns + P.ch - 1) / P.ch);
   uint64_t p = 0;
   P.off_cdf = p;
   p = align256(p + (uint64_t)P.nvec * 8);
@@ -687,11 +1022,15 @@ KmPlan km_plan(const sph_format* fmt, int64_t n, int64_t k, int64_t ns) {
   p = align256(p + (uint64_t)P.nfb * 8);
   P.off_cen = p;
   p = align256(p + (uint64_t)P.ncb * 64);
-  P.off_acc = p;
-  p = align256(p + (uint64_t)P.np * P.ncb * kLimbs * 8);
-  P.off_sbest = p;
+  P.off_words = p;
+  p = align256(p + (uint64_t)P.ncb * 32);
+  P.off_count = p;   // counts, list starts, big centres
+  p = align256(p + ((uint64_t)P.ncb * 2 + 1 + std::min(P.ncb, kMaxBig)) * 4);
+  P.off_hist = p;
+  p = align256(p + (uint64_t)P.nch * P.ncb * 4);
+  P.off_sbest = p;   // after a split's results are combined, the samples listed by centre
   p = align256(p + (uint64_t)P.nsplit * ns * 8);
-  P.off_sidx = p;
+  P.off_sidx = p;    // likewise the samples' ranks
   p = align256(p + (uint64_t)P.nsplit * ns * 4);
   P.total = p;
   return P;
@@ -715,6 +1054,15 @@ int check_common(const sph_format* fmt, int64_t n, int64_t k, const float* d_w, 
   if (!d_w) return SPH_ERR_NULL;
   if (ldw < k || ldw % 4 != 0 || (uintptr_t)d_w % 16 != 0) return SPH_ERR_SHAPE;
   return SPH_OK;
+}
+
+constexpr int kSmallEntries = 256, kMaxEntries = 8192;   // direction bits are 4..8 or 13
+
+int num_cus() {
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
+    return 256;
+  return cus;
 }
 
 template <typename... A>
@@ -747,24 +1095,30 @@ sph_status sph_encode(const sph_format* fmt, int64_t n, int64_t k, const float* 
   a.cb = d_codebook;
   a.ncb = 1 << fmt->dir_bits;
   a.vmax = (1 << fmt->radius_bits) - 1;
+  if (a.nvec < (1ll << 31)) {
+    // exact below 2^31: m = ceil(2^k / nv) with k = 31 + ceil(log2 nv) exceeds 2^k / nv by less than 2^(k - 31) / nv
+    int l = 0;
+    while ((1ll << l) < a.nv) ++l;
+    a.nv_k = 31 + l;
+    a.nv_m = (uint32_t)(((1ull << a.nv_k) + (uint64_t)a.nv - 1) / (uint64_t)a.nv);
+  }
   a.signs = d_signs;
   a.dir = d_dir_idx;
   a.q = d_radius_code;
   a.gmin = d_group_min;
   a.gstep = d_group_step;
-  if (a.ncb == kMxMaxEntries) {
-    // the 2^13-entry codebook: matrix-core search, one 128 KiB codebook copy per CU
-    const int64_t nchunks = (a.nvec + kMxVecPerWg - 1) / kMxVecPerWg;
-    int dev = 0, cus = 256;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-      cus = 256;
-    const int64_t grid = std::min<int64_t>(nchunks, cus);
-    if (!launch_ok((const void*)k_encode_mx, dim3((unsigned)grid), dim3(64 * kMxWaves), (hipStream_t)stream, a, nchunks))
+  const int64_t units = (a.nvec + 63) / 64;
+  if (a.ncb <= kSmallEntries) {
+    if (!launch_ok((const void*)k_encode<kSmallEntries, 4>, dim3((unsigned)((units + 3) / 4)), dim3(256), (hipStream_t)stream, a, units))
       return SPH_ERR_HIP;
     return SPH_OK;
   }
-  const int64_t grid = (a.nvec + kThreads * kVpt - 1) / (kThreads * kVpt);
-  if (!launch_ok((const void*)k_encode, dim3((unsigned)grid), dim3(kThreads), (hipStream_t)stream, a))
+  // the 2^13-entry codebook: one 128 KiB copy per CU, shared by up to 16 waves (at least 4, which
+  // load it)
+  const int cus = num_cus();
+  const int64_t waves = std::min<int64_t>(16, std::max<int64_t>(4, (units + cus - 1) / cus));
+  const int64_t grid = std::min<int64_t>(cus, (units + waves - 1) / waves);
+  if (!launch_ok((const void*)k_encode<kMaxEntries, 16>, dim3((unsigned)grid), dim3((unsigned)(64 * waves)), (hipStream_t)stream, a, units))
     return SPH_ERR_HIP;
   return SPH_OK;
 }
@@ -802,9 +1156,15 @@ sph_status sph_kmeans_codebook(const sph_format* fmt, int64_t n, int64_t k, cons
   int32_t* z = (int32_t*)(ws + P.off_z);
   double* opart = (double*)(ws + P.off_opart);
   double* cen = (double*)(ws + P.off_cen);
-  unsigned long long* acc = (unsigned long long*)(ws + P.off_acc);
+  uint32_t* count = (uint32_t*)(ws + P.off_count);
+  uint32_t* start = count + P.ncb;
+  uint32_t* big = start + P.ncb;
+  uint32_t* hist = (uint32_t*)(ws + P.off_hist);
+  uint4* words = (uint4*)(ws + P.off_words);
   double* sbest = (double*)(ws + P.off_sbest);
   int32_t* sidx = (int32_t*)(ws + P.off_sidx);
+  int32_t* perm = (int32_t*)sbest;
+  int32_t* rank = sidx;
   const int64_t ns = n_samples, nv = k / SPH_VEC, ncb8 = (int64_t)P.ncb * 8;
   const dim3 blk(kThreads);
   const unsigned g_cb = (unsigned)((ncb8 + kThreads - 1) / kThreads);
@@ -814,21 +1174,26 @@ sph_status sph_kmeans_codebook(const sph_format* fmt, int64_t n, int64_t k, cons
             launch_ok((const void*)k_scan_apply, dim3((unsigned)P.nb), blk, s, cdf, (const double*)bsum, P.nvec) &&
             launch_ok((const void*)k_sample, dim3(g_s), blk, s, d_w, ldw, nv, P.nvec, (const double*)cdf, d_u, ns,
                       ds, d_sample_idx) &&
-            launch_ok((const void*)k_init_centres, dim3(g_cb), blk, s, d_init, ncb8, cen);
-  const dim3 g_split((unsigned)P.nab, (unsigned)P.nsplit);
+            launch_ok((const void*)k_init_centres, dim3(g_cb), blk, s, d_init, ncb8, cen, words);
+  const int64_t units = (ns + 63) / 64;
+  const dim3 g_split((unsigned)((units + P.waves - 1) / P.waves), (unsigned)P.nsplit);
+  const void* assign = P.waves == 16 ? (const void*)k_assign_split<16> : (const void*)k_assign_split<4>;
+  const unsigned g_list = (unsigned)((ns + kListThreads - 1) / kListThreads);
+  const unsigned g_upd = (unsigned)((P.ncb + 15) / 16 + std::min(P.ncb, 256));
+  const unsigned g_off = (unsigned)((P.ncb + kThreads - 1) / kThreads + 1);
   for (int32_t it = 0; ok && it <= iters; ++it) {
-    ok = launch_ok((const void*)k_assign_split, g_split, blk, s, (const double*)ds, ns, (const double*)cen, P.ncb,
+    ok = launch_ok(assign, g_split, dim3(64 * P.waves), s, (const double*)ds, ns, (const double*)cen, (const uint4*)words, P.ncb,
                    P.per, sbest, sidx) &&
-         launch_ok((const void*)k_assign_final, dim3((unsigned)P.nfb), blk, s, (const double*)ds, ns,
-                   (const double*)cen, P.nsplit, (const double*)sbest, (const int32_t*)sidx, z, opart);
-    if (ok && d_objective)
-      ok = launch_ok((const void*)k_objective, dim3(1), dim3(64), s, (const double*)opart, P.nfb,
-                     d_objective + it);
+         launch_ok((const void*)k_assign_final, dim3((unsigned)P.nch), dim3(kFinalThreads), s, (const double*)ds, ns, P.ch,
+                   (const double*)cen, P.ncb, P.nsplit, (const double*)sbest, (const int32_t*)sidx, z, rank, hist, opart);
+    if (ok && (d_objective || it < iters))
+      ok = launch_ok((const void*)k_offsets, dim3(g_off), blk, s, hist, P.nch, P.ncb, count, (const double*)opart, P.nfb,
+                     d_objective ? d_objective + it : (double*)nullptr);
     if (ok && it < iters)
-      ok = launch_ok((const void*)k_accumulate, dim3((unsigned)P.nr, (unsigned)P.np), blk, s, (const double*)ds, ns,
-                     (const int32_t*)z, P.ncb, P.ch, acc) &&
-           launch_ok((const void*)k_update, dim3((unsigned)P.ncb), dim3(64), s, (const unsigned long long*)acc, P.np,
-                     P.ncb, cen);
+      ok = launch_ok((const void*)k_list, dim3(g_list), dim3(kListThreads), s, (const int32_t*)z, (const int32_t*)rank, ns, P.ch,
+                     (const uint32_t*)hist, (const uint32_t*)count, P.ncb, start, big, perm) &&
+           launch_ok((const void*)k_update, dim3(g_upd), dim3(1024), s, (const double*)ds, (const int32_t*)perm,
+                     (const uint32_t*)start, (const uint32_t*)count, (const uint32_t*)big, P.ncb, cen, words);
   }
   if (ok) ok = launch_ok((const void*)k_centres_to_f16, dim3(g_cb), blk, s, (const double*)cen, ncb8, d_codebook);
   return ok ? SPH_OK : SPH_ERR_HIP;

@@ -1528,6 +1528,7 @@ __device__ __forceinline__ uint4 pw_decode(uint32_t ra, uint32_t rb, uint32_t rc
 // fp16, rh t - hi is exact (22 bits less their leading 11), and lo adds rl t to it with one
 // rounding, half an ulp of at most 2^-11 of the product.
 __device__ __forceinline__ void rt_split(uint4 t, float rho, uint4& hi, uint4& lo) {
+  asm("" : "+v"(rho));   // taken as it is: one rounding of rh for both of its uses
   const f16 rh = (f16)rho;
   const f16 rl = (f16)(rho - (float)rh);
   const f16x2 a = {rh, rh}, b = {rl, rl};

@@ -106,11 +106,11 @@ bool sph_host_radius_split(const sph_format* fmt, int64_t n, int64_t k, const ui
   if (fmt->vec_dim != SPH_VEC) return false;
   const int64_t ngrp = n * (k / SPH_GROUP);
   const float top = (float)((1 << fmt->radius_bits) - 1);
-  std::vector<float> val(0x7C00);   // values of all finite magnitudes
-  for (int h = 0; h < 0x7C00; ++h) val[h] = f16_value((uint16_t)h);
   for (int64_t i = 0; i < ngrp; ++i) {
-    const float o = val[gmin[i] & 0x7FFF], s = val[gstep[i] & 0x7FFF];
-    if (o != 0.0f && o * 4096.0f < o + top * s) return false;
+    const uint16_t oh = gmin[i] & 0x7FFF, sh = gstep[i] & 0x7FFF;
+    if (oh >= sh || oh == 0) continue;   // an offset of at least the step is above (2^V - 1 <= 255) / 4096 of it
+    const float o = f16_value(oh), s = f16_value(sh);
+    if (o * 4096.0f < o + top * s) return false;
   }
   for (int64_t z = 0; z < (int64_t(1) << fmt->dir_bits); ++z) {
     uint16_t most = 0;   // entries are non-negative, so their bit patterns order them
@@ -118,7 +118,7 @@ bool sph_host_radius_split(const sph_format* fmt, int64_t n, int64_t k, const ui
       const uint16_t c = codebook[z * SPH_VEC + j] & 0x7FFF;
       if (c > most) most = c;
     }
-    if (most != 0 && val[most] < 0.25f) return false;
+    if (most != 0 && most < 0x3400) return false;   // fp16 of 1/4
   }
   return true;
 }
