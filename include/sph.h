@@ -203,9 +203,10 @@ sph_status sph_encode(const sph_format* fmt, int64_t n, int64_t k, const float* 
 /* Device workspace needed by sph_kmeans_codebook for an n x k matrix and n_samples samples
  * (1 <= n_samples <= 2^24): 8 bytes per 8-D vector of the matrix (running sum of squared radii),
  * 76 bytes per sample (direction, assignment, objective part), 12 bytes per sample and codebook
- * split of the assignment (splits x samples stays below about 2^20 + n_samples), and per codebook
- * entry 96 bytes (the fp64 centre and its fp16 words), up to 12 bytes of list positions and 4 bytes for each of up to
- * 64 sample chunks, plus alignment. */
+ * split of the assignment (splits x samples stays below about 2^20 + n_samples), 64 bytes per
+ * codebook entry (the fp64 centre), and 192 bytes per codebook entry and sample chunk (about
+ * 128 / ceil(2^D / 512) chunks, fewer when samples are few) for the counts, the list of samples by
+ * centre and the centres' fp16 words (which take less than that), plus alignment. */
 sph_status sph_kmeans_workspace_bytes(const sph_format* fmt, int64_t n, int64_t k, int64_t n_samples,
                                       size_t* bytes);
 

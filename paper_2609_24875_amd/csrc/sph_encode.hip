@@ -990,6 +990,25 @@ struct KmPlan {
   uint64_t off_cdf, off_bsum, off_ds, off_z, off_opart, off_cen, off_words, off_count, off_hist, off_sbest, off_sidx, total;
 };
 
+// The workspace size that the interface states, per sample, per codebook entry and chunk and per split.
+// The layout of km_plan takes less (its 12 * nsplit bytes per sample, 8 to 12 bytes of counts per
+// entry and 4 per entry and chunk stay within the 12 and 192 bytes of more splits and chunks here);
+// the size stays what callers have sized their buffers by.
+uint64_t stated_bytes(int64_t nvec, int64_t nb, int64_t ns, int64_t ncb) {
+  const int64_t nab = (ns + 1023) / 1024, nr = (ncb + 511) / 512;
+  int64_t sp = std::min<int64_t>((1024 + nab - 1) / nab, std::max<int64_t>(1, ncb / 64));
+  const int64_t per = (ncb + sp - 1) / sp;
+  sp = (ncb + per - 1) / per;
+  int64_t np = std::min<int64_t>((128 + nr - 1) / nr, (ns + kThreads - 1) / kThreads);
+  const int64_t ch = (ns + np - 1) / np;
+  np = (ns + ch - 1) / ch;
+  uint64_t p = 0;
+  for (const int64_t bytes : {nvec * 8, nb * 8, ns * 64, ns * 4, (ns + kThreads - 1) / kThreads * 8, ncb * 64, np * ncb * 192,
+                              sp * ns * 8, sp * ns * 4})
+    p = align256(p + (uint64_t)bytes);
+  return p;
+}
+
 KmPlan km_plan(const sph_format* fmt, int64_t n, int64_t k, int64_t ns) {
   KmPlan P{};
   P.nvec = n * (k / SPH_VEC);
@@ -1032,7 +1051,7 @@ KmPlan km_plan(const sph_format* fmt, int64_t n, int64_t k, int64_t ns) {
   p = align256(p + (uint64_t)P.nsplit * ns * 8);
   P.off_sidx = p;    // likewise the samples' ranks
   p = align256(p + (uint64_t)P.nsplit * ns * 4);
-  P.total = p;
+  P.total = std::max(p, stated_bytes(P.nvec, P.nb, ns, P.ncb));
   return P;
 }
 
