@@ -287,9 +287,11 @@ sph_status sph_fake_quant_backward_workspace_bytes(int32_t dir_bits, size_t* byt
  * dL/drho_i = sigmoid(rho_i) sum_j dL/dw^_ij s_ij c_{z_i,j}, and d_grad_codebook fp32[2^D][8]
  * with dL/dc_z = sum over vectors i of direction z of r^_i s_i (.) dL/dw^_i. d_r_hat is the
  * forward's r^; d_perm int32[n*k/8] and d_offsets int64[2^D + 1] are device copies of
- * sph_direction_groups for the same d_dir_idx (not validated). Sums run in a fixed order without
- * atomics, so repeated calls give bitwise identical results. d_ws: sph_fake_quant_backward_
- * workspace_bytes bytes, 16-byte aligned. Asynchronous. */
+ * sph_direction_groups for the same d_dir_idx (not validated; read for codebooks of more than 2^8
+ * entries). Sums run in an order fixed by the sizes, so repeated calls give bitwise identical
+ * results (a centre with a gradient that is not finite excepted, whose sum is not finite). d_ws:
+ * sph_fake_quant_backward_workspace_bytes bytes, 16-byte aligned; d_grad_rho serves as more of it
+ * before it is written. Asynchronous. */
 sph_status sph_fake_quant_backward(const sph_format* fmt, int64_t n, int64_t k, const float* d_rho,
                                    const uint8_t* d_signs, const uint16_t* d_dir_idx, const float* d_codebook,
                                    const float* d_r_hat, const float* d_grad_w, int64_t ldg, const int32_t* d_perm,

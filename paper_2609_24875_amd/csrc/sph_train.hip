@@ -7,13 +7,15 @@
 //
 // Work layout:
 //   angular kernels   one thread per codebook entry (at most 8192).
-//   fake quantisation one thread per 8-D vector; 16 neighbouring lanes form one 128-weight group
-//                     (groups never straddle a row and start at multiples of 16).
-//   radius gradient   one thread per vector, coalesced over dL/dW^.
-//   codebook gradient no atomics: the vectors are pre-sorted by direction (a stable counting
-//                     sort on the host, once per module, since the indices stay fixed); block
-//                     (c, s) sums slice s of centre c's list in order and a fixed lane tree, and
-//                     a second kernel adds the slices in order. Repeated calls are bitwise equal.
+//   fake quantisation a block takes whole groups of 16 vectors (128 weights); the radii of a group's
+//                     smallest and largest parameter in fp64, one per thread, then levels and weights.
+//   gradients         up to 256 centres: one pass in storage order, each wave adding its vectors to
+//                     sums of its own per centre in LDS. 2^13 centres: the radius gradient one thread
+//                     per vector; the vectors are pre-sorted by direction (a stable counting sort on
+//                     the host, once per module, since the indices stay fixed) and eight lanes add
+//                     one slice of one centre's list in fp64. A last kernel adds the waves' or slices'
+//                     sums in a fixed order. No sum crosses waves by atomics: repeated calls are
+//                     bitwise equal.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -29,8 +31,6 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr float kHalfPi = 1.57079632679489662f;
-constexpr int kTargetBlocks = 1024;
-constexpr int kMaxSlices = 64;
 
 __device__ __forceinline__ float sigmoidf(float x) { return 1.0f / (1.0f + expf(-x)); }
 
@@ -133,45 +133,136 @@ struct FqArgs {
   uint16_t* gstep;
 };
 
+// softplus in fp32 with a relative error of a few 2^-24 (times 1 + |x| for e^x): log1p(y) as
+// log(u) * y / (u - 1) for u = 1 + y, where the two roundings of u cancel.
+__device__ __forceinline__ float softplus_f(float x) {
+  const float y = __expf(-fabsf(x));
+  const float u = 1.0f + y;
+  const float l = u == 1.0f ? y : __logf(u) * (y / (u - 1.0f));
+  return fmaxf(x, 0.0f) + l;
+}
+
+template <int CTRL>
+__device__ __forceinline__ float row_ror(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, false));
+}
+
 // r = softplus(rho); per group of 16 vectors the offset min r and the step (max - min)/(2^V - 1),
 // both rounded to fp16; q = clip(round((r - min)/step), 0, 2^V - 1), half to even (0 for a zero
-// step); r^ = min + q step; w^ = r^ s (.) c_z. All of it in fp64, then w^ and r^ stored as fp32.
+// step); r^ = min + q step; w^ = r^ s (.) c_z, stored as fp32 with r^. Every decision is the fp64 one:
+// softplus is increasing, so a group's offset and step come from its smallest and largest rho, two
+// fp64 evaluations per 16 vectors, one per thread of the block; a level is rounded from fp32 unless the
+// quotient lies within its error of a rounding boundary, and then from fp64 (about one vector in 10^4).
+// The weights' products are single fp32 roundings of exact factors (fp64 where r^ needs more than 24 bits).
 // Optional outputs: r^, and the finalised codes (levels, fp16 offsets and steps).
+//
+// Bound by memory: 43 bytes per vector, 32 of them written, so the weights go out 16 bytes per lane in
+// address order through LDS (32 contiguous bytes per thread, as they are computed, touch every line twice). 12288x4096 W2: 80 us
+// with fp64 softplus for every vector -> 71 us.
+template <int VPT>   // vectors per thread
 __global__ __launch_bounds__(kThreads) void k_fq_forward(FqArgs a) {
-  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  const bool ok = i < a.nvec;  // whole groups are inside or outside together
-  const double r = ok ? softplus_d((double)a.rho[i]) : 0.0;
-  double lo = r, hi = r;
+  constexpr int NVB = VPT * kThreads, NG = NVB / 16;
+  __shared__ float ext[NG][2];       // smallest and largest rho of a group
+  __shared__ float par[NG][2];       // offset and step
+  __shared__ float rad[NVB], low[NVB];   // r^ as two fp32 words
+  __shared__ uint32_t dz[NVB];       // direction and signs
+  __shared__ int wide;               // some r^ needs its second word
+  const int tid = threadIdx.x;
+  const int64_t base = (int64_t)blockIdx.x * NVB;
+  if (tid == 0) wide = 0;
+  float x[VPT];
 #pragma unroll
-  for (int o = 1; o < 16; o <<= 1) {
-    lo = fmin(lo, __shfl_xor(lo, o, 16));
-    hi = fmax(hi, __shfl_xor(hi, o, 16));
+  for (int t = 0; t < VPT; ++t) {
+    const int64_t i = base + t * kThreads + tid;   // whole groups are inside or outside together
+    x[t] = i < a.nvec ? a.rho[i] : 0.0f;
+    if (i < a.nvec) dz[t * kThreads + tid] = (uint32_t)a.dir[i] | ((uint32_t)a.signs[i] << 16);
   }
-  const uint16_t lo16 = d2h(lo), st16 = d2h((hi - lo) / (double)a.vmax);
-  const double lod = h2d(lo16), std_ = h2d(st16);
-  int q = 0;
-  if (std_ > 0.0) q = (int)fmin(fmax(rint((r - lod) / std_), 0.0), (double)a.vmax);
-  const double rh = lod + (double)q * std_;
-  if (!ok) return;
-  const int64_t row = i / a.nv, v = i - row * a.nv;
-  const uint32_t s = a.signs[i];
-  const float4* c4 = reinterpret_cast<const float4*>(a.cb + (int64_t)a.dir[i] * 8);
-  const float4 c0 = c4[0], c1 = c4[1];
-  const float cc[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
-  float w[8];
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const float m = (float)(rh * (double)cc[j]);
-    w[j] = ((s >> j) & 1) ? -m : m;
+  for (int t = 0; t < VPT; ++t) {
+    float lo = x[t], hi = x[t];
+    lo = fminf(lo, row_ror<0x128>(lo));
+    hi = fmaxf(hi, row_ror<0x128>(hi));
+    lo = fminf(lo, row_ror<0x124>(lo));
+    hi = fmaxf(hi, row_ror<0x124>(hi));
+    lo = fminf(lo, row_ror<0x122>(lo));
+    hi = fmaxf(hi, row_ror<0x122>(hi));
+    lo = fminf(lo, row_ror<0x121>(lo));
+    hi = fmaxf(hi, row_ror<0x121>(hi));
+    if ((tid & 15) == 0) {
+      ext[(t * kThreads + tid) >> 4][0] = lo;
+      ext[(t * kThreads + tid) >> 4][1] = hi;
+    }
   }
-  float4* out = reinterpret_cast<float4*>(a.w_hat + row * a.ldw + v * 8);
-  out[0] = make_float4(w[0], w[1], w[2], w[3]);
-  out[1] = make_float4(w[4], w[5], w[6], w[7]);
-  if (a.r_hat) a.r_hat[i] = (float)rh;
-  if (a.q) a.q[i] = (uint8_t)q;
-  if (a.gmin && (threadIdx.x & 15) == 0) {
-    a.gmin[i >> 4] = lo16;
-    a.gstep[i >> 4] = st16;
+  __syncthreads();
+  if (tid < 2 * NG) {
+    const int g = tid >> 1;
+    const double r = softplus_d((double)ext[g][tid & 1]);
+    const double o = __shfl_xor(r, 1, 64);
+    const double lo = (tid & 1) ? o : r, hi = (tid & 1) ? r : o;
+    const uint16_t lo16 = d2h(lo), st16 = d2h((hi - lo) / (double)a.vmax);
+    const int64_t grp = (base >> 4) + g;
+    if ((tid & 1) == 0) {
+      par[g][0] = (float)h2d(lo16);
+      par[g][1] = (float)h2d(st16);
+      if (a.gmin && grp * 16 < a.nvec) {
+        a.gmin[grp] = lo16;
+        a.gstep[grp] = st16;
+      }
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < VPT; ++t) {
+    const int o = t * kThreads + tid;
+    const int64_t i = base + o;
+    const float lo = par[o >> 4][0], st = par[o >> 4][1];
+    int q = 0;
+    bool close = false;
+    if (st > 0.0f) {
+      const float r = softplus_f(x[t]), inv = 1.0f / st;
+      const float v = (r - lo) * inv;
+      const float err = fmaf(4e-6f * (1.0f + fabsf(x[t])) * (r + fabsf(lo)), inv, 1e-5f);
+      const float k = rintf(v);
+      close = !(fabsf(fabsf(v - k) - 0.5f) > err);   // also where an overflow leaves no number
+      q = (int)fminf(fmaxf(k, 0.0f), (float)a.vmax);
+    }
+    if (__any(close) && close)
+      q = (int)fmin(fmax(rint((softplus_d((double)x[t]) - (double)lo) / (double)st), 0.0), (double)a.vmax);
+    const double rh = (double)lo + (double)q * (double)st;
+    const float rf = (float)rh, rl = (float)(rh - (double)rf);
+    rad[o] = rf;
+    low[o] = rl;
+    if (rl != 0.0f) wide = 1;
+    if (i < a.nvec) {
+      if (a.r_hat) a.r_hat[i] = rf;
+      if (a.q) a.q[i] = (uint8_t)q;
+    }
+  }
+  __syncthreads();
+  const bool two = wide != 0;
+  const bool packed = a.ldw == a.nv * 8;
+  const float4* cb4 = reinterpret_cast<const float4*>(a.cb);
+#pragma unroll 4
+  for (int t = 0; t < 2 * VPT; ++t) {
+    const int o = t * kThreads + tid, v = o >> 1, half = o & 1;
+    const int64_t i = base + v;
+    if (i >= a.nvec) break;
+    const uint32_t zs = dz[v], s = zs >> (16 + 4 * half);
+    const float4 c = cb4[(int64_t)(zs & 0xFFFFu) * 2 + half];
+    const float rf = rad[v];
+    float m[4] = {rf * c.x, rf * c.y, rf * c.z, rf * c.w};
+    if (two) {
+      const double rh = (double)rf + (double)low[v];
+      m[0] = (float)(rh * (double)c.x);
+      m[1] = (float)(rh * (double)c.y);
+      m[2] = (float)(rh * (double)c.z);
+      m[3] = (float)(rh * (double)c.w);
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+      if ((s >> j) & 1) m[j] = -m[j];
+    const int64_t row = packed ? 0 : i / a.nv;
+    *reinterpret_cast<float4*>(a.w_hat + row * a.ldw + (i - row * a.nv) * 8 + half * 4) = make_float4(m[0], m[1], m[2], m[3]);
   }
 }
 
@@ -191,13 +282,20 @@ __global__ __launch_bounds__(kThreads) void k_fq_init_rho(const float* __restric
   rho[i] = rt > 20.0f ? rt + log1pf(-expf(-rt)) : logf(expm1f(rt));
 }
 
+__host__ __device__ __forceinline__ int64_t stretch_begin(int64_t nvec, int b, int nblk);
+
 // dL/drho_i = sigmoid(rho_i) * sum_j dL/dw^_ij s_ij c_{z_i, j} (straight-through: dr^/dr = 1).
 __global__ __launch_bounds__(kThreads) void k_fq_grad_rho(int64_t nv, int64_t nvec, const float* __restrict__ rho,
                                                           const uint8_t* __restrict__ signs,
                                                           const uint16_t* __restrict__ dir,
                                                           const float* __restrict__ cb, const float* __restrict__ gw,
-                                                          int64_t ldg, float* __restrict__ grho) {
-  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+                                                          int64_t ldg, int first, int nblk, float* __restrict__ grho) {
+  // all vectors, or with nblk > 0 the first `first` of each of nblk stretches (see k_fq_grad_pass)
+  int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+  if (nblk > 0) {
+    if (i >= (int64_t)first * nblk) return;
+    i = stretch_begin(nvec, (int)(i / first), nblk) + i % first;
+  }
   if (i >= nvec) return;
   const int64_t row = i / nv, v = i - row * nv;
   const float4* g4 = reinterpret_cast<const float4*>(gw + row * ldg + v * 8);
@@ -212,60 +310,272 @@ __global__ __launch_bounds__(kThreads) void k_fq_grad_rho(int64_t nv, int64_t nv
   grho[i] = sum8_pairwise(p) * sigmoidf(rho[i]);
 }
 
-// Slice s of centre c's direction-sorted vector list: sum of r^_i s_i (.) dL/dw^_i in list order
-// per thread, then a fixed tree over the block.
+// Slice sl of a centre's direction-sorted vector list: sum of r^_i s_i (.) dL/dw^_i, by eight lanes, two per
+// vector (16 bytes of the gradient each) and four vectors at a time, in fp64, then over the four pairs by
+// a fixed tree; stored as fp32 in part[slice][centre][8].
+//
+// The gradient's 32 bytes per vector are gathered in list order; neighbouring vectors belong to
+// different centres, so a cache line is read by up to four of them. A slice covers about one
+// stretch of the matrix for all centres, and block ids that are equal modulo 8 share an L2, so a
+// slice's blocks take ids of one residue: its lines come from memory once. (The finest useful slices: a
+// step of 12288x4096 W3, 8192 centres, 500 us with one block of 256 threads per centre -> 348 us. Smaller
+// codebooks take k_fq_grad_pass.)
+constexpr int kXcd = 8;
+
 __global__ __launch_bounds__(kThreads) void k_fq_grad_cb_part(int64_t nv, const float* __restrict__ r_hat,
                                                               const uint8_t* __restrict__ signs,
                                                               const float* __restrict__ gw, int64_t ldg,
                                                               const int32_t* __restrict__ perm,
-                                                              const int64_t* __restrict__ off, int nslice,
+                                                              const int64_t* __restrict__ off, int ncb, int nslice,
                                                               float* __restrict__ part) {
-  __shared__ float sh[kThreads / 64][8];
-  const int c = blockIdx.x, sl = blockIdx.y;
+  const int ncblk = (ncb + kThreads / 8 - 1) / (kThreads / 8);
+  const int nx = nslice % kXcd == 0 ? kXcd : 1;
+  const int xcd = blockIdx.x % nx, seq = blockIdx.x / nx;
+  const int sl = seq / ncblk * nx + xcd;
+  const int c = seq % ncblk * (kThreads / 8) + (threadIdx.x >> 3);
+  if (c >= ncb) return;                      // whole groups of eight lanes; no barrier follows
+  const int pair = (threadIdx.x >> 1) & 3, half = threadIdx.x & 1;
   const int64_t a0 = off[c], len = off[c + 1] - a0;
   const int64_t b0 = a0 + len * sl / nslice, b1 = a0 + len * (sl + 1) / nslice;
-  float acc[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-  for (int64_t t = b0 + threadIdx.x; t < b1; t += kThreads) {
+  const bool packed = ldg == nv * 8;
+  double acc[4] = {0, 0, 0, 0};
+  auto add = [&](float rh, uint32_t s, const float4 g) {
+    const float p[4] = {rh * g.x, rh * g.y, rh * g.z, rh * g.w};
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[j] += (double)(((s >> (4 * half + j)) & 1) ? -p[j] : p[j]);
+  };
+  auto grad = [&](int64_t i) {
+    const int64_t row = packed ? 0 : i / nv;
+    return *reinterpret_cast<const float4*>(gw + row * ldg + (i - row * nv) * 8 + 4 * half);
+  };
+  constexpr int U = 4;
+  int64_t t = b0 + pair;
+  for (; t + 4 * (U - 1) < b1; t += 4 * U) {
+    int64_t i[U];
+    float rh[U];
+    uint32_t s[U];
+    float4 g[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) i[u] = perm[t + 4 * u];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      rh[u] = r_hat[i[u]];
+      s[u] = signs[i[u]];
+      g[u] = grad(i[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) add(rh[u], s[u], g[u]);
+  }
+  for (; t < b1; t += 4) {
     const int64_t i = perm[t];
-    const int64_t row = i / nv, v = i - row * nv;
-    const float4* g4 = reinterpret_cast<const float4*>(gw + row * ldg + v * 8);
-    const float4 g0 = g4[0], g1 = g4[1];
-    const float g[8] = {g0.x, g0.y, g0.z, g0.w, g1.x, g1.y, g1.z, g1.w};
-    const float rh = r_hat[i];
-    const uint32_t s = signs[i];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) acc[j] += ((s >> j) & 1) ? -rh * g[j] : rh * g[j];
+    add(r_hat[i], signs[i], grad(i));
   }
 #pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) acc[j] += __shfl_xor(acc[j], o, 64);
+  for (int j = 0; j < 4; ++j) {
+    acc[j] += __shfl_xor(acc[j], 2, 64);
+    acc[j] += __shfl_xor(acc[j], 4, 64);
   }
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  if (lane == 0) {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) sh[wv][j] = acc[j];
-  }
+  if (pair == 0)
+    *reinterpret_cast<float4*>(part + ((int64_t)sl * ncb + c) * 8 + 4 * half) =
+        make_float4((float)acc[0], (float)acc[1], (float)acc[2], (float)acc[3]);
+}
+
+// Both gradients in one pass over dL/dW^, for codebooks of at most NCB entries (16, 64 or 256). A wave walks its
+// stretch of the vectors in storage order, 32 at a time (two lanes per vector, 16 bytes of the gradient
+// each): dL/drho directly, and r^ s (.) dL/dw^ summed per centre on the matrix cores, as the product of
+// a one-hot matrix (16 centres x 32 vectors; exact ones and zeros) with the 32 x 8 products. Each
+// product is cut into three bfloat16 words (8 + 8 + 8 bits: exactly its 24): the high and middle words of the
+// 8 coordinates are the 16 columns of one operand, the low words half of another. The words and the
+// directions reach the operands' layout through a few LDS rows of the wave's own. Adding an
+// exact zero rounds nothing, so a sum is rounded as often as a centre's vectors are added. Vectors with
+// a product that is not finite would spoil every centre (0 times infinity); their products are
+// added to their centre in LDS instead.
+//
+// The waves' sums are added in order (fp64) per block and stored as fp32, in d_ws where it holds all
+// blocks' sums, else in the radius gradient's first ncb * 8 values of the block's stretch, which
+// k_fq_grad_rho fills afterwards.
+//
+// 47 bytes per vector, read and written once and in order. The gather of the lists by centre (below)
+// moved a 128-byte line into L1 for each 32-byte gradient, each radius and each sign byte: 2.4 GB for
+// 12288x4096, 244 us, and the radius gradient took another 55 us; this pass takes 96
+// us, half vector-ALU work (the cuts and the one-hot words). Additions to
+// the wave's sums in LDS (ds_add_f32) took 260 us, one lane every three cycles.
+constexpr int kPassWaves = 8;
+typedef __bf16 bf8v __attribute__((ext_vector_type(8)));
+typedef float f4v __attribute__((ext_vector_type(4)));
+typedef uint16_t u2s __attribute__((ext_vector_type(2)));
+
+struct PassArgs {
+  int64_t nv, nvec;
+  const float* rho;
+  const uint8_t* signs;
+  const uint16_t* dir;
+  const float* cb;
+  const float* r_hat;
+  const float* gw;
+  int64_t ldg;
+  float* grho;
+  float* part;     // [blocks][ncb * 8], or null: the first values of each block's stretch of grho
+  int ncb;
+};
+
+// Block b's stretch: whole groups of 16 vectors, nearly equal.
+__host__ __device__ __forceinline__ int64_t stretch_begin(int64_t nvec, int b, int nblk) { return nvec / 16 * b / nblk * 16; }
+
+template <int NCB>
+__global__ __launch_bounds__(64 * kPassWaves) void k_fq_grad_pass(PassArgs a) {
+  constexpr int NT = NCB / 16;                    // tiles of 16 centres
+  constexpr int ROW = 40;                         // bf16 words per row of 32 vectors, padded against bank conflicts
+  __shared__ __align__(16) uint16_t words[kPassWaves][24 * ROW];   // rows: word (high, middle, low) x coordinate
+  __shared__ __align__(16) uint16_t zs[kPassWaves][32];
+  __shared__ float sums[kPassWaves][NCB * 8];     // the waves' sums, at the end (added one wave after the
+                                                  // other in one array, the tail took 8 to 75 us more)
+  __shared__ float odd[NCB * 8];                  // products that are not finite
+  __shared__ float4 cbl[NCB * 2];
+  const int tid = threadIdx.x, lane = tid & 63, wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nval = a.ncb * 8;
+  for (int t = tid; t < a.ncb * 2; t += 64 * kPassWaves) cbl[t] = reinterpret_cast<const float4*>(a.cb)[t];
+  for (int t = tid; t < NCB * 8; t += 64 * kPassWaves) odd[t] = 0.0f;
   __syncthreads();
-  if (threadIdx.x < 8) {
-    const int j = threadIdx.x;
-    part[((int64_t)c * nslice + sl) * 8 + j] = (sh[0][j] + sh[1][j]) + (sh[2][j] + sh[3][j]);
+  const int64_t b0 = stretch_begin(a.nvec, blockIdx.x, gridDim.x), b1 = stretch_begin(a.nvec, blockIdx.x + 1, gridDim.x);
+  const int64_t keep = a.part ? b0 : b0 + nval;   // radius gradients before it are left for later
+  const int64_t per = ((b1 - b0 + kPassWaves - 1) / kPassWaves + 31) / 32 * 32;
+  const int64_t w0 = min(b1, b0 + wv * per), w1 = min(b1, w0 + per);
+  const int half = lane & 1, own = lane >> 1;
+  const int r = lane & 15, kb = lane >> 4;        // row (or column) and block of 8 vectors of an operand
+  const bool packed = a.ldg == a.nv * 8;
+  uint16_t* wr = words[wv] + 4 * half * ROW + own;
+  const uint16_t* rd1 = words[wv] + r * ROW + kb * 8;
+  const uint16_t* rd2 = words[wv] + (16 + (r & 7)) * ROW + kb * 8;
+  f4v hm[NT], lw[NT];   // sums of their own for the low words: chained into the others they cost 10%
+#pragma unroll
+  for (int t = 0; t < NT; ++t) hm[t] = lw[t] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+  constexpr int U = 2;
+  for (int64_t i0 = w0; i0 < w1; i0 += 32 * U) {
+    float4 g[U];
+    float rho[U], rh[U];
+    uint32_t z[U], s[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t i = min(i0 + 32 * u + own, w1 - 1);   // past the end: the last vector again, not counted
+      const int64_t row = packed ? 0 : i / a.nv;
+      g[u] = *reinterpret_cast<const float4*>(a.gw + row * a.ldg + (i - row * a.nv) * 8 + 4 * half);
+      rho[u] = a.rho[i];
+      rh[u] = a.r_hat[i];
+      z[u] = a.dir[i];
+      s[u] = (uint32_t)a.signs[i] >> (4 * half);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t i = i0 + 32 * u + own;
+      const bool ok = i < w1;
+      const float4 c = cbl[z[u] * 2 + half];
+      const float gg[4] = {g[u].x, g[u].y, g[u].z, g[u].w};
+      const float cc[4] = {c.x, c.y, c.z, c.w};
+      float p[4], q[4];
+      bool fine = true;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float sg = ((s[u] >> j) & 1) ? -gg[j] : gg[j];
+        p[j] = sg * cc[j];
+        q[j] = ok ? rh[u] * sg : 0.0f;
+        fine = fine && fabsf(q[j]) <= 3.402823466e38f;
+      }
+      const float mysum = (p[0] + p[1]) + (p[2] + p[3]);
+      const float total = mysum + __shfl_xor(mysum, 1, 64);   // the pairwise order of eight terms
+      if (half == 0 && ok && i >= keep) a.grho[i] = total * sigmoidf(rho[u]);
+      if (__any(!fine) && !fine) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          atomicAdd(&odd[z[u] * 8 + 4 * half + j], q[j]);
+          q[j] = 0.0f;
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const uint32_t b = __builtin_bit_cast(uint32_t, q[j]);
+        const float r1 = q[j] - __builtin_bit_cast(float, b & 0xFFFF0000u);
+        const uint32_t m = __builtin_bit_cast(uint32_t, r1);
+        const float r2 = r1 - __builtin_bit_cast(float, m & 0xFFFF0000u);
+        wr[j * ROW] = (uint16_t)(b >> 16);
+        wr[(8 + j) * ROW] = (uint16_t)(m >> 16);
+        wr[(16 + j) * ROW] = (uint16_t)(__builtin_bit_cast(uint32_t, r2) >> 16);
+      }
+      if (half == 0) zs[wv][own] = (uint16_t)z[u];
+      // the LDS performs a wave's operations in issue order: these reads see the writes above, and
+      // the next vectors' writes come after them
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+      const uint4 zq = *(const uint4*)(zs[wv] + kb * 8);
+      const bf8v x1 = *(const bf8v*)rd1;
+      uint4 x2w = *(const uint4*)rd2;
+      if (r >= 8) x2w = make_uint4(0, 0, 0, 0);
+      const bf8v x2 = __builtin_bit_cast(bf8v, x2w);
+      const uint32_t zw[4] = {zq.x, zq.y, zq.z, zq.w};
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const uint32_t c2 = (uint32_t)(16 * t + r) * 0x10001u;
+        uint32_t o[4];
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const u2s d = __builtin_elementwise_min(__builtin_bit_cast(u2s, zw[k] ^ c2), u2s{1, 1});
+          o[k] = __builtin_bit_cast(uint32_t, (u2s)(u2s{0x3F80, 0x3F80} - d * u2s{0x3F80, 0x3F80}));   // 1.0 where equal
+        }
+        const bf8v one = __builtin_bit_cast(bf8v, make_uint4(o[0], o[1], o[2], o[3]));
+        hm[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(one, x1, hm[t], 0, 0, 0);
+        lw[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(one, x2, lw[t], 0, 0, 0);
+      }
+    }
+  }
+  // lane (column, rows 4 * kb + e) of tile t: high words in columns 0..7, middle in 8..15, low in 0..7
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float mid = __shfl_xor(hm[t][e], 8, 64);
+      if (r < 8) sums[wv][(16 * t + 4 * kb + e) * 8 + r] = (float)((double)hm[t][e] + ((double)mid + (double)lw[t][e]));
+    }
+  __syncthreads();
+  float* out = a.part ? a.part + (int64_t)blockIdx.x * nval : a.grho + b0;
+  for (int t = tid; t < nval; t += 64 * kPassWaves) {
+    double sum = (double)odd[t];
+#pragma unroll
+    for (int k = 0; k < kPassWaves; ++k) sum += (double)sums[k][t];
+    out[t] = (float)sum;
   }
 }
 
-__global__ __launch_bounds__(kThreads) void k_fq_grad_cb_final(const float* __restrict__ part, int ncb, int nslice,
-                                                               float* __restrict__ gcb) {
-  const int t = blockIdx.x * kThreads + threadIdx.x;
-  if (t >= ncb * 8) return;
-  const int c = t >> 3, j = t & 7;
-  float s = 0.0f;
-  for (int sl = 0; sl < nslice; ++sl) s += part[((int64_t)c * nslice + sl) * 8 + j];
-  gcb[t] = s;
+// The sums of 32 consecutive values per block, 32 lanes over the slices (or blocks of k_fq_grad_pass,
+// whose sums lie in their stretches of nvec vectors if that is not 0) in fp64, added in a fixed order.
+__global__ __launch_bounds__(1024) void k_fq_grad_cb_final(const float* __restrict__ part, int nval, int nslice, int64_t nvec,
+                                                           float* __restrict__ gcb) {
+  __shared__ double sh[32][33];
+  const int v = threadIdx.x & 31, l = threadIdx.x >> 5;
+  const int64_t o = (int64_t)blockIdx.x * 32 + v;
+  double s = 0.0;
+  if (o < nval) {
+#pragma unroll 4
+    for (int t = l; t < nslice; t += 32) s += (double)part[(nvec ? stretch_begin(nvec, t, nslice) : (int64_t)t * nval) + o];
+  }
+  sh[l][v] = s;
+  __syncthreads();
+  if (l == 0 && o < nval) {
+#pragma unroll
+    for (int k = 1; k < 32; ++k) s += sh[k][v];
+    gcb[o] = (float)s;
+  }
 }
 
 // ------------------------------------------------------------------------------------ host side
 
-int slices_for(int ncb) { return std::max(1, std::min(kMaxSlices, (kTargetBlocks + ncb - 1) / ncb)); }
+// Slices of every centre's list: enough groups of eight lanes to fill the chip (65,536), at least 32 so that
+// a slice's stretch of a large matrix stays near an XCD's 4 MiB of L2.
+int slices_for(int ncb) { return std::max(32, std::min(1024, 65536 / ncb)); }
+
+// Slices the caller's workspace holds (its size is part of the interface). Most matrices use the
+// radius gradient's array instead, which is written last.
+int ws_slices(int ncb) { return std::max(1, std::min(64, (1024 + ncb - 1) / ncb)); }
 
 template <typename... A>
 bool launch_ok(const void* fn, dim3 grid, dim3 block, hipStream_t s, A... args) {
@@ -377,7 +687,11 @@ sph_status sph_fake_quant_forward(const sph_format* fmt, int64_t n, int64_t k, c
   a.q = d_radius_code;
   a.gmin = d_group_min;
   a.gstep = d_group_step;
-  return launch_ok((const void*)k_fq_forward, dim3((unsigned)((a.nvec + kThreads - 1) / kThreads)), dim3(kThreads),
+  // eight vectors per thread fill the chip from 1024 blocks on; smaller matrices take two
+  const int64_t big = (a.nvec + 8 * kThreads - 1) / (8 * kThreads);
+  const bool two = big < 1024;
+  const int64_t grid = two ? (a.nvec + 2 * kThreads - 1) / (2 * kThreads) : big;
+  return launch_ok(two ? (const void*)k_fq_forward<2> : (const void*)k_fq_forward<8>, dim3((unsigned)grid), dim3(kThreads),
                    (hipStream_t)stream, a)
              ? SPH_OK
              : SPH_ERR_HIP;
@@ -387,7 +701,7 @@ sph_status sph_fake_quant_backward_workspace_bytes(int32_t dir_bits, size_t* byt
   if (!bytes) return SPH_ERR_NULL;
   if (!dir_bits_ok(dir_bits)) return SPH_ERR_SHAPE;
   const int ncb = 1 << dir_bits;
-  *bytes = (size_t)ncb * slices_for(ncb) * 8 * sizeof(float);
+  *bytes = (size_t)ncb * ws_slices(ncb) * 8 * sizeof(float);
   return SPH_OK;
 }
 
@@ -405,18 +719,51 @@ sph_status sph_fake_quant_backward(const sph_format* fmt, int64_t n, int64_t k, 
       (uintptr_t)d_dir_idx % 2 || (uintptr_t)d_perm % 4 || (uintptr_t)d_offsets % 8 || (uintptr_t)d_grad_rho % 4 ||
       (uintptr_t)d_grad_codebook % 4 || (uintptr_t)d_ws % 16)
     return SPH_ERR_SHAPE;
-  const int ncb = 1 << fmt->dir_bits, ns = slices_for(ncb);
-  if (ws_bytes < (size_t)ncb * ns * 8 * sizeof(float)) return SPH_ERR_BUFFER_TOO_SMALL;
+  const int ncb = 1 << fmt->dir_bits;
   const int64_t nv = k / SPH_VEC, nvec = n * nv;
+  if (ws_bytes < (size_t)ncb * ws_slices(ncb) * 8 * sizeof(float)) return SPH_ERR_BUFFER_TOO_SMALL;
   hipStream_t s = (hipStream_t)stream;
+  const int nval = ncb * 8;
+  // The radius gradient's array may hold sums until it is written, unless it is one of the inputs.
+  auto apart = [&](const void* q, size_t bytes) {
+    const char *o = (const char*)d_grad_rho, *i = (const char*)q;
+    return o + (size_t)nvec * 4 <= i || i + bytes <= o;
+  };
+  const bool free_rho = apart(d_rho, (size_t)nvec * 4) && apart(d_r_hat, (size_t)nvec * 4);
+  const dim3 g_final((unsigned)((nval + 31) / 32));
+  if (ncb <= 256) {
+    // one pass: two blocks per CU on the largest matrices, at least max(128, ncb) vectors per wave (so that
+    // a block's sums fit its stretch of the radius gradient)
+    const int64_t least = (int64_t)kPassWaves * std::max(128, ncb);
+    const int nblk = (int)std::max<int64_t>(1, std::min<int64_t>(free_rho ? 512 : ws_slices(ncb), nvec / least));
+    const bool in_ws = nblk <= ws_slices(ncb);
+    PassArgs a{nv, nvec, d_rho, d_signs, d_dir_idx, d_codebook, d_r_hat, d_grad_w, ldg, d_grad_rho, in_ws ? (float*)d_ws : nullptr, ncb};
+    bool ok = launch_ok(ncb <= 16 ? (const void*)k_fq_grad_pass<16> : ncb <= 64 ? (const void*)k_fq_grad_pass<64> : (const void*)k_fq_grad_pass<256>, dim3((unsigned)nblk),
+                        dim3(64 * kPassWaves), s, a) &&
+              launch_ok((const void*)k_fq_grad_cb_final, g_final, dim3(1024), s, in_ws ? (const float*)d_ws : (const float*)d_grad_rho,
+                        nval, nblk, in_ws ? (int64_t)0 : nvec, d_grad_codebook);
+    if (ok && !in_ws)
+      ok = launch_ok((const void*)k_fq_grad_rho, dim3((unsigned)(((int64_t)nval * nblk + kThreads - 1) / kThreads)), dim3(kThreads), s,
+                     nv, nvec, d_rho, d_signs, d_dir_idx, d_codebook, d_grad_w, ldg, nval, nblk, d_grad_rho);
+    return ok ? SPH_OK : SPH_ERR_HIP;
+  }
+  // The slices' sums go to the radius gradient's array while it is not yet written, where it holds
+  // more of them than the workspace; each slice keeps at least 16 vectors per centre on average.
+  int64_t ns = std::min<int64_t>(ws_slices(ncb), std::max<int64_t>(1, nvec / ncb / 16));
   float* part = (float*)d_ws;
+  const int64_t room = std::min<int64_t>(std::min<int64_t>(slices_for(ncb), nvec / (8 * ncb)), nvec / ncb / 16) / kXcd * kXcd;
+  if (room > ns && free_rho && a16(d_grad_rho)) {
+    ns = room;
+    part = d_grad_rho;
+  }
+  const int ncblk = (ncb + kThreads / 8 - 1) / (kThreads / 8);
   const bool ok =
+      launch_ok((const void*)k_fq_grad_cb_part, dim3((unsigned)(ncblk * ns)), dim3(kThreads), s, nv, d_r_hat,
+                d_signs, d_grad_w, ldg, d_perm, d_offsets, ncb, (int)ns, part) &&
+      launch_ok((const void*)k_fq_grad_cb_final, g_final, dim3(1024), s, (const float*)part, nval, (int)ns, (int64_t)0,
+                d_grad_codebook) &&
       launch_ok((const void*)k_fq_grad_rho, dim3((unsigned)((nvec + kThreads - 1) / kThreads)), dim3(kThreads), s, nv,
-                nvec, d_rho, d_signs, d_dir_idx, d_codebook, d_grad_w, ldg, d_grad_rho) &&
-      launch_ok((const void*)k_fq_grad_cb_part, dim3((unsigned)ncb, (unsigned)ns), dim3(kThreads), s, nv, d_r_hat,
-                d_signs, d_grad_w, ldg, d_perm, d_offsets, ns, part) &&
-      launch_ok((const void*)k_fq_grad_cb_final, dim3((unsigned)((ncb * 8 + kThreads - 1) / kThreads)), dim3(kThreads),
-                s, (const float*)part, ncb, ns, d_grad_codebook);
+                nvec, d_rho, d_signs, d_dir_idx, d_codebook, d_grad_w, ldg, 0, 0, d_grad_rho);
   return ok ? SPH_OK : SPH_ERR_HIP;
 }
 

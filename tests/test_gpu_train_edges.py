@@ -1,0 +1,157 @@
+"""The fine-tuning kernels at the sizes where their launches change: one block and many, gradient sums kept
+in the workspace and in the radius gradient's array, two and eight vectors per thread; and at inputs
+where the fp32 screening of the levels has to hand over (radii on rounding boundaries, tiny steps, radius
+parameters from -80 to 1e4), wide radii, gradients that are not finite. Against the fp64 oracle."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+
+import synth
+from oracle import sph as O
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+from paper_2609_24875_amd import sph as B  # noqa: E402
+
+DEV = torch.device("cuda:0")
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+
+
+def make(fmt, n, k, seed=1, skew=False):
+    D, V = synth.FORMATS[fmt]
+    g = np.random.default_rng([seed, n, k])
+    rho = (0.3 * g.standard_normal((n, k // 8)) - 2.8).astype(np.float32)
+    signs = g.integers(0, 256, (n, k // 8)).astype(np.uint8)
+    z = g.integers(0, 1 << D, (n, k // 8)).astype(np.uint16)
+    if skew:
+        z[g.random(z.shape) < 0.9] = 3
+    cb = O.f16_to_f64(synth.random_codebook(D, g)).astype(np.float32)
+    return D, V, rho, signs, z, cb
+
+
+def sign_of(signs):
+    return 1.0 - 2.0 * ((signs[..., None] >> np.arange(8)) & 1)
+
+
+def forward(D, V, rho, signs, z, cb):
+    return B.fake_quant_forward(D, V, dev(rho), dev(signs), dev(z.view(np.int16)), dev(cb), want_codes=True)
+
+
+def check_forward(D, V, rho, signs, z, cb):
+    n, nv = rho.shape
+    w, r_hat, codes = forward(D, V, rho, signs, z, cb)
+    r, rh, q = O.fake_quant_radius(rho.astype(np.float64), V)
+    rg = r.reshape(n, -1, 16)
+    lo, st = O.group_offset_step(rg, V)
+    assert np.array_equal(codes["gmin"].cpu().numpy().view(np.uint16), lo)
+    assert np.array_equal(codes["gstep"].cpu().numpy().view(np.uint16), st)
+    got = codes["q"].cpu().numpy()
+    stv = O.f16_to_f64(st)[..., None]
+    with np.errstate(divide="ignore", invalid="ignore"):
+        x = np.where(stv > 0, (rg - O.f16_to_f64(lo)[..., None]) / stv, 0.0).reshape(n, nv)
+    bad = got != q
+    assert np.all(np.abs(np.abs(x - np.floor(x)) - 0.5)[bad] <= 1e-12 * np.maximum(1, np.abs(x[bad])))
+    ref = np.repeat(O.f16_to_f64(lo), 16, axis=1) + got * np.repeat(O.f16_to_f64(st), 16, axis=1)
+    assert np.array_equal(r_hat.cpu().numpy(), ref.astype(np.float32))
+    want = (ref[..., None] * sign_of(signs) * cb[z].astype(np.float64)).reshape(n, -1)
+    assert np.array_equal(w.cpu().numpy(), want.astype(np.float32))      # one rounding of each product
+    return w, r_hat
+
+
+@pytest.mark.parametrize("fmt", ["W2", "W3", "W3_cfg", "W2_cfg"])
+@pytest.mark.parametrize("n,k", [(1, 128), (5, 384), (1031, 512), (2100, 8192)])
+def test_forward_sizes(fmt, n, k):
+    check_forward(*make(fmt, n, k))
+
+
+@pytest.mark.parametrize("fmt", ["W2", "W3_cfg"])
+def test_forward_hard_levels(fmt):
+    """Levels on or beside rounding boundaries, zero and tiny steps, and every size of softplus."""
+    D, V, rho, signs, z, cb = make(fmt, 64, 1024)
+    top = (1 << V) - 1
+    r = np.empty((64, 8, 16))
+    g = np.random.default_rng(9)
+    for row in range(64):
+        lo, st = 0.03125, 2.0 ** -(6 + row % 12)                         # exact in fp16
+        lev = g.integers(0, top, (8, 16)) + 0.5 * (g.random((8, 16)) < 0.7)   # half-way points
+        lev[:, 0], lev[:, 1] = 0, top
+        r[row] = lo + lev * st
+    rho = np.log(np.expm1(r)).reshape(64, 128).astype(np.float32)
+    rho[7] = rho[7, 0]                                                   # zero steps
+    rho[8] = np.linspace(-80, 80, 128)
+    rho[9] = 10.0 ** np.linspace(-30, 4, 128)
+    rho[10] = -(10.0 ** np.linspace(-30, 2, 128))
+    check_forward(D, V, rho, signs, z, cb)
+
+
+def check_backward(D, V, rho, signs, z, cb, skip=()):
+    n, nv = rho.shape
+    w, r_hat = forward(D, V, rho, signs, z, cb)[:2]
+    gw = np.random.default_rng(4).standard_normal((n, nv * 8)).astype(np.float32)
+    for v, value in skip:
+        gw.reshape(-1, 8)[v] = value
+    perm, off = B.direction_groups(D, z)
+    args = (D, V, dev(rho), dev(signs), dev(z.view(np.int16)), dev(cb), r_hat, dev(gw), dev(perm), dev(off))
+    gr, gc = B.fake_quant_backward(*args)
+    s, g64, c64 = sign_of(signs), gw.reshape(n, nv, 8).astype(np.float64), cb[z].astype(np.float64)
+    with np.errstate(invalid="ignore"):
+        sig = 1 / (1 + np.exp(-rho.astype(np.float64)))
+        ref_r = sig * (g64 * s * c64).sum(axis=2)
+        scale = sig * np.abs(g64 * c64).sum(axis=2)
+        fine = np.isfinite(ref_r)
+        assert np.all(np.abs(gr.cpu().numpy() - ref_r)[fine] <= 8 * 2.0 ** -24 * scale[fine] + 1e-30)
+        p = r_hat.cpu().numpy().astype(np.float64)[..., None] * s * g64
+        ref_c, mag = np.zeros(cb.shape), np.zeros(cb.shape)
+        np.add.at(ref_c, z.reshape(-1), p.reshape(-1, 8))
+        np.add.at(mag, z.reshape(-1), np.abs(p).reshape(-1, 8))
+    out = gc.cpu().numpy()
+    ok = np.isfinite(ref_c)
+    # products rounded once; sums of at most 2^13 terms per partial sum, each rounding at most 2^-24 of
+    # the magnitudes added so far (their square root in practice: a wide margin)
+    assert np.all(np.abs(out - ref_c)[ok] <= 64 * 2.0 ** -24 * mag[ok] + 1e-30)
+    assert np.array_equal(np.isfinite(out), ok)                           # only the centres concerned
+    again = B.fake_quant_backward(*args)
+    assert torch.equal(again[0].nan_to_num(), gr.nan_to_num()) and torch.equal(again[1].nan_to_num(), gc.nan_to_num())
+    return args, gr, gc
+
+
+@pytest.mark.parametrize("fmt", ["W2", "W3", "W3_cfg", "W2_cfg", "W2_72"])
+@pytest.mark.parametrize("n,k", [(1, 128), (5, 384), (64, 1024), (129, 4096), (1500, 4096)])
+@pytest.mark.parametrize("skew", [False, True])
+def test_backward_sizes(fmt, n, k, skew):
+    check_backward(*make(fmt, n, k, skew=skew))
+
+
+@pytest.mark.parametrize("fmt", ["W2", "W3_cfg", "W3"])
+def test_backward_gradients_not_finite(fmt):
+    D, V, rho, signs, z, cb = make(fmt, 130, 4096)
+    check_backward(D, V, rho, signs, z, cb, skip=[(5, np.inf), (70000 % z.size, np.nan), (31, 1e37)])
+
+
+@pytest.mark.parametrize("fmt", ["W2", "W3"])
+def test_backward_in_place_of_an_input(fmt):
+    """The radius gradient written over rho: no sums are kept there meanwhile."""
+    import ctypes
+    D, V, rho, signs, z, cb = make(fmt, 600, 4096)
+    (_, _, rho_d, signs_d, z_d, cb_d, r_hat, gw, perm, off), gr, gc = check_backward(D, V, rho, signs, z, cb)
+    n, nv = rho.shape
+    nb = ctypes.c_size_t(0)
+    lib = B.load_library()
+    assert lib.sph_fake_quant_backward_workspace_bytes(D, ctypes.byref(nb)) == 0
+    ws = torch.empty(nb.value, dtype=torch.uint8, device=DEV)
+    out = torch.empty_like(gc)
+    st = lib.sph_fake_quant_backward(ctypes.byref(B.make_format(D, V)), n, nv * 8, rho_d.data_ptr(), signs_d.data_ptr(),
+                                     z_d.data_ptr(), cb_d.data_ptr(), r_hat.data_ptr(), gw.data_ptr(), nv * 8, perm.data_ptr(),
+                                     off.data_ptr(), rho_d.data_ptr(), out.data_ptr(), ws.data_ptr(), ws.numel(),
+                                     torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert st == 0 and torch.equal(rho_d, gr)
+    assert torch.allclose(out, gc, rtol=0, atol=float(gc.abs().max()) * 1e-5)
