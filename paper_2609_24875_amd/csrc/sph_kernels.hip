@@ -46,7 +46,6 @@ struct KArgs {
   const uint16_t* C;  // codebook kind with 4 radius bits: bit 3 of q, one 16-bit word per record
   const uint4* T;
   const uint16_t* CB;  // the codebook as packed (read from memory by the 16-D kernel)
-  uint32_t t_bytes;   // bytes of lookup tables staged into LDS
   const uint16_t* x;
   int64_t ldx;
   void* y;
@@ -119,13 +118,15 @@ __device__ __forceinline__ uint4 signed_dir_nib(const unsigned char* lds, uint32
   return make_uint4(a.x, a.y, b.x, b.y);
 }
 
-__device__ __forceinline__ uint4 signed_dir_cb13(const unsigned char* lds, uint32_t mask_off, uint32_t s,
-                                                 uint32_t z) {
+// The signs by shifts, nine operations, against two LDS reads of a 16-entry mask table: the lookups
+// share the LDS port with the entries' 16-byte reads, which is what bounds the codebook kinds. W3,
+// kernels alone: batch 1 8.34 -> 8.14 us (6144x4096), 16.6 -> 15.7 (24576x4096), 9.93 -> 9.66
+// (4096x12288); batch 32 29.1 -> 28.3 (12288x4096); batch 16 within the runs' spread (20.1).
+__device__ __forceinline__ uint4 signed_dir_cb13(const unsigned char* lds, uint32_t s, uint32_t z) {
   const uint4 c = ((const uint4*)lds)[z];
-  const uint2* mask = (const uint2*)(lds + mask_off);
-  const uint2 ml = mask[s & 15u];
-  const uint2 mh = mask[s >> 4];
-  return make_uint4(c.x ^ ml.x, c.y ^ ml.y, c.z ^ mh.x, c.w ^ mh.y);
+  const uint32_t u = s | (s << 15);   // sign of element 2i at bit 2i, of element 2i + 1 at bit 2i + 16
+  return make_uint4(c.x ^ ((u << 15) & 0x80008000u), c.y ^ ((u << 13) & 0x80008000u), c.z ^ ((u << 11) & 0x80008000u),
+                    c.w ^ ((u << 9) & 0x80008000u));
 }
 
 __device__ __forceinline__ float f16lo(uint32_t u) { return (float)__builtin_bit_cast(f16, (uint16_t)(u & 0xFFFFu)); }
@@ -222,7 +223,7 @@ constexpr bool IS_CB = KIND == SPH_KIND_CB13 || KIND == SPH_KIND_CB13Q4;
 
 template <int KIND, int D>
 struct Tables {
-  static constexpr uint32_t bytes = IS_CB<KIND> ? ((16u << D) + 128u) : (256u << D);
+  static constexpr uint32_t bytes = IS_CB<KIND> ? (16u << D) : (256u << D);
 };
 
 // The tile variant (batch 9..16) passes each step's activations through a per-wave LDS buffer
@@ -241,7 +242,7 @@ __host__ __device__ constexpr bool xt_staged(int kind, int mode) {
 // Whether the split-tile slots and counters of one workgroup's waves fit in LDS next to the lookup
 // table and the parameter (modes 0, 1) or activation (mode 2) staging. Host and device.
 __host__ __device__ constexpr bool lds_handover_fits(int kind, int D, int M, int mode) {
-  return ((kind == SPH_KIND_CB13 || kind == SPH_KIND_CB13Q4) ? ((16u << D) + 128u) : (256u << D)) +
+  return ((kind == SPH_KIND_CB13 || kind == SPH_KIND_CB13Q4) ? (16u << D) : (256u << D)) +
              (16u * M * 16u * 4u + 17u * 4u) +
              (mode == 2 ? (xt_staged(kind, mode) ? 16u * (uint32_t)XT_WAVE : 0u) : 16u * 256u) <=
          160u * 1024u;
@@ -306,7 +307,7 @@ __device__ __forceinline__ void load_rec(Rec<KIND, M, RPL, MX>& R, const KArgs& 
 // Table lookups of the rows [r0, r0 + RB) of a record: field extraction and the LDS reads.
 template <int KIND, int D, int M, int RPL, int RB, bool MX = false>
 __device__ __forceinline__ void lookup_rows(const Rec<KIND, M, RPL, MX>& R, int r0, uint32_t qodd, const unsigned char* lds,
-                                            uint32_t mask_off, uint4 (&tt)[RB], float (&qf)[RB]) {
+                                            uint4 (&tt)[RB], float (&qf)[RB]) {
 #pragma unroll
   for (int i = 0; i < RB; ++i) {
     const int r = r0 + i;
@@ -315,7 +316,7 @@ __device__ __forceinline__ void lookup_rows(const Rec<KIND, M, RPL, MX>& R, int 
       uint32_t s, z;
       decode_cb13(R.ra[r / 4], r % 4, R.rb[r / 2], r & 1, s, z, q);
       if constexpr (KIND == SPH_KIND_CB13Q4) q |= ((qodd >> r) & 1u) << 3;
-      tt[i] = signed_dir_cb13(lds, mask_off, s, z);
+      tt[i] = signed_dir_cb13(lds, s, z);
     } else {
       uint32_t lo, hi, qx = 0;
       if constexpr (KIND == SPH_KIND_W2) qx = (qodd >> (4 * (r / 2))) & 15u;
@@ -334,7 +335,7 @@ __device__ __forceinline__ void lookup_rows(const Rec<KIND, M, RPL, MX>& R, int 
 // LDS latency under bank conflicts needs).
 template <int KIND, int D, int M, int RPL, bool MX = false>
 __device__ __forceinline__ void compute_rec(const Rec<KIND, M, RPL, MX>& R, float (&acc)[M][RPL],
-                                            const unsigned char* lds, uint32_t mask_off, uint32_t* pstage,
+                                            const unsigned char* lds, uint32_t* pstage,
                                             int lane, int h, int vloc) {
   constexpr int RB = RPL < VALU_RB ? RPL : VALU_RB;
   constexpr int NB = RPL / RB;
@@ -357,10 +358,10 @@ __device__ __forceinline__ void compute_rec(const Rec<KIND, M, RPL, MX>& R, floa
   if constexpr (KIND == SPH_KIND_CB13Q4) qodd = R.rc >> (h * RPL);
   uint4 tt[2][RB];
   float qf[2][RB];
-  lookup_rows<KIND, D, M, RPL, RB, MX>(R, 0, qodd, lds, mask_off, tt[0], qf[0]);
+  lookup_rows<KIND, D, M, RPL, RB, MX>(R, 0, qodd, lds, tt[0], qf[0]);
 #pragma unroll
   for (int j = 0; j < NB; ++j) {
-    if (j + 1 < NB) lookup_rows<KIND, D, M, RPL, RB, MX>(R, (j + 1) * RB, qodd, lds, mask_off, tt[(j + 1) & 1], qf[(j + 1) & 1]);
+    if (j + 1 < NB) lookup_rows<KIND, D, M, RPL, RB, MX>(R, (j + 1) * RB, qodd, lds, tt[(j + 1) & 1], qf[(j + 1) & 1]);
     if constexpr (VALU_PIPE_BARRIERS<MX>) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < RB; ++i) {
@@ -462,7 +463,7 @@ __device__ __forceinline__ void load_rec_t(RecT<KIND, NB>& R, const KArgs& a, in
 
 template <int KIND, int D, int NB>
 __device__ __forceinline__ void compute_rec_t(const RecT<KIND, NB>& R, float (&acc)[NB][4], const unsigned char* lds,
-                                              uint32_t mask_off, unsigned char* xs, int lane) {
+                                              unsigned char* xs, int lane) {
   const int r = lane & 15;
   if constexpr (xt_staged(KIND, 2)) {
     // row-order words into the wave's buffer; read back in operand order below (the LDS performs
@@ -480,7 +481,7 @@ __device__ __forceinline__ void compute_rec_t(const RecT<KIND, NB>& R, float (&a
       uint32_t sg, z;
       decode_cb13(R.ra[i], r % 4, R.rb[i], r & 1, sg, z, q[i]);
       if constexpr (KIND == SPH_KIND_CB13Q4) q[i] |= ((R.rc[i] >> r) & 1u) << 3;
-      tt[i] = signed_dir_cb13(lds, mask_off, sg, z);
+      tt[i] = signed_dir_cb13(lds, sg, z);
     } else {
       uint32_t l, hh, qx = 0;
       if constexpr (KIND == SPH_KIND_W2) qx = (R.rb[i] >> (4 * (r / 2))) & 15u;
@@ -529,9 +530,9 @@ struct Step {
     else load_rec<KIND, M, RPL, MODE == 1>(rec, a, t, c, h, vloc, lane);
   }
   static __device__ __forceinline__ void compute(const R& rec, float (&acc)[AR][RPL], const unsigned char* lds,
-                                                 uint32_t mask_off, uint32_t* pstage, int lane, int h, int vloc) {
-    if constexpr (MODE == 2) compute_rec_t<KIND, D, M / 16>(rec, acc, lds, mask_off, (unsigned char*)pstage, lane);
-    else compute_rec<KIND, D, M, RPL, MODE == 1>(rec, acc, lds, mask_off, pstage, lane, h, vloc);
+                                                 uint32_t* pstage, int lane, int h, int vloc) {
+    if constexpr (MODE == 2) compute_rec_t<KIND, D, M / 16>(rec, acc, lds, (unsigned char*)pstage, lane);
+    else compute_rec<KIND, D, M, RPL, MODE == 1>(rec, acc, lds, pstage, lane, h, vloc);
   }
 };
 
@@ -965,7 +966,7 @@ template <int KIND, int D>
 struct TableWords {
   static constexpr bool EXPAND = !IS_CB<KIND> && D >= 8;
   static constexpr int NLO = 16 << D;                       // entries of T_lo (and of T_hi)
-  static constexpr int N16 = (int)((Tables<KIND, D>::bytes - (IS_CB<KIND> ? 128u : 0u)) / 16u);
+  static constexpr int N16 = (int)(Tables<KIND, D>::bytes / 16u);
   static constexpr int NITEM = EXPAND ? 2 * NLO : N16;     // 8-byte entries, or 16-byte words
   static constexpr int PER = (NITEM + VALU_THREADS - 1) / VALU_THREADS;
   typename std::conditional<EXPAND, uint2, uint4>::type w[PER];
@@ -988,7 +989,7 @@ __device__ __forceinline__ void fetch_tables(TableWords<KIND, D>& tw, const KArg
 }
 
 template <int KIND, int D>
-__device__ __forceinline__ void store_tables(unsigned char* lds, const TableWords<KIND, D>& tw, const KArgs& a) {
+__device__ __forceinline__ void store_tables(unsigned char* lds, const TableWords<KIND, D>& tw) {
   using TW = TableWords<KIND, D>;
 #pragma unroll
   for (int i = 0; i < TW::PER; ++i) {
@@ -1003,16 +1004,6 @@ __device__ __forceinline__ void store_tables(unsigned char* lds, const TableWord
       } else {
         ((uint4*)lds)[j] = tw.w[i];
       }
-    }
-  }
-  if constexpr (IS_CB<KIND>) {
-    // mask[s] flips the fp16 sign bit of element j (of 4) where bit j of the nibble s is set.
-    if (threadIdx.x < 16) {
-      const uint32_t s = threadIdx.x;
-      uint2 m;
-      m.x = ((s & 1u) << 15) | ((s & 2u) << 30);
-      m.y = ((s & 4u) << 13) | ((s & 8u) << 28);
-      *(uint2*)(lds + a.t_bytes + s * 8u) = m;
     }
   }
 }
@@ -1061,10 +1052,9 @@ __attribute__((amdgpu_waves_per_eu(VALU_WPB * VALU_WG_PER_CU / 4))) k_gemm_valu(
   const int tl = __builtin_amdgcn_readfirstlane((s_end - 1) / a.nc);
   const int gr0 = wave_of_step(a, t0 * a.nc), gl0 = wave_of_step(a, t0 * a.nc + a.nc - 1);
   const int grl = wave_of_step(a, tl * a.nc), gll = wave_of_step(a, tl * a.nc + a.nc - 1);
-  store_tables<KIND, D>(lds, tw, a);
+  store_tables<KIND, D>(lds, tw);
   if constexpr (LDS_HO)
     if (threadIdx.x <= VALU_WPB) ho->cnt[threadIdx.x] = 0u;
-  const uint32_t mask_off = a.t_bytes;
   __syncthreads();
   if (!active) return;                       // no barrier follows
   uint32_t* pstage = pstage_all + wave * PST;
@@ -1094,7 +1084,7 @@ __attribute__((amdgpu_waves_per_eu(VALU_WPB * VALU_WG_PER_CU / 4))) k_gemm_valu(
       c1 = 0;
     }
     S::load(r1, a, t1, c1, h, vloc, lane);
-    S::compute(r0, acc, lds, mask_off, pstage, lane, h, vloc);
+    S::compute(r0, acc, lds, pstage, lane, h, vloc);
     if (c1 == 0) emit_part<M, RPL, MODE, LDS_HO, false>(a, acc, t, t == t0 ? c0 : 0, a.nc, g, gr0, gl0, lane, ho, pend, xnone);
     int t2 = t1, c2 = c1 + 1;
     if (c2 == a.nc) {
@@ -1102,7 +1092,7 @@ __attribute__((amdgpu_waves_per_eu(VALU_WPB * VALU_WG_PER_CU / 4))) k_gemm_valu(
       c2 = 0;
     }
     S::load(r0, a, t2, c2, h, vloc, lane);   // step 2i + 2 <= nsteps - 1 exists
-    S::compute(r1, acc, lds, mask_off, pstage, lane, h, vloc);
+    S::compute(r1, acc, lds, pstage, lane, h, vloc);
     if (c2 == 0) emit_part<M, RPL, MODE, LDS_HO, false>(a, acc, t1, t1 == t0 ? c0 : 0, a.nc, g, gr0, gl0, lane, ho, pend, xnone);
     t = t2;
     c = c2;
@@ -1116,7 +1106,7 @@ __attribute__((amdgpu_waves_per_eu(VALU_WPB * VALU_WG_PER_CU / 4))) k_gemm_valu(
       cf = 0;
     }
     S::load(r1, a, tf, cf, h, vloc, lane);
-    S::compute(r0, acc, lds, mask_off, pstage, lane, h, vloc);
+    S::compute(r0, acc, lds, pstage, lane, h, vloc);
     if (cf == 0) emit_part<M, RPL, MODE, LDS_HO, false>(a, acc, t, t == t0 ? c0 : 0, a.nc, g, gr0, gl0, lane, ho, pend, xnone);
   }
   const int caf = tf == t0 ? c0 : 0;
@@ -1138,7 +1128,7 @@ __attribute__((amdgpu_waves_per_eu(VALU_WPB * VALU_WG_PER_CU / 4))) k_gemm_valu(
         xw[i] = ix.writer ? __hip_atomic_load(words + ix.idx[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0ull;
     }
   }
-  S::compute(r0, acc, lds, mask_off, pstage, lane, h, vloc);
+  S::compute(r0, acc, lds, pstage, lane, h, vloc);
   emit_part<M, RPL, MODE, LDS_HO, true>(a, acc, tf, caf, cf + 1, g, grl, gll, lane, ho, pend, xw);
   follow_up<M, RPL, MODE, LDS_HO>(a, g, gr0, gl0, lane, ho, pend);
 }
@@ -1237,14 +1227,14 @@ struct PfOp {
 
 template <int KIND, int D>
 __device__ __forceinline__ PfOp pf_rebuild(const uint32_t ra, const uint32_t rb, const uint32_t rc,
-                                           const unsigned char* lds, uint32_t mask_off, int r) {
+                                           const unsigned char* lds, int r) {
   PfOp o;
   uint32_t q;
   if constexpr (IS_CB<KIND>) {
     uint32_t sg, z;
     decode_cb13(ra, r % 4, rb, r & 1, sg, z, q);
     if constexpr (KIND == SPH_KIND_CB13Q4) q |= ((rc >> r) & 1u) << 3;
-    o.t = signed_dir_cb13(lds, mask_off, sg, z);
+    o.t = signed_dir_cb13(lds, sg, z);
   } else {
     uint32_t l, hh, qx = 0;
     if constexpr (KIND == SPH_KIND_W2) qx = (rb >> (4 * (r / 2))) & 15u;
@@ -1323,7 +1313,7 @@ __global__ void __launch_bounds__(PF_THREADS) k_gemm_prefill(KArgs a) {
   pf_fetch<KIND, MC>(pre, a, t0, mc0, c0);
   {
     // the tables in batches of up to 8 loads per thread, each batch one round trip
-    constexpr int n16 = (int)((Tables<KIND, D>::bytes - (IS_CB<KIND> ? 128u : 0u)) / 16u);
+    constexpr int n16 = (int)(Tables<KIND, D>::bytes / 16u);
     constexpr int TPER = (n16 + PF_THREADS - 1) / PF_THREADS, TB = TPER < 8 ? TPER : 8;
 #pragma unroll
     for (int p0 = 0; p0 < TPER; p0 += TB) {
@@ -1334,15 +1324,6 @@ __global__ void __launch_bounds__(PF_THREADS) k_gemm_prefill(KArgs a) {
       for (int p = 0; p < TB; ++p) {
         const int t = (int)threadIdx.x + PF_THREADS * (p0 + p);
         if (t < n16) ((uint4*)lds)[t] = tv[p];
-      }
-    }
-    if constexpr (IS_CB<KIND>) {
-      if (threadIdx.x < 16) {
-        const uint32_t sm = threadIdx.x;
-        uint2 mk;
-        mk.x = ((sm & 1u) << 15) | ((sm & 2u) << 30);
-        mk.y = ((sm & 4u) << 13) | ((sm & 8u) << 28);
-        *(uint2*)(lds + a.t_bytes + sm * 8u) = mk;
       }
     }
   }
@@ -1376,7 +1357,7 @@ __global__ void __launch_bounds__(PF_THREADS) k_gemm_prefill(KArgs a) {
         if constexpr (S::BDW > 0) rb = sb[rec * S::BDW + bdw];
         uint32_t rc = 0u;
         if constexpr (S::CH > 0) rc = sc[rec];
-        w[u] = pf_rebuild<KIND, D>(ra, rb, rc, lds, a.t_bytes, r);
+        w[u] = pf_rebuild<KIND, D>(ra, rb, rc, lds, r);
       }
     };
     // A chunk is one radius group, so Eq. 7 factors over it: per (row, batch row) the chunk adds
@@ -1509,10 +1490,7 @@ __device__ __forceinline__ uint4 pw_decode(uint32_t ra, uint32_t rb, uint32_t rc
     uint32_t sg, z;
     decode_cb13(ra, r % 4, rb, r & 1, sg, z, q);
     if constexpr (KIND == SPH_KIND_CB13Q4) q |= ((rc >> r) & 1u) << 3;
-    const uint4 c = ((const uint4*)lds)[z];
-    const uint32_t u = sg | (sg << 15);   // sign of element 2i at bit 2i, of element 2i + 1 at bit 2i + 16
-    return make_uint4(c.x ^ ((u << 15) & 0x80008000u), c.y ^ ((u << 13) & 0x80008000u), c.z ^ ((u << 11) & 0x80008000u),
-                      c.w ^ ((u << 9) & 0x80008000u));
+    return signed_dir_cb13(lds, sg, z);
   } else {
     uint32_t l, hh, qx = 0;
     if constexpr (KIND == SPH_KIND_W2) qx = (rb >> (4 * (r / 2))) & 15u;
@@ -1937,7 +1915,6 @@ struct Launch {
 
 KArgs make_args(const sph_weights* w) {
   KArgs a{};
-  const int kind = sph_kind_of_fmt(w->fmt.vec_dim, w->fmt.dir_bits, w->fmt.radius_bits);
   const char* base = (const char*)w->d_base;
   a.A = (const uint32_t*)(base + w->off[SPH_OFF_A]);
   a.B = (const uint32_t*)(base + w->off[SPH_OFF_B]);
@@ -1945,7 +1922,6 @@ KArgs make_args(const sph_weights* w) {
   a.C = (const uint16_t*)(base + w->off[SPH_OFF_C]);
   a.T = (const uint4*)(base + w->off[SPH_OFF_TABLES]);
   a.CB = (const uint16_t*)(base + w->off[SPH_OFF_CODEBOOK]);
-  a.t_bytes = (uint32_t)sph_table_bytes(kind, w->fmt.dir_bits);
   a.n = (int)w->n;
   a.nt = (int)((w->n + 15) / 16);
   a.nv = (int)(w->k / w->fmt.vec_dim);

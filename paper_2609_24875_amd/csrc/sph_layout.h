@@ -40,8 +40,8 @@
 //   T_lo[z*16 + s_lo]   = 4 fp16: element j of c_z for j = 0..3, negated where bit j of s_lo is set
 //   T_hi[s_hi*2^D + z]  = 4 fp16: element 4+j of c_z for j = 0..3, negated where bit j of s_hi is set
 // so that the low table index is the field bits [D+3:0] and the high table index is the field
-// bits [D+7:4]. The codebook kinds (CB13*) look up the unsigned entry c_z (16 bytes) and apply
-// the signs with two 16-entry XOR-mask tables.
+// bits [D+7:4]. The codebook kinds (CB13*) look up the unsigned entry c_z (16 bytes) and flip
+// the sign bits with shifts of the 8-bit sign field.
 //
 // Group parameters: half2 (x = offset, y = step) at ((t * NG + g) * 16 + r), NG = k/128.
 // Padded rows (r >= n) carry zero codes and zero parameters, so they decode to zero.
