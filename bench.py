@@ -260,11 +260,10 @@ def encode_main(args):
     enc_ms = timed(enc, args.steps)
     km_ms = timed(km, max(1, args.steps // 4))
     nvec = n * k // 8
-    # 2^13 entries: the search runs on the matrix cores (two passes of 16-deep fp16 products per
-    # entry and vector, hi/lo split of the direction); smaller codebooks: fp64 cosines on the ALUs
-    mfma = D == 13
-    flops = nvec * (1 << D) * (2 * 16 * 2 if mfma else 15)
-    peak = MFMA_F16_PEAK_TFS if mfma else FP64_PEAK_TFS
+    # the search runs on the matrix cores: one 16-deep fp16 product per entry and vector (the
+    # direction's eight coordinates in two fp16 words each), fp64 only between near-ties
+    flops = nvec * (1 << D) * 16 * 2
+    peak = MFMA_F16_PEAK_TFS
     out = {
         "metric": "device encoder: weights encoded per second (Eq. 3, 5-7) and k-means codebook time",
         "value": round(n * k / (enc_ms / 1e3) / 1e9, 3),
@@ -278,8 +277,8 @@ def encode_main(args):
         "config": {"workload": f"encode-{fmt}-{n}x{k}", "format": f"{fmt} (8 sign + {D} direction + "
                    f"{V} radius bits)", "kmeans_samples": ns, "kmeans_iters": iters,
                    "encode_ms": round(enc_ms, 4), "kmeans_ms": round(km_ms, 4)},
-        "roofline": {"kernel": f"{'k_encode_mx' if mfma else 'k_encode'} {fmt} {n}x{k}",
-                     "bound": "mfma" if mfma else "alu",
+        "roofline": {"kernel": f"k_encode {fmt} {n}x{k}",
+                     "bound": "mfma",
                      "achieved": round(flops / (enc_ms / 1e3) / 1e12, 2), "peak": peak,
                      "unit": "TFLOP/s", "frac": round(flops / (enc_ms / 1e3) / 1e12 / peak, 4),
                      "traffic": None, "flops_per_launch": flops},

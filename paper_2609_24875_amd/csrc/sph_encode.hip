@@ -742,7 +742,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(4)))
 // block's chunk of ch samples (in whatever order they arrive), hist[block][centre] their number. Each
 // 256 samples' cosines to their centres are summed (each in pairwise order, then in a fixed order) into
 // opart. Counted in LDS: a few centres take thousands of samples each (weight vectors with an outlier),
-// and global atomics on them took 30 us. rank may be sidx's first split.
+// and global atomics on them took 30 us. rank may be sidx's first split. Without hist nothing is counted.
 constexpr int kFinalThreads = 1024;
 
 __global__ __launch_bounds__(kFinalThreads) void k_assign_final(const double* __restrict__ ds, int64_t ns, int64_t ch,
@@ -752,7 +752,8 @@ __global__ __launch_bounds__(kFinalThreads) void k_assign_final(const double* __
                                                                 uint32_t* __restrict__ hist, double* __restrict__ opart) {
   __shared__ uint32_t cnt[8192];
   __shared__ double wsum[kFinalThreads / 64];
-  for (int t = threadIdx.x; t < ncb; t += kFinalThreads) cnt[t] = 0;
+  if (hist)
+    for (int t = threadIdx.x; t < ncb; t += kFinalThreads) cnt[t] = 0;
   __syncthreads();
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int64_t j0 = blockIdx.x * ch, j1 = min(ns, j0 + ch);
@@ -770,7 +771,7 @@ __global__ __launch_bounds__(kFinalThreads) void k_assign_final(const double* __
         }
       }
       z[j] = bz;
-      rank[j] = (int32_t)atomicAdd(&cnt[bz], 1u);
+      if (hist) rank[j] = (int32_t)atomicAdd(&cnt[bz], 1u);
       double d[8];
 #pragma unroll
       for (int c = 0; c < 8; ++c) d[c] = ds[j * 8 + c];
@@ -792,7 +793,8 @@ __global__ __launch_bounds__(kFinalThreads) void k_assign_final(const double* __
     }
   }
   __syncthreads();
-  for (int t = threadIdx.x; t < ncb; t += kFinalThreads) hist[(int64_t)blockIdx.x * ncb + t] = cnt[t];
+  if (hist)
+    for (int t = threadIdx.x; t < ncb; t += kFinalThreads) hist[(int64_t)blockIdx.x * ncb + t] = cnt[t];
 }
 
 // Per centre, the running sum of the chunks' counts over the nch chunks, in place, and their total;
@@ -914,9 +916,80 @@ __device__ __forceinline__ void store_words(uint4* words, int ncb, int c, int e,
   ((_Float16*)(words + ncb + c))[e] = l;
 }
 
-// New centres: eight lanes per sample, one for each component, add a centre's listed samples; the
-// sums are converted to fp64 and normalised to unit length; a centre without directions keeps its
-// position. One wave per centre of at most kBig samples (blocks of 16), and one block for each of the
+// Centre c's sum of component lane % 8 (the same in all of the wave's lanes of that component) converted
+// to fp64, and the sums normalised to unit length; a centre without directions keeps its position.
+__device__ __forceinline__ void finish_centre(unsigned __int128 sum, int ncb, int c, int lane, double* cen, uint4* words) {
+#pragma clang fp contract(off)
+  const int e = lane & 7;
+  // limbs of 40 bits convert exactly; two roundings combine them
+  const uint64_t l0 = (uint64_t)sum & kLimbMask, l1 = (uint64_t)(sum >> kLimbBits) & kLimbMask, l2 = (uint64_t)(sum >> (2 * kLimbBits));
+  const double hi = ((double)l2 * 0x1p40 + (double)l1) * 0x1p40;
+  const double mine = (hi + (double)l0) * 0x1p-100;
+  double s[8];
+#pragma unroll
+  for (int t = 0; t < 8; ++t) s[t] = __shfl(mine, t, 64);
+  const double norm = sqrt(dot8_pairwise(s, s));
+  if (norm > 0.0 && lane < 8) {
+    const double v = mine / norm;
+    cen[(int64_t)c * 8 + e] = v;
+    store_words(words, ncb, c, e, v);
+  }
+}
+
+// Up to 256 centres are summed without a list: block p adds chunk p's samples with 64-bit LDS atomics,
+// three 40-bit limbs a component, and stores 128-bit sums; a wave per centre adds the chunks'.
+// A list gives such a codebook only as many blocks as it has centres. k-means of 4096x4096, 65,536
+// samples, 20 iterations, by lists -> by chunks: 936 -> 514 us (16 entries), 921 -> 541 (64), 958 -> 629
+// (256). With 2^13 centres the chunks' sums are more bytes than the samples, and the list wins (101 + 30
+// us an iteration against 10 + 22).
+constexpr int kAccMax = 256;
+constexpr int kLimbs = 8 * 3;
+
+__global__ __launch_bounds__(kThreads) void k_accumulate(const double* __restrict__ ds, int64_t ns, const int32_t* __restrict__ z,
+                                                         int ncb, int64_t ch, ulonglong2* __restrict__ part) {
+  __shared__ unsigned long long la[kAccMax * kLimbs];
+  for (int t = threadIdx.x; t < ncb * kLimbs; t += kThreads) la[t] = 0;
+  __syncthreads();
+  const int64_t j0 = (int64_t)blockIdx.x * ch, j1 = min(ns, j0 + ch);
+  for (int64_t j = j0 + threadIdx.x; j < j1; j += kThreads) {
+    unsigned long long* a = la + z[j] * kLimbs;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const unsigned __int128 t = to_fixed(ds[j * 8 + e]);
+#pragma unroll
+      for (int l = 0; l < 3; ++l) {
+        const uint64_t v = (uint64_t)(t >> (l * kLimbBits)) & kLimbMask;
+        if (v) atomicAdd(a + 3 * e + l, (unsigned long long)v);
+      }
+    }
+  }
+  __syncthreads();
+  for (int t = threadIdx.x; t < ncb * 8; t += kThreads) {
+    const unsigned __int128 v = (unsigned __int128)la[3 * t] + ((unsigned __int128)la[3 * t + 1] << kLimbBits) +
+                                ((unsigned __int128)la[3 * t + 2] << (2 * kLimbBits));
+    part[(int64_t)blockIdx.x * ncb * 8 + t] = make_ulonglong2((uint64_t)v, (uint64_t)(v >> 64));
+  }
+}
+
+__global__ __launch_bounds__(64) void k_update_chunks(const ulonglong2* __restrict__ part, int np, int ncb, double* __restrict__ cen,
+                                                      uint4* __restrict__ words) {
+  const int lane = threadIdx.x, c = blockIdx.x;
+  unsigned __int128 sum = 0;
+#pragma unroll 8
+  for (int p = lane >> 3; p < np; p += 8) {
+    const ulonglong2 v = part[((int64_t)p * ncb + c) * 8 + (lane & 7)];
+    sum += ((unsigned __int128)v.y << 64) | v.x;
+  }
+#pragma unroll
+  for (int o = 8; o <= 32; o <<= 1) {
+    const uint64_t lo = __shfl_xor((uint64_t)sum, o, 64), hi = __shfl_xor((uint64_t)(sum >> 64), o, 64);
+    sum += ((unsigned __int128)hi << 64) | lo;
+  }
+  finish_centre(sum, ncb, c, lane, cen, words);
+}
+
+// New centres of large codebooks: eight lanes per sample, one for each component, add a centre's listed
+// samples. One wave per centre of at most kBig samples (blocks of 16), and one block for each of the
 // big ones, which the last gridDim.x - (ncb + 15) / 16 blocks share. (65,536 samples, 8192 centres,
 // a few of them with thousands: 101 + 30 us with LDS atomics in passes over all samples per centre range,
 // 10 + 22 us with the list; 148 us with one wave per centre whatever its size.)
@@ -956,19 +1029,7 @@ __global__ __launch_bounds__(1024) void k_update(const double* __restrict__ ds, 
       __syncthreads();
     }
     if (have && (one || wv == 0)) {
-      // limbs of 40 bits convert exactly; two roundings combine them
-      const uint64_t l0 = (uint64_t)sum & kLimbMask, l1 = (uint64_t)(sum >> kLimbBits) & kLimbMask, l2 = (uint64_t)(sum >> (2 * kLimbBits));
-      const double hi = ((double)l2 * 0x1p40 + (double)l1) * 0x1p40;
-      const double mine = (hi + (double)l0) * 0x1p-100;
-      double s[8];
-#pragma unroll
-      for (int t = 0; t < 8; ++t) s[t] = __shfl(mine, t, 64);
-      const double norm = sqrt(dot8_pairwise(s, s));
-      if (norm > 0.0 && lane < 8) {
-        const double v = mine / norm;
-        cen[(int64_t)c * 8 + e] = v;
-        store_words(words, ncb, c, e, v);
-      }
+      finish_centre(sum, ncb, c, lane, cen, words);
     }
     if (one) break;
   }
@@ -987,12 +1048,15 @@ inline uint64_t align256(uint64_t x) { return (x + 255) / 256 * 256; }
 struct KmPlan {
   int64_t nvec, nb, nfb, ch;
   int ncb, nsplit, per, waves, nch;
+  int np;           // chunks of chp samples summed without a list, 0: by lists
+  int64_t chp;
   uint64_t off_cdf, off_bsum, off_ds, off_z, off_opart, off_cen, off_words, off_count, off_hist, off_sbest, off_sidx, total;
 };
 
 // The workspace size that the interface states, per sample, per codebook entry and chunk and per split.
-// The layout of km_plan takes less (its 12 * nsplit bytes per sample, 8 to 12 bytes of counts per
-// entry and 4 per entry and chunk stay within the 12 and 192 bytes of more splits and chunks here);
+// The layout of km_plan takes no more (its 12 * nsplit bytes per sample, and 32 bytes of words and 8 to 12 of
+// counts per entry with 4 per entry and chunk, or 32 with 128 per entry and chunk, stay within the 12
+// and 192 bytes of more splits and chunks here);
 // the size stays what callers have sized their buffers by.
 uint64_t stated_bytes(int64_t nvec, int64_t nb, int64_t ns, int64_t ncb) {
   const int64_t nab = (ns + 1023) / 1024, nr = (ncb + 511) / 512;
@@ -1028,6 +1092,13 @@ KmPlan km_plan(const sph_format* fmt, int64_t n, int64_t k, int64_t ns) {
   // sample chunks of the counting: whole rounds of kFinalThreads samples, at most 64 chunks
   P.ch = ((ns + 63) / 64 + kFinalThreads - 1) / kFinalThreads * kFinalThreads;
   P.nch = (int)((ns + P.ch - 1) / P.ch);
+  if (P.ncb <= kAccMax) {   // at most 128 chunks, a thread per sample at least
+    P.np = (int)std::min<int64_t>(128, (ns + kThreads - 1) / kThreads);
+    P.chp = (ns + P.np - 1) / P.np;
+    P.np = (int)((ns + P.chp - 1) / P.chp);
+    P.ch = kFinalThreads;
+    P.nch = (int)((ns + P.ch - 1) / P.ch);
+  }
   uint64_t p = 0;
   P.off_cdf = p;
   p = align256(p + (uint64_t)P.nvec * 8);
@@ -1044,9 +1115,9 @@ KmPlan km_plan(const sph_format* fmt, int64_t n, int64_t k, int64_t ns) {
   P.off_words = p;
   p = align256(p + (uint64_t)P.ncb * 32);
   P.off_count = p;   // counts, list starts, big centres
-  p = align256(p + ((uint64_t)P.ncb * 2 + 1 + std::min(P.ncb, kMaxBig)) * 4);
-  P.off_hist = p;
-  p = align256(p + (uint64_t)P.nch * P.ncb * 4);
+  if (P.np == 0) p = align256(p + ((uint64_t)P.ncb * 2 + 1 + std::min(P.ncb, kMaxBig)) * 4);
+  P.off_hist = p;    // or the chunks' sums
+  p = align256(p + (P.np > 0 ? (uint64_t)P.np * P.ncb * 128 : (uint64_t)P.nch * P.ncb * 4));
   P.off_sbest = p;   // after a split's results are combined, the samples listed by centre
   p = align256(p + (uint64_t)P.nsplit * ns * 8);
   P.off_sidx = p;    // likewise the samples' ranks
@@ -1204,7 +1275,18 @@ sph_status sph_kmeans_codebook(const sph_format* fmt, int64_t n, int64_t k, cons
     ok = launch_ok(assign, g_split, dim3(64 * P.waves), s, (const double*)ds, ns, (const double*)cen, (const uint4*)words, P.ncb,
                    P.per, sbest, sidx) &&
          launch_ok((const void*)k_assign_final, dim3((unsigned)P.nch), dim3(kFinalThreads), s, (const double*)ds, ns, P.ch,
-                   (const double*)cen, P.ncb, P.nsplit, (const double*)sbest, (const int32_t*)sidx, z, rank, hist, opart);
+                   (const double*)cen, P.ncb, P.nsplit, (const double*)sbest, (const int32_t*)sidx, z, rank,
+                   P.np > 0 ? (uint32_t*)nullptr : hist, opart);
+    if (P.np > 0) {
+      if (ok && d_objective)
+        ok = launch_ok((const void*)k_offsets, dim3(1), blk, s, hist, 0, 0, count, (const double*)opart, P.nfb, d_objective + it);
+      if (ok && it < iters)
+        ok = launch_ok((const void*)k_accumulate, dim3((unsigned)P.np), blk, s, (const double*)ds, ns, (const int32_t*)z, P.ncb, P.chp,
+                       (ulonglong2*)hist) &&
+             launch_ok((const void*)k_update_chunks, dim3((unsigned)P.ncb), dim3(64), s, (const ulonglong2*)hist, P.np, P.ncb, cen,
+                       words);
+      continue;
+    }
     if (ok && (d_objective || it < iters))
       ok = launch_ok((const void*)k_offsets, dim3(g_off), blk, s, hist, P.nch, P.ncb, count, (const double*)opart, P.nfb,
                      d_objective ? d_objective + it : (double*)nullptr);

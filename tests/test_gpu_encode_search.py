@@ -91,7 +91,9 @@ def test_scales(fmt, scale):
         assert np.array_equal(got, (d @ O.f16_to_f64(cb).T).argmax(axis=1))
 
 
-@pytest.mark.parametrize("fmt,ns", [("W2", 5000), ("W3", 5000), ("W3_cfg", 1023), ("W2", 64), ("W3", 70000)])
+@pytest.mark.parametrize("fmt,ns", [("W2", 5000), ("W3", 5000), ("W3_cfg", 1023), ("W2", 64), ("W3", 70000),
+                                    # sums by chunks: a chunk of one sample over, and the most chunks
+                                    ("W2_cfg", 32769), ("W3_cfg", 257), ("W2_cfg", 70000)])
 def test_kmeans_samples_on_few_centres(fmt, ns):
     """Half of the weight vectors lie beside one of three directions, so a few centres hold most
     samples: objective and codebook against the oracle's fp64 sums."""
