@@ -156,7 +156,6 @@ def cpu_baseline(mats, budget_s, step_bytes_total, per_mat_bytes, layers):
     }
 
 
-FP64_PEAK_TFS = 78.6   # MI355X fp64 vector peak
 
 
 def cpu_model() -> str:
