@@ -724,12 +724,14 @@ sph_status sph_fake_quant_backward(const sph_format* fmt, int64_t n, int64_t k, 
   if (ws_bytes < (size_t)ncb * ws_slices(ncb) * 8 * sizeof(float)) return SPH_ERR_BUFFER_TOO_SMALL;
   hipStream_t s = (hipStream_t)stream;
   const int nval = ncb * 8;
-  // The radius gradient's array may hold sums until it is written, unless it is one of the inputs.
-  auto apart = [&](const void* q, size_t bytes) {
-    const char *o = (const char*)d_grad_rho, *i = (const char*)q;
-    return o + (size_t)nvec * 4 <= i || i + bytes <= o;
+  // The radius gradient's array may hold sums until it is written, unless it is one of the inputs, or
+  // the codebook's gradient replaces the codebook, which the radius gradient reads.
+  auto apart = [](const void* p, size_t np, const void* q, size_t nq) {
+    return (const char*)p + np <= (const char*)q || (const char*)q + nq <= (const char*)p;
   };
-  const bool free_rho = apart(d_rho, (size_t)nvec * 4) && apart(d_r_hat, (size_t)nvec * 4);
+  const size_t rho_bytes = (size_t)nvec * 4, cb_bytes = (size_t)nval * 4;
+  const bool free_rho = apart(d_grad_rho, rho_bytes, d_rho, rho_bytes) && apart(d_grad_rho, rho_bytes, d_r_hat, rho_bytes) &&
+                        apart(d_grad_codebook, cb_bytes, d_codebook, cb_bytes);
   const dim3 g_final((unsigned)((nval + 31) / 32));
   if (ncb <= 256) {
     // one pass: two blocks per CU on the largest matrices, at least max(128, ncb) vectors per wave (so that
@@ -757,13 +759,18 @@ sph_status sph_fake_quant_backward(const sph_format* fmt, int64_t n, int64_t k, 
     part = d_grad_rho;
   }
   const int ncblk = (ncb + kThreads / 8 - 1) / (kThreads / 8);
+  auto sums = [&] {
+    return launch_ok((const void*)k_fq_grad_cb_final, g_final, dim3(1024), s, (const float*)part, nval, (int)ns, (int64_t)0,
+                     d_grad_codebook);
+  };
+  auto radii = [&] {
+    return launch_ok((const void*)k_fq_grad_rho, dim3((unsigned)((nvec + kThreads - 1) / kThreads)), dim3(kThreads), s, nv,
+                     nvec, d_rho, d_signs, d_dir_idx, d_codebook, d_grad_w, ldg, 0, 0, d_grad_rho);
+  };
   const bool ok =
       launch_ok((const void*)k_fq_grad_cb_part, dim3((unsigned)(ncblk * ns)), dim3(kThreads), s, nv, d_r_hat,
                 d_signs, d_grad_w, ldg, d_perm, d_offsets, ncb, (int)ns, part) &&
-      launch_ok((const void*)k_fq_grad_cb_final, g_final, dim3(1024), s, (const float*)part, nval, (int)ns, (int64_t)0,
-                d_grad_codebook) &&
-      launch_ok((const void*)k_fq_grad_rho, dim3((unsigned)((nvec + kThreads - 1) / kThreads)), dim3(kThreads), s, nv,
-                nvec, d_rho, d_signs, d_dir_idx, d_codebook, d_grad_w, ldg, 0, 0, d_grad_rho);
+      (part == d_grad_rho ? sums() && radii() : radii() && sums());
   return ok ? SPH_OK : SPH_ERR_HIP;
 }
 

@@ -137,8 +137,10 @@ def test_backward_gradients_not_finite(fmt):
 
 
 @pytest.mark.parametrize("fmt", ["W2", "W3"])
-def test_backward_in_place_of_an_input(fmt):
-    """The radius gradient written over rho: no sums are kept there meanwhile."""
+@pytest.mark.parametrize("over", ["rho", "codebook"])
+def test_backward_in_place_of_an_input(fmt, over):
+    """The radius gradient written over rho (no sums are kept there meanwhile), or the codebook's over
+    the codebook (which the radius gradient reads first)."""
     import ctypes
     D, V, rho, signs, z, cb = make(fmt, 600, 4096)
     (_, _, rho_d, signs_d, z_d, cb_d, r_hat, gw, perm, off), gr, gc = check_backward(D, V, rho, signs, z, cb)
@@ -147,11 +149,13 @@ def test_backward_in_place_of_an_input(fmt):
     lib = B.load_library()
     assert lib.sph_fake_quant_backward_workspace_bytes(D, ctypes.byref(nb)) == 0
     ws = torch.empty(nb.value, dtype=torch.uint8, device=DEV)
-    out = torch.empty_like(gc)
+    out_r = rho_d if over == "rho" else torch.empty_like(gr)
+    out_c = cb_d if over == "codebook" else torch.empty_like(gc)
     st = lib.sph_fake_quant_backward(ctypes.byref(B.make_format(D, V)), n, nv * 8, rho_d.data_ptr(), signs_d.data_ptr(),
                                      z_d.data_ptr(), cb_d.data_ptr(), r_hat.data_ptr(), gw.data_ptr(), nv * 8, perm.data_ptr(),
-                                     off.data_ptr(), rho_d.data_ptr(), out.data_ptr(), ws.data_ptr(), ws.numel(),
+                                     off.data_ptr(), out_r.data_ptr(), out_c.data_ptr(), ws.data_ptr(), ws.numel(),
                                      torch.cuda.current_stream().cuda_stream)
     torch.cuda.synchronize()
-    assert st == 0 and torch.equal(rho_d, gr)
-    assert torch.allclose(out, gc, rtol=0, atol=float(gc.abs().max()) * 1e-5)
+    assert st == 0 and torch.equal(out_r, gr)
+    # the same terms in another split: fp32 partial sums, each rounding 2^-24 of the magnitudes added
+    assert torch.allclose(out_c, gc, rtol=0, atol=float(gc.abs().max()) * 1e-5)
