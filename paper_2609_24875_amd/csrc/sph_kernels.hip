@@ -1454,7 +1454,7 @@ __global__ void __launch_bounds__(PF_THREADS) k_gemm_prefill(KArgs a) {
 // is what remains: a fold per half chunk cost 15%, fp16 conversions through fp32 products 10%,
 // v_fma_mixlo/hi_f16 (half rate) 8%, 32x32x16 products 20%, all more exact by under 4%.
 // ------------------------------------------------------------------------------------------
-constexpr int PW_MC = 128;   // batch rows per workgroup
+constexpr int PW_MC = 128;   // batch rows per workgroup (or 96 where as many workgroups then cover the batch)
 
 // The largest level of a format, for the scale (W2 with D = 6 has 4 or 3 radius bits: the larger).
 template <int KIND, int D>
@@ -1464,23 +1464,24 @@ constexpr float PW_QMAX = KIND == SPH_KIND_NIB16Q8   ? 255.0f
                           : KIND == SPH_KIND_NIB16Q2 || (KIND == SPH_KIND_W2 && D == 7) ? 3.0f
                                                                                          : 15.0f;
 
-template <int KIND, int D>
+template <int KIND, int D, int MC>
 struct PwCfg {
   static constexpr bool SPLIT = IS_CB<KIND>;               // half a chunk of X per LDS buffer
   static constexpr int KC = SPLIT ? 64 : 128;              // columns of X per buffer
   static constexpr int XP = KC / 8;                        // 16-byte pieces per staged row
   static constexpr int GPB = KC / 32;                      // position groups (4 positions) per buffer
-  static constexpr int NB = PW_MC / 16;
-  static constexpr int XPER = PW_MC * XP / PF_THREADS;     // pieces each thread stages
+  static constexpr int NB = MC / 16;
+  static constexpr int XSTEP = PF_THREADS / XP;            // rows staged by one piece of every thread
+  static constexpr int XPER = (MC + XSTEP - 1) / XSTEP;    // pieces each thread stages
   static constexpr uint32_t t_bytes = IS_CB<KIND> ? (16u << D) : (256u << D);
-  static constexpr uint32_t stage = PW_MC * KC * 2;
+  static constexpr uint32_t stage = MC * KC * 2;
   static constexpr uint32_t bytes = t_bytes + 2 * stage;
   static constexpr bool B1 = KIND == SPH_KIND_W2 || KIND == SPH_KIND_NIB16Q2;
   static constexpr int ADW = IS_CB<KIND> ? 4 : 8;
   static constexpr int BDW = KIND == SPH_KIND_NIB16 ? 0 : B1 ? 1 : (KIND == SPH_KIND_NIB16Q8) ? 4 : 8;
   static constexpr bool HAS_C = KIND == SPH_KIND_CB13Q4;
   static_assert(bytes <= 160u * 1024u, "tables and two X buffers fit in LDS");
-  static_assert(PF_THREADS / XP % 16 == 0, "pieces of one thread share a swizzle");
+  static_assert(XSTEP % 16 == 0, "pieces of one thread share a swizzle");
 };
 
 // The signed direction and level of a row's vector.
@@ -1526,20 +1527,20 @@ __device__ __forceinline__ void rt_split(uint4 t, float rho, uint4& hi, uint4& l
 
 // One wave's TPW tiles from tile tw0 over the chunks [c0, c1). Every wave of the workgroup runs the
 // same number of barriers whatever its TPW.
-template <int KIND, int D, int TPW>
+template <int KIND, int D, int MC, int TPW>
 __device__ __forceinline__ void pw_wave(const KArgs& a, unsigned char* lds, int tw0, int mc0, int c0, int c1) {
-  using C = PwCfg<KIND, D>;
+  using C = PwCfg<KIND, D, MC>;
   constexpr int NB = C::NB;
   const int lane = threadIdx.x & 63;
   const int r = lane & 15, j = lane >> 4;
   unsigned char* xs = lds + C::t_bytes;
-  // this thread's pieces of X: byte offsets from the first batch row's chunk (rows past the batch
-  // repeat the last one; the launch keeps 127 row strides within 32 bits), and its place in LDS
+  // this thread's pieces of X: byte offsets from the first batch row's chunk (rows past the batch or
+  // the workgroup's repeat the last one; the launch keeps 127 row strides within 32 bits), and its place in LDS
   uint32_t xg[C::XPER];
   const int xrow0 = (int)threadIdx.x / C::XP, xpos = (int)threadIdx.x % C::XP;
 #pragma unroll
   for (int p = 0; p < C::XPER; ++p)
-    xg[p] = (uint32_t)(min(mc0 + xrow0 + p * (PF_THREADS / C::XP), a.m - 1) - mc0) * (uint32_t)(2 * a.ldx) + (uint32_t)xpos * 16u;
+    xg[p] = (uint32_t)min(min(xrow0 + p * C::XSTEP, MC - 1), a.m - 1 - mc0) * (uint32_t)(2 * a.ldx) + (uint32_t)xpos * 16u;
   const uint32_t xo = (uint32_t)(xrow0 * (C::KC * 2) + ((xpos ^ (xrow0 & (C::XP - 1))) * 16));
   const char* xb = (const char*)(a.x + (int64_t)mc0 * a.ldx + (int64_t)c0 * 128);
   // wave-uniform stream positions and the lane's offsets in a position group
@@ -1578,7 +1579,9 @@ __device__ __forceinline__ void pw_wave(const KArgs& a, unsigned char* lds, int 
   };
   auto put_x = [&](int buf) {
 #pragma unroll
-    for (int p = 0; p < C::XPER; ++p) *(uint4*)(xs + buf * C::stage + xo + p * (PF_THREADS / C::XP) * (C::KC * 2)) = xr[p];
+    for (int p = 0; p < C::XPER; ++p)
+      if (MC % C::XSTEP == 0 || xrow0 + p * C::XSTEP < MC)
+        *(uint4*)(xs + buf * C::stage + xo + p * C::XSTEP * (C::KC * 2)) = xr[p];
   };
   fetch_x();
   load_codes(0);
@@ -1693,9 +1696,9 @@ __device__ __forceinline__ void pw_wave(const KArgs& a, unsigned char* lds, int 
   }
 }
 
-template <int KIND, int D, int T>
+template <int KIND, int D, int MC, int T>
 __global__ void __launch_bounds__(PF_THREADS) k_gemm_wide(KArgs a) {
-  using C = PwCfg<KIND, D>;
+  using C = PwCfg<KIND, D, MC>;
   static_assert(T == 16 || T == 12, "two tiles per wave, or two and one");
   __shared__ __align__(16) unsigned char lds[C::bytes];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -1713,9 +1716,9 @@ __global__ void __launch_bounds__(PF_THREADS) k_gemm_wide(KArgs a) {
     }
   }
   const int c0 = (int)((int64_t)a.ng * blockIdx.z / a.ks), c1 = (int)((int64_t)a.ng * (blockIdx.z + 1) / a.ks);
-  const int t0 = (int)blockIdx.x * T, mc0 = (int)blockIdx.y * PW_MC;
-  if (T == 16 || wave < PF_WAVES / 2) pw_wave<KIND, D, 2>(a, lds, t0 + 2 * wave, mc0, c0, c1);
-  else pw_wave<KIND, D, 1>(a, lds, t0 + PF_WAVES / 2 + wave, mc0, c0, c1);
+  const int t0 = (int)blockIdx.x * T, mc0 = (int)blockIdx.y * MC;
+  if (T == 16 || wave < PF_WAVES / 2) pw_wave<KIND, D, MC, 2>(a, lds, t0 + 2 * wave, mc0, c0, c1);
+  else pw_wave<KIND, D, MC, 1>(a, lds, t0 + PF_WAVES / 2 + wave, mc0, c0, c1);
 }
 
 // y[b][row] = sum over the K ranges, in range order, of the prefill partials, which are cleared.
@@ -1965,20 +1968,24 @@ const void* pick(int D, int V, int M) {
   return nullptr;
 }
 
-// The prefill kernel of a plan: `wide` its tiles per workgroup on the two-product kernel, or 0 for
-// the three-product kernel with `mc` batch rows per workgroup.
+// The prefill kernel of a plan with `mc` batch rows per workgroup: `wide` its tiles per workgroup on
+// the two-product kernel, or 0 for the three-product kernel.
 template <int KIND, int D>
 const void* prefill_fn_mc(int mc, int wide) {
-  if (wide == 16) return (const void*)k_gemm_wide<KIND, D, 16>;
-  if (wide == 12) return (const void*)k_gemm_wide<KIND, D, 12>;
+  if (wide == 16) return mc == 96 ? (const void*)k_gemm_wide<KIND, D, 96, 16> : (const void*)k_gemm_wide<KIND, D, PW_MC, 16>;
+  if (wide == 12) return mc == 96 ? (const void*)k_gemm_wide<KIND, D, 96, 12> : (const void*)k_gemm_wide<KIND, D, PW_MC, 12>;
   if (mc == 16) return (const void*)k_gemm_prefill<KIND, D, 16>;
   if (mc == 32) return (const void*)k_gemm_prefill<KIND, D, 32>;
+  if (mc == 48) return (const void*)k_gemm_prefill<KIND, D, 48>;
   return (const void*)k_gemm_prefill<KIND, D, 64>;
 }
 
 // Batch rows per workgroup: 16 for batches 9..16, 32 for 17..32, else 64 (the two fp32 sums of
-// the factored product double the accumulators, which 128 rows would not leave room for).
-int prefill_mc(int, int, int64_t m) { return m <= 16 ? 16 : m <= 32 ? 32 : 64; }
+// the factored product double the accumulators, which 128 rows would not leave room for), or 48
+// where as many workgroups then cover the batch (33..48, 65..96, 129..144 rows): the same grid, K
+// ranges and sums with a quarter less work for padding. Whole calls, 64 -> 48 rows: W2 12288x4096 at 48
+// rows 33.5 -> 30.4 us, W3 6144x4096 at 96 rows 36.0 -> 31.3, 5003x2944 (D = 4) at 77 26.2 -> 22.6.
+int prefill_mc(int, int, int64_t m) { return m <= 16 ? 16 : m <= 32 ? 32 : (m + 47) / 48 == (m + 63) / 64 ? 48 : 64; }
 
 // Batches 17..32 always, and 9..16 on large matrices, run on the prefill kernel, whose activations
 // are staged in LDS once per workgroup and chunk and shared by its 16 row tiles; in the 16x16x32
@@ -2115,7 +2122,10 @@ PrefillPlan wide_plan(const sph_weights* w, int64_t m, const PrefillPlan& old) {
       best.gx = (int)gx;
       best.gy = (int)gy;
       best.ks = (int)ks;
-      best.mc = PW_MC;
+      // The same grid and sums with less work for padding; 128 -> 96 rows (calls, us): W2 24576x4096
+      // 111.3 -> 87.0 at 192 rows, 69.7 -> 59.6 at 96; W3, whose X is staged by half chunks, 12288x4096
+      // 74.9 -> 71.6 at 192, 24576x4096 71.9 -> 72.0 at 96 (within the noise).
+      best.mc = m <= 96 * gy ? 96 : PW_MC;
       best.wide = T;
       best.ws_bytes = partial_bytes(w, m, ks);
     }

@@ -103,3 +103,19 @@ def test_unknown_flags_are_refused():
     w.desc.off[FLAGS] = 2
     with pytest.raises(pkg.SphError):
         pkg.gemm(w, x)
+
+
+# batches at the edges of 48, 64, 96 and 128 batch rows per workgroup: (n, k) on the three-product
+# kernel, then on the two-product kernel with 12 and 16 tiles
+@pytest.mark.parametrize("fmt", ["W2", "W3", "W3_cfg", "W3_25"])
+@pytest.mark.parametrize("n,k,m", [(261, 1024, m) for m in (33, 48, 49, 64, 65, 96, 97, 128, 129, 144, 145)]
+                         + [(1033, 12416, m) for m in (95, 96, 97, 128)] + [(24686, 2816, m) for m in (129, 192, 193)])
+def test_batch_rows_per_workgroup(fmt, n, k, m):
+    D, V, codes, cb, x = make(fmt, n, k, m)
+    w = pkg.pack(D, V, codes, cb, device=DEV)
+    buf = torch.full((m + 1, n + 3), float("nan"), dtype=torch.float32, device=DEV)
+    y = pkg.gemm(w, x, out=buf[:m, :n])
+    check(y, codes, cb, x)
+    assert bool(torch.isnan(buf[:, n:]).all()) and bool(torch.isnan(buf[m]).all())
+    for ws in w.workspaces.values():
+        assert int(torch.count_nonzero(ws)) == 0
