@@ -1425,7 +1425,7 @@ __global__ void __launch_bounds__(PF_THREADS) k_gemm_prefill(KArgs a) {
 
 // ------------------------------------------------------------------------------------------
 // Wide prefill kernel (large batches on matrices whose radii allow it, see SPH_FLAG_RADIUS_SPLIT and
-// wide_plan): two MFMA operands per weight instead of three, 128 batch rows per workgroup.
+// wide_plan): two MFMA operands per weight instead of three, up to 128 batch rows per workgroup.
 //
 // The matrix cores bound this path (2 m n k flop against 0.3-0.4 bytes per weight), and random
 // fp16 data runs them at about 1.75 PFLOP/s on this part (power; 16x16x32, measured in registers),
@@ -1454,7 +1454,7 @@ __global__ void __launch_bounds__(PF_THREADS) k_gemm_prefill(KArgs a) {
 // is what remains: a fold per half chunk cost 15%, fp16 conversions through fp32 products 10%,
 // v_fma_mixlo/hi_f16 (half rate) 8%, 32x32x16 products 20%, all more exact by under 4%.
 // ------------------------------------------------------------------------------------------
-constexpr int PW_MC = 128;   // batch rows per workgroup (or 96 where as many workgroups then cover the batch)
+constexpr int PW_MC = 128;   // batch rows per workgroup, or fewer where as many workgroups cover the batch (see wide_plan)
 
 // The largest level of a format, for the scale (W2 with D = 6 has 4 or 3 radius bits: the larger).
 template <int KIND, int D>
@@ -1474,7 +1474,7 @@ struct PwCfg {
   static constexpr int XSTEP = PF_THREADS / XP;            // rows staged by one piece of every thread
   static constexpr int XPER = (MC + XSTEP - 1) / XSTEP;    // pieces each thread stages
   static constexpr uint32_t t_bytes = IS_CB<KIND> ? (16u << D) : (256u << D);
-  static constexpr uint32_t stage = MC * KC * 2;
+  static constexpr uint32_t stage = XPER * XSTEP * KC * 2;   // rows past MC are staged too: a test per piece cost 8-20%
   static constexpr uint32_t bytes = t_bytes + 2 * stage;
   static constexpr bool B1 = KIND == SPH_KIND_W2 || KIND == SPH_KIND_NIB16Q2;
   static constexpr int ADW = IS_CB<KIND> ? 4 : 8;
@@ -1579,9 +1579,7 @@ __device__ __forceinline__ void pw_wave(const KArgs& a, unsigned char* lds, int 
   };
   auto put_x = [&](int buf) {
 #pragma unroll
-    for (int p = 0; p < C::XPER; ++p)
-      if (MC % C::XSTEP == 0 || xrow0 + p * C::XSTEP < MC)
-        *(uint4*)(xs + buf * C::stage + xo + p * C::XSTEP * (C::KC * 2)) = xr[p];
+    for (int p = 0; p < C::XPER; ++p) *(uint4*)(xs + buf * C::stage + xo + p * C::XSTEP * (C::KC * 2)) = xr[p];
   };
   fetch_x();
   load_codes(0);
@@ -1970,10 +1968,19 @@ const void* pick(int D, int V, int M) {
 
 // The prefill kernel of a plan with `mc` batch rows per workgroup: `wide` its tiles per workgroup on
 // the two-product kernel, or 0 for the three-product kernel.
+template <int KIND, int D, int T>
+const void* wide_fn_mc(int mc) {
+  if constexpr (!IS_CB<KIND>) {
+    if (mc == 80) return (const void*)k_gemm_wide<KIND, D, 80, T>;
+    if (mc == 112) return (const void*)k_gemm_wide<KIND, D, 112, T>;
+  }
+  return mc == 96 ? (const void*)k_gemm_wide<KIND, D, 96, T> : (const void*)k_gemm_wide<KIND, D, PW_MC, T>;
+}
+
 template <int KIND, int D>
 const void* prefill_fn_mc(int mc, int wide) {
-  if (wide == 16) return mc == 96 ? (const void*)k_gemm_wide<KIND, D, 96, 16> : (const void*)k_gemm_wide<KIND, D, PW_MC, 16>;
-  if (wide == 12) return mc == 96 ? (const void*)k_gemm_wide<KIND, D, 96, 12> : (const void*)k_gemm_wide<KIND, D, PW_MC, 12>;
+  if (wide == 16) return wide_fn_mc<KIND, D, 16>(mc);
+  if (wide == 12) return wide_fn_mc<KIND, D, 12>(mc);
   if (mc == 16) return (const void*)k_gemm_prefill<KIND, D, 16>;
   if (mc == 32) return (const void*)k_gemm_prefill<KIND, D, 32>;
   if (mc == 48) return (const void*)k_gemm_prefill<KIND, D, 48>;
@@ -2065,7 +2072,7 @@ int num_cus() {
 
 // Prefill plan: workgroups of PF_WAVES * PF_TPW tiles by MC batch rows; K is split only while the
 // split grid still fits in one round on the CUs (each split adds a pass over fp32 partial outputs).
-// wide: tiles per workgroup on the two-product kernel (12 or 16, 128 batch rows), or 0.
+// wide: tiles per workgroup on the two-product kernel (12 or 16, up to 128 batch rows), or 0.
 struct PrefillPlan {
   int gx, gy, ks, mc, wide;
   size_t ws_bytes;
@@ -2105,6 +2112,8 @@ PrefillPlan wide_plan(const sph_weights* w, int64_t m, const PrefillPlan& old) {
   PrefillPlan best{};
   if (m <= 64 || !(w->off[SPH_OFF_FLAGS] & SPH_FLAG_RADIUS_SPLIT)) return best;
   const int64_t nt = (w->n + 15) / 16, ng = w->k / 128, cus = num_cus();
+  const int kind = sph_kind_of(w->fmt.dir_bits, w->fmt.radius_bits);
+  const bool cb = kind == SPH_KIND_CB13 || kind == SPH_KIND_CB13Q4;
   auto cost = [&](int64_t wgs, int64_t ks, int64_t per_chunk) {
     const int64_t c = (wgs * ks + cus - 1) / cus * ((ng + ks - 1) / ks) * per_chunk;
     return ks > 1 ? c + 4000 + (int64_t)(partial_bytes(w, m, ks) / 1000) : c;
@@ -2122,10 +2131,12 @@ PrefillPlan wide_plan(const sph_weights* w, int64_t m, const PrefillPlan& old) {
       best.gx = (int)gx;
       best.gy = (int)gy;
       best.ks = (int)ks;
-      // The same grid and sums with less work for padding; 128 -> 96 rows (calls, us): W2 24576x4096
-      // 111.3 -> 87.0 at 192 rows, 69.7 -> 59.6 at 96; W3, whose X is staged by half chunks, 12288x4096
-      // 74.9 -> 71.6 at 192, 24576x4096 71.9 -> 72.0 at 96 (within the noise).
-      best.mc = m <= 96 * gy ? 96 : PW_MC;
+      // The fewest rows that this grid's workgroups need: the same sums with less work for padding. Calls with
+      // 128 rows -> fewer, 24576x4096, us: W2 69.7 -> 59.6 (96 rows), 111.3 -> 87.0 (192); W3 71.9 -> 62.0
+      // (96), 110.1 -> 90.6 (150). 80 and 112 rows against 96 and 128: W2 84.9 -> 79.4 (150), 109.3 -> 98.5
+      // (220); not built for the 2^13 codebook, whose X is staged 64 rows at a time.
+      const int64_t even = (m + gy - 1) / gy;
+      best.mc = cb ? (even <= 96 ? 96 : PW_MC) : (int)std::max<int64_t>(80, (even + 15) / 16 * 16);
       best.wide = T;
       best.ws_bytes = partial_bytes(w, m, ks);
     }

@@ -105,11 +105,11 @@ def test_unknown_flags_are_refused():
         pkg.gemm(w, x)
 
 
-# batches at the edges of 48, 64, 96 and 128 batch rows per workgroup: (n, k) on the three-product
+# batches at the edges of 48, 64, 80, 96, 112 and 128 batch rows per workgroup: (n, k) on the three-product
 # kernel, then on the two-product kernel with 12 and 16 tiles
 @pytest.mark.parametrize("fmt", ["W2", "W3", "W3_cfg", "W3_25"])
 @pytest.mark.parametrize("n,k,m", [(261, 1024, m) for m in (33, 48, 49, 64, 65, 96, 97, 128, 129, 144, 145)]
-                         + [(1033, 12416, m) for m in (95, 96, 97, 128)] + [(24686, 2816, m) for m in (129, 192, 193)])
+                         + [(1033, 12416, m) for m in (80, 81, 96, 97, 112, 113, 128)] + [(24686, 2816, m) for m in (160, 161, 192, 193, 224, 225)])
 def test_batch_rows_per_workgroup(fmt, n, k, m):
     D, V, codes, cb, x = make(fmt, n, k, m)
     w = pkg.pack(D, V, codes, cb, device=DEV)
