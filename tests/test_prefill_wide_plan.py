@@ -136,3 +136,28 @@ def test_flag_bounds_the_operand_error():
                 lo = (t * b + d).astype(f16).astype(np.float64)
                 err = np.abs(hi + lo - t * (rho[:, None]))
                 assert np.all(err <= np.maximum(2.0 ** -25, 1.5 * 2.0 ** -23 * np.abs(t * rho[:, None])) + 1e-12), (V, ratio, q)
+
+
+def wide_rows(m: int, gy: int, codebook13: bool) -> int:
+    """Batch rows per workgroup on the two-product kernel."""
+    even = (m + gy - 1) // gy
+    if codebook13:
+        return 96 if even <= 96 else 128
+    return max(80, (even + 15) // 16 * 16)
+
+
+def test_batch_rows_per_workgroup_keep_the_grid():
+    """Fewer rows per workgroup: the same number of workgroups covers the batch, none of them empty,
+    and both staged X buffers (whole passes of 512 threads) fit beside the tables."""
+    for m in range(33, 4097):
+        mc = 48 if (m + 47) // 48 == (m + 63) // 64 else 64
+        gy = (m + 63) // 64
+        assert gy * mc >= m > (gy - 1) * mc
+        if m <= 64:
+            continue
+        gy = (m + PW_MC - 1) // PW_MC
+        for cb, table, kc in ((True, 16 << 13, 64), (False, 256 << 8, 128)):
+            mc = wide_rows(m, gy, cb)
+            assert mc in ((96, 128) if cb else (80, 96, 112, 128)) and gy * mc >= m > (gy - 1) * mc
+            step = 512 // (kc // 8)
+            assert table + 2 * ((mc + step - 1) // step * step) * kc * 2 <= 160 * 1024
