@@ -287,8 +287,8 @@ sph_status sph_fake_quant_backward_workspace_bytes(int32_t dir_bits, size_t* byt
  * dL/drho_i = sigmoid(rho_i) sum_j dL/dw^_ij s_ij c_{z_i,j}, and d_grad_codebook fp32[2^D][8]
  * with dL/dc_z = sum over vectors i of direction z of r^_i s_i (.) dL/dw^_i. d_r_hat is the
  * forward's r^; d_perm int32[n*k/8] and d_offsets int64[2^D + 1] are device copies of
- * sph_direction_groups for the same d_dir_idx (not validated; read for codebooks of more than 2^8
- * entries). Sums run in an order fixed by the sizes, so repeated calls give bitwise identical
+ * sph_direction_groups for the same d_dir_idx (not validated). d_grad_rho may be d_rho or d_r_hat, and
+ * d_grad_codebook may be d_codebook. Sums run in an order fixed by the sizes, so repeated calls give bitwise identical
  * results (a centre with a gradient that is not finite excepted, whose sum is not finite). d_ws:
  * sph_fake_quant_backward_workspace_bytes bytes, 16-byte aligned; d_grad_rho serves as more of it
  * before it is written. Asynchronous. */

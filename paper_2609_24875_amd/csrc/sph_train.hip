@@ -9,13 +9,13 @@
 //   angular kernels   one thread per codebook entry (at most 8192).
 //   fake quantisation a block takes whole groups of 16 vectors (128 weights); the radii of a group's
 //                     smallest and largest parameter in fp64, one per thread, then levels and weights.
-//   gradients         up to 256 centres: one pass in storage order, each wave adding its vectors to
-//                     sums of its own per centre in LDS. 2^13 centres: the radius gradient one thread
-//                     per vector; the vectors are pre-sorted by direction (a stable counting sort on
-//                     the host, once per module, since the indices stay fixed) and eight lanes add
-//                     one slice of one centre's list in fp64. A last kernel adds the waves' or slices'
-//                     sums in a fixed order. No sum crosses waves by atomics: repeated calls are
-//                     bitwise equal.
+//   gradients         codebooks of up to 256 entries on matrices large enough for them: one pass in storage
+//                     order, each wave adding its vectors to sums of its own per centre on the matrix cores.
+//                     Otherwise the radius gradient one thread per vector; the vectors are pre-sorted by
+//                     direction (a stable counting sort on the host, once per module, since the indices
+//                     stay fixed) and the lanes of a centre's slice add its list in fp64. A last
+//                     kernel adds the waves' or slices' sums in a fixed order. No sum crosses waves by
+//                     atomics: repeated calls are bitwise equal.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <stdint.h>
@@ -310,35 +310,42 @@ __global__ __launch_bounds__(kThreads) void k_fq_grad_rho(int64_t nv, int64_t nv
   grho[i] = sum8_pairwise(p) * sigmoidf(rho[i]);
 }
 
-// Slice sl of a centre's direction-sorted vector list: sum of r^_i s_i (.) dL/dw^_i, by eight lanes, two per
-// vector (16 bytes of the gradient each) and four vectors at a time, in fp64, then over the four pairs by
-// a fixed tree; stored as fp32 in part[slice][centre][8].
+// Slice sl of a centre's direction-sorted vector list: sum of r^_i s_i (.) dL/dw^_i, two lanes per vector
+// (16 bytes of the gradient each) and U vectors at a time, in fp64, then over the lanes by a fixed
+// tree; stored as fp32 in part[slice][centre][8]. A block holds G centres, 256 / G lanes each, and then takes
+// those of them together whose slice is longer than `most`: weight vectors with one large coordinate lie near an
+// axis and crowd into a few centres, and eight lanes alone take as long as such a list is (W3, the sums in
+// the workspace: 1024x4096 encoded 47 -> 30 us, 1024x1024 with nine vectors in ten in one centre 4.7 -> 0.21 ms).
+//
+// G = 32 where the radius gradient's array holds eight slices or more, G = 4 for 2^13 centres otherwise (a
+// wave per centre: 1024x4096 encoded 30 us against 31 with G = 1 and 47 with 32, 256x1024 12 against
+// 25 and 11), G = 1 for up to 256 centres, which have no more blocks to offer.
 //
 // The gradient's 32 bytes per vector are gathered in list order; neighbouring vectors belong to
 // different centres, so a cache line is read by up to four of them. A slice covers about one
 // stretch of the matrix for all centres, and block ids that are equal modulo 8 share an L2, so a
 // slice's blocks take ids of one residue: its lines come from memory once. (The finest useful slices: a
-// step of 12288x4096 W3, 8192 centres, 500 us with one block of 256 threads per centre -> 348 us. Smaller
-// codebooks take k_fq_grad_pass.)
+// step of 12288x4096 W3, 8192 centres, 500 us with one block of 256 threads per centre -> 348 us.)
 constexpr int kXcd = 8;
 
+template <int G>
 __global__ __launch_bounds__(kThreads) void k_fq_grad_cb_part(int64_t nv, const float* __restrict__ r_hat,
                                                               const uint8_t* __restrict__ signs,
                                                               const float* __restrict__ gw, int64_t ldg,
                                                               const int32_t* __restrict__ perm,
-                                                              const int64_t* __restrict__ off, int ncb, int nslice,
+                                                              const int64_t* __restrict__ off, int ncb, int nslice, int most,
                                                               float* __restrict__ part) {
-  const int ncblk = (ncb + kThreads / 8 - 1) / (kThreads / 8);
+  constexpr int L = kThreads / G;          // lanes per centre
+  constexpr int U = G == 1 ? 8 : 4;        // vectors in flight per pair of lanes
+  static_assert(G == 1 || (L >= 8 && L <= 64), "a block, or lanes of one wave");
+  __shared__ double sh[kThreads / 64][8];
+  const int ncblk = (ncb + G - 1) / G;
   const int nx = nslice % kXcd == 0 ? kXcd : 1;
   const int xcd = blockIdx.x % nx, seq = blockIdx.x / nx;
-  const int sl = seq / ncblk * nx + xcd;
-  const int c = seq % ncblk * (kThreads / 8) + (threadIdx.x >> 3);
-  if (c >= ncb) return;                      // whole groups of eight lanes; no barrier follows
-  const int pair = (threadIdx.x >> 1) & 3, half = threadIdx.x & 1;
-  const int64_t a0 = off[c], len = off[c + 1] - a0;
-  const int64_t b0 = a0 + len * sl / nslice, b1 = a0 + len * (sl + 1) / nslice;
+  const int sl = seq / ncblk * nx + xcd, cfirst = seq % ncblk * G;
+  const int half = threadIdx.x & 1;
   const bool packed = ldg == nv * 8;
-  double acc[4] = {0, 0, 0, 0};
+  double acc[4];
   auto add = [&](float rh, uint32_t s, const float4 g) {
     const float p[4] = {rh * g.x, rh * g.y, rh * g.z, rh * g.w};
 #pragma unroll
@@ -348,36 +355,75 @@ __global__ __launch_bounds__(kThreads) void k_fq_grad_cb_part(int64_t nv, const 
     const int64_t row = packed ? 0 : i / nv;
     return *reinterpret_cast<const float4*>(gw + row * ldg + (i - row * nv) * 8 + 4 * half);
   };
-  constexpr int U = 4;
-  int64_t t = b0 + pair;
-  for (; t + 4 * (U - 1) < b1; t += 4 * U) {
-    int64_t i[U];
-    float rh[U];
-    uint32_t s[U];
-    float4 g[U];
+  // every step-th vector of the list's places [t, b1)
+  auto walk = [&](int64_t t, int64_t b1, int step) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) i[u] = perm[t + 4 * u];
+    for (int j = 0; j < 4; ++j) acc[j] = 0.0;
+    for (; t + step * (U - 1) < b1; t += step * U) {
+      int64_t i[U];
+      float rh[U];
+      uint32_t s[U];
+      float4 g[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      rh[u] = r_hat[i[u]];
-      s[u] = signs[i[u]];
-      g[u] = grad(i[u]);
+      for (int u = 0; u < U; ++u) i[u] = perm[t + step * u];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        rh[u] = r_hat[i[u]];
+        s[u] = signs[i[u]];
+        g[u] = grad(i[u]);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) add(rh[u], s[u], g[u]);
     }
+    for (; t < b1; t += step) {
+      const int64_t i = perm[t];
+      add(r_hat[i], signs[i], grad(i));
+    }
+  };
+  auto over_lanes = [&](int lanes) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) add(rh[u], s[u], g[u]);
-  }
-  for (; t < b1; t += 4) {
-    const int64_t i = perm[t];
-    add(r_hat[i], signs[i], grad(i));
-  }
+    for (int o = 2; o < 64; o <<= 1)
+      if (o < lanes)
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    acc[j] += __shfl_xor(acc[j], 2, 64);
-    acc[j] += __shfl_xor(acc[j], 4, 64);
+        for (int j = 0; j < 4; ++j) acc[j] += __shfl_xor(acc[j], o, 64);
+  };
+  auto bounds = [&](int c, int64_t& b0, int64_t& b1) {
+    const int64_t a0 = off[c], len = off[c + 1] - a0;
+    b0 = a0 + len * sl / nslice;
+    b1 = a0 + len * (sl + 1) / nslice;
+  };
+  auto store = [&](int c, const double (&v)[4]) {
+    *reinterpret_cast<float4*>(part + ((int64_t)sl * ncb + c) * 8 + 4 * half) = make_float4((float)v[0], (float)v[1], (float)v[2], (float)v[3]);
+  };
+  if constexpr (G > 1) {
+    const int c = cfirst + (int)threadIdx.x / L;
+    int64_t b0 = 0, b1 = 0;
+    if (c < ncb) bounds(c, b0, b1);
+    const bool mine = c < ncb && b1 - b0 <= most;
+    walk(b0 + (threadIdx.x % L >> 1), mine ? b1 : b0, L / 2);
+    over_lanes(L);
+    if (mine && threadIdx.x % L < 2) store(c, acc);
+    if (!__syncthreads_or(c < ncb && !mine)) return;
   }
-  if (pair == 0)
-    *reinterpret_cast<float4*>(part + ((int64_t)sl * ncb + c) * 8 + 4 * half) =
-        make_float4((float)acc[0], (float)acc[1], (float)acc[2], (float)acc[3]);
+  const int cend = min(ncb, cfirst + G);
+  for (int c = cfirst; c < cend; ++c) {   // the same for all threads
+    int64_t b0, b1;
+    bounds(c, b0, b1);
+    if (G > 1 && b1 - b0 <= most) continue;
+    walk(b0 + (threadIdx.x >> 1), b1, kThreads / 2);
+    over_lanes(64);
+    __syncthreads();                      // the last centre's sums have been read
+    if ((threadIdx.x & 63) < 2)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) sh[threadIdx.x >> 6][4 * half + j] = acc[j];
+    __syncthreads();
+    if (threadIdx.x < 2) {
+      double v[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) v[j] = (sh[0][4 * half + j] + sh[1][4 * half + j]) + (sh[2][4 * half + j] + sh[3][4 * half + j]);
+      store(c, v);
+    }
+  }
 }
 
 // Both gradients in one pass over dL/dW^, for codebooks of at most NCB entries (16, 64 or 256). A wave walks its
@@ -733,32 +779,50 @@ sph_status sph_fake_quant_backward(const sph_format* fmt, int64_t n, int64_t k, 
   const bool free_rho = apart(d_grad_rho, rho_bytes, d_rho, rho_bytes) && apart(d_grad_rho, rho_bytes, d_r_hat, rho_bytes) &&
                         apart(d_grad_codebook, cb_bytes, d_codebook, cb_bytes);
   const dim3 g_final((unsigned)((nval + 31) / 32));
-  if (ncb <= 256) {
-    // one pass: two blocks per CU on the largest matrices, at least max(128, ncb) vectors per wave (so that
-    // a block's sums fit its stretch of the radius gradient)
-    const int64_t least = (int64_t)kPassWaves * std::max(128, ncb);
-    const int nblk = (int)std::max<int64_t>(1, std::min<int64_t>(free_rho ? 512 : ws_slices(ncb), nvec / least));
-    const bool in_ws = nblk <= ws_slices(ncb);
+  // One pass: two blocks per CU on the largest matrices, at least max(128, ncb) vectors per wave (so that a
+  // block's sums fit its stretch of the radius gradient), where there is memory for their sums (in place of
+  // an input only the workspace: 16 blocks for 64 centres, 12288x4096 1.58 ms against 0.13 by lists) and it is
+  // the faster way. Its work per vector grows with the centres, the lists' does not: whole calls, us, encoded
+  // directions, before the pass / lists / pass: 64 centres 2^15 vectors 9.5 / 9.2 / 11.9, 2^18 17.0 / 12.0 / 15.1,
+  // 2^21 92 / 52 / 42; 128 centres 2^19 27.5 / 18.7 / 43, 2^21 101 / 59 / 98; 256 centres 2^17 10.8 / 11.1 / 30, 2^19
+  // 30 / 29 / 35, 2^20 57 / 54 / 65, 2^21 112 / 107 / 102; 16 and 32 centres never behind the former kernels.
+  // The lists slow down where most vectors share one centre (2^21 vectors, nine in ten: 0.25 ms for 64 centres,
+  // 1.3 ms for 256; the pass 0.04 and 0.10), which is why the lines are not drawn higher.
+  const int64_t least = (int64_t)kPassWaves * std::max(128, ncb);
+  const int64_t nblk = std::max<int64_t>(1, std::min<int64_t>(512, nvec / least));
+  const bool in_ws = nblk <= ws_slices(ncb);
+  if (ncb <= 256 && (in_ws || free_rho) && (ncb <= 32 || nvec >= (ncb <= 64 ? 3ll << 16 : 1ll << 21))) {
     PassArgs a{nv, nvec, d_rho, d_signs, d_dir_idx, d_codebook, d_r_hat, d_grad_w, ldg, d_grad_rho, in_ws ? (float*)d_ws : nullptr, ncb};
     bool ok = launch_ok(ncb <= 16 ? (const void*)k_fq_grad_pass<16> : ncb <= 64 ? (const void*)k_fq_grad_pass<64> : (const void*)k_fq_grad_pass<256>, dim3((unsigned)nblk),
                         dim3(64 * kPassWaves), s, a) &&
               launch_ok((const void*)k_fq_grad_cb_final, g_final, dim3(1024), s, in_ws ? (const float*)d_ws : (const float*)d_grad_rho,
-                        nval, nblk, in_ws ? (int64_t)0 : nvec, d_grad_codebook);
+                        nval, (int)nblk, in_ws ? (int64_t)0 : nvec, d_grad_codebook);
     if (ok && !in_ws)
       ok = launch_ok((const void*)k_fq_grad_rho, dim3((unsigned)(((int64_t)nval * nblk + kThreads - 1) / kThreads)), dim3(kThreads), s,
-                     nv, nvec, d_rho, d_signs, d_dir_idx, d_codebook, d_grad_w, ldg, nval, nblk, d_grad_rho);
+                     nv, nvec, d_rho, d_signs, d_dir_idx, d_codebook, d_grad_w, ldg, nval, (int)nblk, d_grad_rho);
     return ok ? SPH_OK : SPH_ERR_HIP;
   }
-  // The slices' sums go to the radius gradient's array while it is not yet written, where it holds
-  // more of them than the workspace; each slice keeps at least 16 vectors per centre on average.
-  int64_t ns = std::min<int64_t>(ws_slices(ncb), std::max<int64_t>(1, nvec / ncb / 16));
+  // By lists, in as many slices as the workspace holds. The slices' sums of 2^13 centres go to the radius
+  // gradient's array while it is not yet written, where it holds more of them; each slice then keeps
+  // at least 16 vectors per centre on average.
+  int group = 1;
+  int64_t ns = ws_slices(ncb);
   float* part = (float*)d_ws;
-  const int64_t room = std::min<int64_t>(std::min<int64_t>(slices_for(ncb), nvec / (8 * ncb)), nvec / ncb / 16) / kXcd * kXcd;
-  if (room > ns && free_rho && a16(d_grad_rho)) {
-    ns = room;
-    part = d_grad_rho;
+  if (ncb > 256) {
+    group = 4;
+    const int64_t room = std::min<int64_t>(std::min<int64_t>(slices_for(ncb), nvec / (8 * ncb)), nvec / ncb / 16) / kXcd * kXcd;
+    if (room > ns && free_rho && a16(d_grad_rho)) {
+      ns = room;
+      part = d_grad_rho;
+      group = 32;
+    }
   }
-  const int ncblk = (ncb + kThreads / 8 - 1) / (kThreads / 8);
+  // lists up to four times the mean stay with their lanes
+  const int most = (int)std::min<int64_t>(1 << 30, std::max<int64_t>(group == 32 ? 256 : 1024, 4 * (nvec / ncb / ns)));
+  const int ncblk = (ncb + group - 1) / group;
+  const void* fn = group == 1 ? (const void*)k_fq_grad_cb_part<1> : group == 32 ? (const void*)k_fq_grad_cb_part<32> : (const void*)k_fq_grad_cb_part<4>;
+  // the lists' sums before the radius gradient (which may be written over r^), that before the
+  // codebook's (which may be written over the codebook) unless the sums wait in its array
   auto sums = [&] {
     return launch_ok((const void*)k_fq_grad_cb_final, g_final, dim3(1024), s, (const float*)part, nval, (int)ns, (int64_t)0,
                      d_grad_codebook);
@@ -768,8 +832,8 @@ sph_status sph_fake_quant_backward(const sph_format* fmt, int64_t n, int64_t k, 
                      nvec, d_rho, d_signs, d_dir_idx, d_codebook, d_grad_w, ldg, 0, 0, d_grad_rho);
   };
   const bool ok =
-      launch_ok((const void*)k_fq_grad_cb_part, dim3((unsigned)(ncblk * ns)), dim3(kThreads), s, nv, d_r_hat,
-                d_signs, d_grad_w, ldg, d_perm, d_offsets, ncb, (int)ns, part) &&
+      launch_ok(fn, dim3((unsigned)(ncblk * ns)), dim3(kThreads), s, nv, d_r_hat, d_signs, d_grad_w, ldg, d_perm, d_offsets, ncb, (int)ns,
+                most, part) &&
       (part == d_grad_rho ? sums() && radii() : radii() && sums());
   return ok ? SPH_OK : SPH_ERR_HIP;
 }

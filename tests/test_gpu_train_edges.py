@@ -136,26 +136,72 @@ def test_backward_gradients_not_finite(fmt):
     check_backward(D, V, rho, signs, z, cb, skip=[(5, np.inf), (70000 % z.size, np.nan), (31, 1e37)])
 
 
-@pytest.mark.parametrize("fmt", ["W2", "W3"])
-@pytest.mark.parametrize("over", ["rho", "codebook"])
-def test_backward_in_place_of_an_input(fmt, over):
-    """The radius gradient written over rho (no sums are kept there meanwhile), or the codebook's over
-    the codebook (which the radius gradient reads first)."""
+def in_place(over, args, gr, gc):
+    """The gradients again through the C entry point, one of them over an input: a callable and its outputs."""
     import ctypes
-    D, V, rho, signs, z, cb = make(fmt, 600, 4096)
-    (_, _, rho_d, signs_d, z_d, cb_d, r_hat, gw, perm, off), gr, gc = check_backward(D, V, rho, signs, z, cb)
-    n, nv = rho.shape
+    D, V, rho_d, signs_d, z_d, cb_d, r_hat, gw, perm, off = args
+    n, nv = rho_d.shape
     nb = ctypes.c_size_t(0)
     lib = B.load_library()
     assert lib.sph_fake_quant_backward_workspace_bytes(D, ctypes.byref(nb)) == 0
     ws = torch.empty(nb.value, dtype=torch.uint8, device=DEV)
-    out_r = rho_d if over == "rho" else torch.empty_like(gr)
+    out_r = {"rho": rho_d, "r_hat": r_hat}.get(over, torch.empty_like(gr))
     out_c = cb_d if over == "codebook" else torch.empty_like(gc)
-    st = lib.sph_fake_quant_backward(ctypes.byref(B.make_format(D, V)), n, nv * 8, rho_d.data_ptr(), signs_d.data_ptr(),
-                                     z_d.data_ptr(), cb_d.data_ptr(), r_hat.data_ptr(), gw.data_ptr(), nv * 8, perm.data_ptr(),
-                                     off.data_ptr(), out_r.data_ptr(), out_c.data_ptr(), ws.data_ptr(), ws.numel(),
-                                     torch.cuda.current_stream().cuda_stream)
+
+    def call():
+        assert lib.sph_fake_quant_backward(ctypes.byref(B.make_format(D, V)), n, nv * 8, rho_d.data_ptr(), signs_d.data_ptr(),
+                                           z_d.data_ptr(), cb_d.data_ptr(), r_hat.data_ptr(), gw.data_ptr(), nv * 8, perm.data_ptr(),
+                                           off.data_ptr(), out_r.data_ptr(), out_c.data_ptr(), ws.data_ptr(), ws.numel(),
+                                           torch.cuda.current_stream().cuda_stream) == 0
+
+    call.keep = ws
+    return call, out_r, out_c
+
+
+@pytest.mark.parametrize("fmt", ["W2", "W3", "W3_cfg"])
+@pytest.mark.parametrize("over", ["rho", "r_hat", "codebook"])
+@pytest.mark.parametrize("skew", [False, True])
+def test_backward_in_place_of_an_input(fmt, over, skew):
+    """The radius gradient written over rho or r^ (no sums are kept there meanwhile), or the codebook's over
+    the codebook (which the radius gradient reads first)."""
+    args, gr, gc = check_backward(*make(fmt, 1500, 4096, skew=skew))
+    call, out_r, out_c = in_place(over, args, gr, gc)
+    call()
     torch.cuda.synchronize()
-    assert st == 0 and torch.equal(out_r, gr)
+    assert torch.equal(out_r, gr)
     # the same terms in another split: fp32 partial sums, each rounding 2^-24 of the magnitudes added
     assert torch.allclose(out_c, gc, rtol=0, atol=float(gc.abs().max()) * 1e-5)
+
+
+# either side of the sizes where one pass takes over from the lists (64 entries: 3 * 2^16 vectors, 128 and 256: 2^21),
+# and 2^13 entries with the slices' sums in the workspace and in the radius gradient's array
+@pytest.mark.parametrize("fmt,n,k", [("W2", 1535, 1024), ("W2", 1536, 1024), ("W2_72", 4095, 4096), ("W2_72", 4096, 4096),
+                                     ("W3_cfg", 4095, 4096), ("W3_cfg", 4096, 4096), ("W3", 2047, 4096), ("W3", 2048, 4096)])
+@pytest.mark.parametrize("skew", [False, True])
+def test_backward_route_edges(fmt, n, k, skew):
+    check_backward(*make(fmt, n, k, skew=skew))
+
+
+def test_backward_time_in_place_and_with_a_crowded_centre():
+    """Neither writing a gradient over an input nor nine vectors in ten of one direction may leave the gradients
+    to a handful of workgroups (12 to 43 times and 780 times as long as plain calls where they did; now
+    about 1 and 30)."""
+    def us(fn):
+        best = float("inf")
+        for _ in range(5):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(5):
+                fn()
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b) * 200)
+        return best
+
+    for fmt in ("W2", "W3_cfg"):
+        args, gr, gc = check_backward(*make(fmt, 4096, 4096))
+        plain = us(lambda: B.fake_quant_backward(*args))
+        for over in ("rho", "codebook"):
+            assert us(in_place(over, args, gr, gc)[0]) <= 4 * plain, (fmt, over)
+    t = [us(lambda: B.fake_quant_backward(*a)) for a in (check_backward(*make("W3", 1024, 4096, skew=s))[0] for s in (False, True))]
+    assert t[1] <= 120 * t[0], t
