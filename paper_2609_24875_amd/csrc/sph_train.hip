@@ -21,6 +21,7 @@
 #include <stdint.h>
 
 #include <algorithm>
+#include <type_traits>
 #include <vector>
 
 #include "sph_fp.h"
@@ -433,9 +434,15 @@ __global__ __launch_bounds__(kThreads) void k_fq_grad_cb_part(int64_t nv, const 
 // product is cut into three bfloat16 words (8 + 8 + 8 bits: exactly its 24): the high and middle words of the
 // 8 coordinates are the 16 columns of one operand, the low words half of another. The words and the
 // directions reach the operands' layout through a few LDS rows of the wave's own. Adding an
-// exact zero rounds nothing, so a sum is rounded as often as a centre's vectors are added. Vectors with
-// a product that is not finite would spoil every centre (0 times infinity); their products are
-// added to their centre in LDS instead.
+// exact zero rounds nothing, so a sum is rounded as often as a centre's vectors are added. Products
+// that are not finite would spoil every centre (0 times infinity); a wave that meets one takes its vectors again
+// and adds such products to their centre in LDS instead.
+//
+// The matrix cores take subnormal bfloat16 words as zero, which unscaled would cost products below 2^-110 their low
+// words (gradients of 1e-33: error 8e-7 of the sums, of 1e-37: 8e-3). The radius carries a factor of 2^24 into the
+// products, so that the low words of every normal fp32 product stay normal. A wave that meets a product beyond
+// 2^80 takes its vectors again with 2^-40, so that no sum of finite products overflows before its own size does. (The
+// same loop with that case inside it took 3% longer.)
 //
 // The waves' sums are added in order (fp64) per block and stored as fp32, in d_ws where it holds all
 // blocks' sums, else in the radius gradient's first ncb * 8 values of the block's stretch, which
@@ -447,6 +454,7 @@ __global__ __launch_bounds__(kThreads) void k_fq_grad_cb_part(int64_t nv, const 
 // us, half vector-ALU work (the cuts and the one-hot words). Additions to
 // the wave's sums in LDS (ds_add_f32) took 260 us, one lane every three cycles.
 constexpr int kPassWaves = 8;
+constexpr float kPassUp = 0x1p24f, kPassDown = 0x1p-40f, kPassMost = 0x1p104f;
 typedef __bf16 bf8v __attribute__((ext_vector_type(8)));
 typedef float f4v __attribute__((ext_vector_type(4)));
 typedef uint16_t u2s __attribute__((ext_vector_type(2)));
@@ -494,93 +502,108 @@ __global__ __launch_bounds__(64 * kPassWaves) void k_fq_grad_pass(PassArgs a) {
   const uint16_t* rd1 = words[wv] + r * ROW + kb * 8;
   const uint16_t* rd2 = words[wv] + (16 + (r & 7)) * ROW + kb * 8;
   f4v hm[NT], lw[NT];   // sums of their own for the low words: chained into the others they cost 10%
+  bool again = false;
+  // the wave's vectors; CAREFUL: the small scale, and products that are not finite apart
+  auto run = [&](auto careful) {
+    constexpr bool CAREFUL = decltype(careful)::value;
+    constexpr float up = CAREFUL ? kPassDown : kPassUp;
+    constexpr int U = 2;
 #pragma unroll
-  for (int t = 0; t < NT; ++t) hm[t] = lw[t] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
-  constexpr int U = 2;
-  for (int64_t i0 = w0; i0 < w1; i0 += 32 * U) {
-    float4 g[U];
-    float rho[U], rh[U];
-    uint32_t z[U], s[U];
+    for (int t = 0; t < NT; ++t) hm[t] = lw[t] = f4v{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int64_t i0 = w0; i0 < w1; i0 += 32 * U) {
+      float4 g[U];
+      float rho[U], rh[U];
+      uint32_t z[U], s[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t i = min(i0 + 32 * u + own, w1 - 1);   // past the end: the last vector again, not counted
-      const int64_t row = packed ? 0 : i / a.nv;
-      g[u] = *reinterpret_cast<const float4*>(a.gw + row * a.ldg + (i - row * a.nv) * 8 + 4 * half);
-      rho[u] = a.rho[i];
-      rh[u] = a.r_hat[i];
-      z[u] = a.dir[i];
-      s[u] = (uint32_t)a.signs[i] >> (4 * half);
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t i = i0 + 32 * u + own;
-      const bool ok = i < w1;
-      const float4 c = cbl[z[u] * 2 + half];
-      const float gg[4] = {g[u].x, g[u].y, g[u].z, g[u].w};
-      const float cc[4] = {c.x, c.y, c.z, c.w};
-      float p[4], q[4];
-      bool fine = true;
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const float sg = ((s[u] >> j) & 1) ? -gg[j] : gg[j];
-        p[j] = sg * cc[j];
-        q[j] = ok ? rh[u] * sg : 0.0f;
-        fine = fine && fabsf(q[j]) <= 3.402823466e38f;
+      for (int u = 0; u < U; ++u) {
+        const int64_t i = min(i0 + 32 * u + own, w1 - 1);   // past the end: the last vector again, not counted
+        const int64_t row = packed ? 0 : i / a.nv;
+        g[u] = *reinterpret_cast<const float4*>(a.gw + row * a.ldg + (i - row * a.nv) * 8 + 4 * half);
+        rho[u] = a.rho[i];
+        rh[u] = a.r_hat[i];
+        z[u] = a.dir[i];
+        s[u] = (uint32_t)a.signs[i] >> (4 * half);
       }
-      const float mysum = (p[0] + p[1]) + (p[2] + p[3]);
-      const float total = mysum + __shfl_xor(mysum, 1, 64);   // the pairwise order of eight terms
-      if (half == 0 && ok && i >= keep) a.grho[i] = total * sigmoidf(rho[u]);
-      if (__any(!fine) && !fine) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int64_t i = i0 + 32 * u + own;
+        const bool ok = i < w1;
+        const float4 c = cbl[z[u] * 2 + half];
+        const float gg[4] = {g[u].x, g[u].y, g[u].z, g[u].w};
+        const float cc[4] = {c.x, c.y, c.z, c.w};
+        float p[4], q[4];
+        [[maybe_unused]] bool fine = true;
+        const float rs = rh[u] * up;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-          atomicAdd(&odd[z[u] * 8 + 4 * half + j], q[j]);
-          q[j] = 0.0f;
+          const float sg = ((s[u] >> j) & 1) ? -gg[j] : gg[j];
+          p[j] = sg * cc[j];
+          q[j] = ok ? rs * sg : 0.0f;
+          if constexpr (CAREFUL) {
+            const float raw = ok ? rh[u] * sg : 0.0f;
+            if (!(fabsf(raw) <= 3.402823466e38f)) {
+              atomicAdd(&odd[z[u] * 8 + 4 * half + j], raw);
+              q[j] = 0.0f;
+            }
+          } else {
+            fine = fine && fabsf(q[j]) <= kPassMost;
+          }
         }
-      }
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const uint32_t b = __builtin_bit_cast(uint32_t, q[j]);
-        const float r1 = q[j] - __builtin_bit_cast(float, b & 0xFFFF0000u);
-        const uint32_t m = __builtin_bit_cast(uint32_t, r1);
-        const float r2 = r1 - __builtin_bit_cast(float, m & 0xFFFF0000u);
-        wr[j * ROW] = (uint16_t)(b >> 16);
-        wr[(8 + j) * ROW] = (uint16_t)(m >> 16);
-        wr[(16 + j) * ROW] = (uint16_t)(__builtin_bit_cast(uint32_t, r2) >> 16);
-      }
-      if (half == 0) zs[wv][own] = (uint16_t)z[u];
-      // the LDS performs a wave's operations in issue order: these reads see the writes above, and
-      // the next vectors' writes come after them
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-      __builtin_amdgcn_wave_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-      const uint4 zq = *(const uint4*)(zs[wv] + kb * 8);
-      const bf8v x1 = *(const bf8v*)rd1;
-      uint4 x2w = *(const uint4*)rd2;
-      if (r >= 8) x2w = make_uint4(0, 0, 0, 0);
-      const bf8v x2 = __builtin_bit_cast(bf8v, x2w);
-      const uint32_t zw[4] = {zq.x, zq.y, zq.z, zq.w};
-#pragma unroll
-      for (int t = 0; t < NT; ++t) {
-        const uint32_t c2 = (uint32_t)(16 * t + r) * 0x10001u;
-        uint32_t o[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const u2s d = __builtin_elementwise_min(__builtin_bit_cast(u2s, zw[k] ^ c2), u2s{1, 1});
-          o[k] = __builtin_bit_cast(uint32_t, (u2s)(u2s{0x3F80, 0x3F80} - d * u2s{0x3F80, 0x3F80}));   // 1.0 where equal
+        if constexpr (!CAREFUL) {
+          again = again || !fine;
+          const float mysum = (p[0] + p[1]) + (p[2] + p[3]);
+          const float total = mysum + __shfl_xor(mysum, 1, 64);   // the pairwise order of eight terms
+          if (half == 0 && ok && i >= keep) a.grho[i] = total * sigmoidf(rho[u]);
         }
-        const bf8v one = __builtin_bit_cast(bf8v, make_uint4(o[0], o[1], o[2], o[3]));
-        hm[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(one, x1, hm[t], 0, 0, 0);
-        lw[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(one, x2, lw[t], 0, 0, 0);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const uint32_t b = __builtin_bit_cast(uint32_t, q[j]);
+          const float r1 = q[j] - __builtin_bit_cast(float, b & 0xFFFF0000u);
+          const uint32_t m = __builtin_bit_cast(uint32_t, r1);
+          const float r2 = r1 - __builtin_bit_cast(float, m & 0xFFFF0000u);
+          wr[j * ROW] = (uint16_t)(b >> 16);
+          wr[(8 + j) * ROW] = (uint16_t)(m >> 16);
+          wr[(16 + j) * ROW] = (uint16_t)(__builtin_bit_cast(uint32_t, r2) >> 16);
+        }
+        if (half == 0) zs[wv][own] = (uint16_t)z[u];
+        // the LDS performs a wave's operations in issue order: these reads see the writes above, and
+        // the next vectors' writes come after them
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        const uint4 zq = *(const uint4*)(zs[wv] + kb * 8);
+        const bf8v x1 = *(const bf8v*)rd1;
+        uint4 x2w = *(const uint4*)rd2;
+        if (r >= 8) x2w = make_uint4(0, 0, 0, 0);
+        const bf8v x2 = __builtin_bit_cast(bf8v, x2w);
+        const uint32_t zw[4] = {zq.x, zq.y, zq.z, zq.w};
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          const uint32_t c2 = (uint32_t)(16 * t + r) * 0x10001u;
+          uint32_t o[4];
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            const u2s d = __builtin_elementwise_min(__builtin_bit_cast(u2s, zw[k] ^ c2), u2s{1, 1});
+            o[k] = __builtin_bit_cast(uint32_t, (u2s)(u2s{0x3F80, 0x3F80} - d * u2s{0x3F80, 0x3F80}));   // 1.0 where equal
+          }
+          const bf8v one = __builtin_bit_cast(bf8v, make_uint4(o[0], o[1], o[2], o[3]));
+          hm[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(one, x1, hm[t], 0, 0, 0);
+          lw[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(one, x2, lw[t], 0, 0, 0);
+        }
       }
     }
-  }
+  };
+  run(std::false_type{});
+  const bool redo = __any(again);
+  if (redo) run(std::true_type{});
+  const double down = redo ? 1.0 / kPassDown : 1.0 / kPassUp;
   // lane (column, rows 4 * kb + e) of tile t: high words in columns 0..7, middle in 8..15, low in 0..7
 #pragma unroll
   for (int t = 0; t < NT; ++t)
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const float mid = __shfl_xor(hm[t][e], 8, 64);
-      if (r < 8) sums[wv][(16 * t + 4 * kb + e) * 8 + r] = (float)((double)hm[t][e] + ((double)mid + (double)lw[t][e]));
+      if (r < 8) sums[wv][(16 * t + 4 * kb + e) * 8 + r] = (float)(((double)hm[t][e] + ((double)mid + (double)lw[t][e])) * down);
     }
   __syncthreads();
   float* out = a.part ? a.part + (int64_t)blockIdx.x * nval : a.grho + b0;
@@ -791,7 +814,7 @@ sph_status sph_fake_quant_backward(const sph_format* fmt, int64_t n, int64_t k, 
   const int64_t least = (int64_t)kPassWaves * std::max(128, ncb);
   const int64_t nblk = std::max<int64_t>(1, std::min<int64_t>(512, nvec / least));
   const bool in_ws = nblk <= ws_slices(ncb);
-  if (ncb <= 256 && (in_ws || free_rho) && (ncb <= 32 || nvec >= (ncb <= 64 ? 3ll << 16 : 1ll << 21))) {
+  if (ncb <= 256 && free_rho && (ncb <= 32 || nvec >= (ncb <= 64 ? 3ll << 16 : 1ll << 21))) {
     PassArgs a{nv, nvec, d_rho, d_signs, d_dir_idx, d_codebook, d_r_hat, d_grad_w, ldg, d_grad_rho, in_ws ? (float*)d_ws : nullptr, ncb};
     bool ok = launch_ok(ncb <= 16 ? (const void*)k_fq_grad_pass<16> : ncb <= 64 ? (const void*)k_fq_grad_pass<64> : (const void*)k_fq_grad_pass<256>, dim3((unsigned)nblk),
                         dim3(64 * kPassWaves), s, a) &&

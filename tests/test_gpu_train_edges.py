@@ -136,6 +136,27 @@ def test_backward_gradients_not_finite(fmt):
     check_backward(D, V, rho, signs, z, cb, skip=[(5, np.inf), (70000 % z.size, np.nan), (31, 1e37)])
 
 
+@pytest.mark.parametrize("fmt", ["W2", "W2_cfg", "W3_cfg", "W3"])
+@pytest.mark.parametrize("scale", [1e-36, 1e-34, 1e-32, 1.0, 1e20, 1e26, 1e34])
+def test_backward_gradient_scales(fmt, scale):
+    """Gradients of any size that fp32 holds, some rows a million times smaller or larger than the others."""
+    n, k = 2048, 8192
+    D, V, rho, signs, z, cb = make(fmt, n, k)
+    r_hat = forward(D, V, rho, signs, z, cb)[1]
+    gw = torch.randn((n, k), generator=torch.Generator(DEV).manual_seed(3), device=DEV)
+    gw[::31] *= 1e-6
+    gw[1::97] *= 30.0
+    gw = (gw.double() * scale).float()
+    perm, off = (dev(a) for a in B.direction_groups(D, z))
+    gc = B.fake_quant_backward(D, V, dev(rho), dev(signs), dev(z.view(np.int16)), dev(cb), r_hat, gw, perm, off)[1].double()
+    i = perm.long()
+    p = r_hat.reshape(-1)[i].double()[:, None] * dev(sign_of(signs)).reshape(-1, 8)[i] * gw.reshape(-1, 8)[i].double() / scale
+    run = torch.cat([torch.zeros((1, 8), dtype=torch.float64, device=DEV), p.cumsum(dim=0)])
+    ref = run[off[1:]] - run[off[:-1]]
+    # a rounding of each product and a few of the sums, each of at most 2^-24, over the norm
+    assert float((gc / scale - ref).norm() / ref.norm()) <= 8 * 2.0 ** -24
+
+
 def in_place(over, args, gr, gc):
     """The gradients again through the C entry point, one of them over an input: a callable and its outputs."""
     import ctypes
