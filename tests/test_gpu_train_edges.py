@@ -92,6 +92,21 @@ def test_forward_hard_levels(fmt):
     check_forward(D, V, rho, signs, z, cb)
 
 
+@pytest.mark.parametrize("fmt", ["W2", "W3", "W3_cfg"])
+def test_forward_parameters_that_are_no_numbers(fmt):
+    """They count as 0 (radius log 2), for their own vector and in their group's offset and step, alone or in
+    groups full of them."""
+    D, V, rho, signs, z, cb = make(fmt, 40, 1024)
+    rho.reshape(-1)[::37] = 0.0
+    rho[3, 16:32] = 0.0
+    want = forward(D, V, rho, signs, z, cb)
+    rho.reshape(-1)[::37] = np.nan
+    rho[3, 16:32] = np.nan
+    got = forward(D, V, rho, signs, z, cb)
+    assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+    assert all(torch.equal(got[2][key], want[2][key]) for key in want[2])
+
+
 def check_backward(D, V, rho, signs, z, cb, skip=()):
     n, nv = rho.shape
     w, r_hat = forward(D, V, rho, signs, z, cb)[:2]
