@@ -132,8 +132,9 @@ sph_status sph_gemm_small(const sph_weights* w, const void* d_x, int64_t m, int6
  * rebuilt once per 64-row slice of X and per 128-column chunk of K; or, on large shapes, with the
  * radius applied first and radius times direction split into two fp16 operands (23 bits), rebuilt
  * once per 128-row slice, where the rounding error is no larger: that needs group offsets of 0 or of
- * at least 2^-12 of the group's largest radius (found by sph_pack_weights and kept in the
- * descriptor). Same argument rules as sph_gemm_small. When the
+ * at least 2^-12 of the group's largest radius, and neither zero offsets nor zero steps in more than 3
+ * groups of 16 (found by sph_pack_weights and kept in the
+ * descriptor), and enough columns. Same argument rules as sph_gemm_small. When the
  * grid would not cover the chip, K is split and fp32 partial outputs go through the workspace
  * (sph_workspace_bytes(w, m); for m > 32 it needs no zero-fill) and are added in a fixed order,
  * so repeated calls give bitwise identical results. Asynchronous on `stream`. */

@@ -1449,7 +1449,7 @@ __global__ void __launch_bounds__(PF_THREADS) k_gemm_prefill(KArgs a) {
 // weights of position group i + 1 are rebuilt between the lo and the hi products of group i.
 //
 // Measured (one box, HIP events, us; three-product kernel -> this one): W2 24576x4096 at 256 rows
-// 176 -> 116 (T = 12; T = 16 takes 134), W2 5120x5120 at 1024 217 -> 134, W3 4096x12288 at 2048
+// 176 -> 106 (T = 12), W2 5120x5120 at 1024 217 -> 134, W3 4096x12288 at 2048
 // 550 -> 388, W3_cfg 9000x3072 at 700 146 -> 102. Three waves' VALU work per two matrix instructions
 // is what remains: a fold per half chunk cost 15%, fp16 conversions through fp32 products 10%,
 // v_fma_mixlo/hi_f16 (half rate) 8%, 32x32x16 products 20%, all more exact by under 4%.
@@ -2098,15 +2098,18 @@ PrefillPlan prefill_plan(const sph_weights* w, int64_t m) {
   return P;
 }
 
-// The plan of a batch above 32 on the two-product kernel, where it applies and pays; otherwise
+// The plan of a batch above 64 on the two-product kernel, where it applies and pays; otherwise
 // wide = 0. It applies to matrices flagged at pack time, and where its rounding error is no larger
-// than the three-product kernel's under plan `old`. In units of the variance of one rounding at
-// the size of the result, with C chunks per K range: C / 2 for the folds, 14.5 for the roundings of
-// a chunk's sums and 2.2 for the operands here, against C for two folds, 6 and, before its partials
-// were added in fp64, ks / 2 there (measured on fp32 outputs against fp64: 1.22e-7 against 1.25e-7
-// for W2 6144x4096 at 256 rows, where the two sides are 20 and 23). It pays by a cost in ns fitted to
-// the launches named at the kernel and at 14 other shapes (within 15%): 4.0 us per chunk and round
-// of workgroups with 16 tiles, 3.2 with 12, 3.2 on the three-product kernel; split-K partials 4 us
+// than the three-product kernel's under plan `old`. Variance of fp32 outputs against fp64, relative to the
+// outputs' and in units of 2^-48, fitted to 119 matrices of W2, W3, W3_cfg and (8, 2) with 4 to 97 chunks
+// and 1 to 16 K ranges, encoded radii and others (within 3% of each in the error itself, C chunks per range):
+//   three products  0.18 C + 1.3, and 0.104 per range of a split
+//   two products    0.10 C + 3.2, and 0.05 + 0.005 C + 0.0075 per chunk of all ranges for a split
+// So one range takes it from 24 chunks on (k = 3072); 6144x4096 at 256 rows in 4 ranges is the same error
+// (1.249e-7 against 1.244e-7), 4096x12288 at 66 rows in 11 would be 6% more and keeps three products.
+//
+// It pays by a cost in ns fitted to the launches named at the kernel and at 14 other shapes (within 15%): 4.0 us per
+// chunk and round of workgroups with 16 tiles, 3.2 with 12, 3.2 on the three-product kernel; split-K partials 4 us
 // and 1 us per megabyte.
 PrefillPlan wide_plan(const sph_weights* w, int64_t m, const PrefillPlan& old) {
   PrefillPlan best{};
@@ -2119,12 +2122,13 @@ PrefillPlan wide_plan(const sph_weights* w, int64_t m, const PrefillPlan& old) {
     return ks > 1 ? c + 4000 + (int64_t)(partial_bytes(w, m, ks) / 1000) : c;
   };
   int64_t least = cost((int64_t)old.gx * old.gy, old.ks, 3200);
-  const double old_err = (double)ng / old.ks + 6.0 + (old.ks > 1 ? old.ks / 2.0 : 0.0);
+  const double old_err = 0.18 * ng / old.ks + (old.ks > 1 ? 0.104 * old.ks : 0.0);
   for (const int T : {16, 12}) {
     const int64_t gx = (nt + T - 1) / T, gy = (m + PW_MC - 1) / PW_MC;
     const int64_t most = std::max<int64_t>(1, std::min<int64_t>(std::min<int64_t>(cus / (gx * gy), ng), PF_KS_MAX));
     for (int64_t ks = 1; ks <= most; ++ks) {
-      if (ng / (2.0 * ks) + 16.7 > old_err) continue;
+      const double err = 1.9 + 0.1 * ng / ks + (ks > 1 ? 0.05 + 0.005 * ng / ks + 0.0075 * ng : 0.0);
+      if (err > old_err) continue;
       const int64_t c = cost(gx * gy, ks, T == 16 ? 4000 : 3200);
       if (c >= least) continue;
       least = c;

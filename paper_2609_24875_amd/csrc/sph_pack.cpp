@@ -106,12 +106,16 @@ bool sph_host_radius_split(const sph_format* fmt, int64_t n, int64_t k, const ui
   if (fmt->vec_dim != SPH_VEC) return false;
   const int64_t ngrp = n * (k / SPH_GROUP);
   const float top = (float)((1 << fmt->radius_bits) - 1);
+  int64_t one = 0, both = 0;   // groups with only one of the two parameters, or with both
   for (int64_t i = 0; i < ngrp; ++i) {
     const uint16_t oh = gmin[i] & 0x7FFF, sh = gstep[i] & 0x7FFF;
+    one += (oh == 0) != (sh == 0);
+    both += oh != 0 && sh != 0;
     if (oh >= sh || oh == 0) continue;   // an offset of at least the step is above (2^V - 1 <= 255) / 4096 of it
     const float o = f16_value(oh), s = f16_value(sh);
     if (o * 4096.0f < o + top * s) return false;
   }
+  if (one * 13 > both * 3) return false;
   for (int64_t z = 0; z < (int64_t(1) << fmt->dir_bits); ++z) {
     uint16_t most = 0;   // entries are non-negative, so their bit patterns order them
     for (int j = 0; j < SPH_VEC; ++j) {

@@ -1,22 +1,28 @@
 """CPU checks of the two-product prefill kernel's routing and work split, on a model that restates
 `wide_plan()`, the kernel's tile and K-range bounds and its LDS sizes in
 paper_2609_24875_amd/csrc/sph_kernels.hip, and of the pack-time flag that admits a matrix to it
-(`sph_host_radius_split()`, through the packer built for the host).
+(`sph_host_radius_split()` itself, from csrc/sph_pack.cpp built for the host).
 
 - every row tile belongs to exactly one wave, every chunk to exactly one K range, for 12 and 16 tiles
   per workgroup;
 - partial outputs fit the workspace the plan sizes;
 - the modelled rounding error of the chosen plan is never above the three-product kernel's;
-- no plan is chosen at up to 64 batch rows or without the flag.
+- no plan is chosen at up to 64 batch rows or without the flag;
+- the flag is set exactly where its conditions hold, at their edges.
 """
 from __future__ import annotations
 
+import os
 import random
+import shutil
+import subprocess
 
+import numpy as np
 import pytest
 
 from test_prefill_plan_model import prefill_plan
 
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 PW_MC, KS_MAX = 128, 16
 
 
@@ -35,19 +41,19 @@ def wide_plan(n: int, k: int, m: int, cus: int = 256, flag: bool = True) -> dict
         return c + 4000 + partial_bytes(n, m, ks) // 1000 if ks > 1 else c
 
     least = cost(old["gx"] * old["gy"], old["ks"], 3200)
-    old_err = ng / old["ks"] + 6.0 + (old["ks"] / 2.0 if old["ks"] > 1 else 0.0)
+    old_err = 0.18 * ng / old["ks"] + (0.104 * old["ks"] if old["ks"] > 1 else 0.0)
     best = None
     for T in (16, 12):
         gx, gy = (nt + T - 1) // T, (m + PW_MC - 1) // PW_MC
         most = max(1, min(min(cus // (gx * gy), ng), KS_MAX))
         for ks in range(1, most + 1):
-            if ng / (2.0 * ks) + 16.7 > old_err:
+            err = 1.9 + 0.1 * ng / ks + (0.05 + 0.005 * ng / ks + 0.0075 * ng if ks > 1 else 0.0)
+            if err > old_err:
                 continue
             c = cost(gx * gy, ks, 4000 if T == 16 else 3200)
             if c < least:
                 least = c
-                best = dict(T=T, gx=gx, gy=gy, ks=ks, nt=nt, ng=ng, err=ng / (2.0 * ks) + 16.7, old_err=old_err,
-                            ws=partial_bytes(n, m, ks))
+                best = dict(T=T, gx=gx, gy=gy, ks=ks, nt=nt, ng=ng, err=err, old_err=old_err, ws=partial_bytes(n, m, ks))
     return best
 
 
@@ -75,14 +81,19 @@ def check(n: int, k: int, m: int, cus: int = 256) -> bool:
     return True
 
 
-# shapes of the GPU test (tests/test_gpu_prefill_wide.py): both tile counts, with and without a K split
-WIDE_SHAPES = {(1033, 12416, 65): (12, 15), (17462, 1664, 65): (16, 3), (21885, 2816, 129): (12, 1), (24686, 2816, 129): (16, 1)}
+# shapes of the GPU tests (tests/test_gpu_prefill_wide.py): both tile counts, with and without a K split; then
+# those whose batches run through the rows per workgroup
+WIDE_SHAPES = {(10764, 3968, 66): (12, 4), (16627, 2304, 65): (16, 3), (21807, 3072, 129): (12, 1), (24629, 3072, 130): (16, 1)}
+ROW_SHAPES = {**{(10753, 3968, m): (12, 4) for m in (80, 81, 96, 97, 112, 113, 128)},
+              **{(7169, 3968, m): (16, 4) for m in (160, 161, 192, 193, 224, 225)}}
 
 
-@pytest.mark.parametrize("n,k,m", WIDE_SHAPES)
+@pytest.mark.parametrize("n,k,m", [*WIDE_SHAPES, *ROW_SHAPES])
 def test_gpu_test_shapes_take_the_wide_kernel(n, k, m):
+    want = {**WIDE_SHAPES, **ROW_SHAPES}[n, k, m]
+    assert check(n, k, m)
     P = wide_plan(n, k, m)
-    assert check(n, k, m) and (P["T"], P["ks"]) == WIDE_SHAPES[(n, k, m)]
+    assert (P["T"], P["ks"]) == want
 
 
 def test_random_shapes():
@@ -101,18 +112,133 @@ def test_lds_fits():
         assert table + 2 * PW_MC * kc * 2 <= 160 * 1024
 
 
-def split_flag(gmin, gstep, codebook, radius_bits: int) -> bool:
-    """`sph_host_radius_split()` on values."""
-    top = (1 << radius_bits) - 1
-    return (all(o == 0 or abs(o) * 4096 >= abs(o) + top * s for o, s in zip(gmin, gstep))
-            and all(max(c) == 0 or max(c) >= 0.25 for c in codebook))
+DRIVER = r"""
+#include <cstdio>
+#include <vector>
+#include "../../paper_2609_24875_amd/csrc/sph_host.h"
+int main(int argc, char** argv) {
+  FILE* f = argc == 2 ? fopen(argv[1], "rb") : nullptr;
+  int32_t h[2];   // direction and radius bits, then rows and columns
+  int64_t nk[2];
+  while (f && fread(h, 4, 2, f) == 2 && fread(nk, 8, 2, f) == 2) {
+    const size_t g = (size_t)(nk[0] * (nk[1] / 128)), c = (size_t)8 << h[0];
+    std::vector<uint16_t> off(g), st(g), cb(c);
+    if (fread(off.data(), 2, g, f) != g || fread(st.data(), 2, g, f) != g || fread(cb.data(), 2, c, f) != c) return 2;
+    const sph_format fmt = {8, h[0], h[1], 128};
+    printf("%d\n", sph_host_radius_split(&fmt, nk[0], nk[1], off.data(), st.data(), cb.data()) ? 1 : 0);
+  }
+  return f ? 0 : 1;
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def host_flag(tmp_path_factory):
+    """flag(cases): `sph_host_radius_split()` of (D, V, offsets, steps, codebook) in fp16 bits, offsets and
+    steps [n][k/128]."""
+    gxx = shutil.which("g++")
+    if gxx is None:
+        pytest.skip("g++ not available")
+    d = tmp_path_factory.mktemp("flag")
+    src, exe = d / "a" / "b" / "flag.cpp", str(d / "flag")
+    src.parent.mkdir(parents=True)
+    os.symlink(os.path.join(ROOT, "paper_2609_24875_amd"), d / "paper_2609_24875_amd")
+    os.symlink(os.path.join(ROOT, "include"), d / "include")
+    src.write_text(DRIVER)
+    res = subprocess.run([gxx, "-std=c++17", "-O1", "-I", os.path.join(ROOT, "include"), str(src),
+                          os.path.join(ROOT, "paper_2609_24875_amd", "csrc", "sph_pack.cpp"), "-o", exe], capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr
+
+    def flag(cases):
+        path = d / "cases.bin"
+        with open(path, "wb") as f:
+            for D, V, off, st, cb in cases:
+                f.write(np.array([D, V], np.int32).tobytes() + np.array([off.shape[0], off.shape[1] * 128], np.int64).tobytes())
+                for a in (off, st, cb):
+                    f.write(np.ascontiguousarray(a, np.uint16).tobytes())
+        out = subprocess.run([exe, str(path)], capture_output=True, text=True, timeout=60)
+        assert out.returncode == 0
+        return [int(x) for x in out.stdout.split()]
+
+    return flag
+
+
+def split_flag(off, st, cb, V: int) -> int:
+    """The flag's conditions on fp16 bits, in fp64 (exact)."""
+    o, s = (np.asarray(a, np.uint16).view(np.float16).astype(np.float64).reshape(-1) for a in (off, st))
+    c = np.asarray(cb, np.uint16).view(np.float16).astype(np.float64).max(axis=1)
+    o = np.abs(o)
+    one, both = int(((o == 0) != (s == 0)).sum()), int(((o != 0) & (s != 0)).sum())
+    return int(np.all((o == 0) | (o * 4096 >= o + (2 ** V - 1) * s)) and np.all((c == 0) | (c >= 0.25)) and 16 * one <= 3 * (one + both))
+
+
+def bits(a):
+    return np.asarray(a, np.float64).astype(np.float16).view(np.uint16)
+
+
+def test_flag_at_its_edges(host_flag):
+    g = np.random.default_rng(11)
+    cases, want = [], []
+
+    def case(D, V, off, st, cb=None, flag=None):
+        if cb is None:
+            a = np.abs(g.standard_normal((1 << D, 8)))
+            cb = bits(a / np.linalg.norm(a, axis=1, keepdims=True))
+        cases.append((D, V, off, st, cb))
+        want.append(split_flag(off, st, cb, V) if flag is None else flag)
+        assert flag is None or split_flag(off, st, cb, V) == flag
+
+    plain = lambda v: np.full((4, 8), v, np.uint16)
+    for V, D in ((2, 6), (3, 6), (4, 6), (8, 8), (3, 13)):
+        top = 2 ** V - 1
+        # one group's offset on either side of 2^-12 of its largest radius, of either sign
+        for step in (1.0, 0.0371, 2.0 ** -9):
+            st = bits(step)
+            edge = top * float(st.view(np.float16)) / 4095
+            near = bits(edge)
+            for k in range(-2, 3):
+                for sign in (0, 0x8000):
+                    off, steps = plain(0x3800), plain(int(st))
+                    off[2, 3] = (int(near) + k) | sign
+                    case(D, V, off, steps)
+        # subnormal offsets and steps, zeros of either sign
+        for o, s in ((0x0001, 0x0001), (0x0001, 0x0400), (0x03FF, 0x0001), (0x8001, 0x0003), (0x8000, 0x3C00), (0x0000, 0x3C00), (0x7BFF, 0x7BFF)):
+            off, st = plain(0x3800), plain(0x2000)
+            off[0, 0], st[0, 0] = o, s
+            case(D, V, off, st)
+        # zero offsets or steps in 3 and 4 of 16 groups; all-zero groups do not count
+        for which in (0, 1):
+            for bad, flag in ((6, 1), (7, 0)):
+                p = [plain(0x3800), plain(0x2000)]
+                p[which].reshape(-1)[:bad] = 0
+                case(D, V, *p, flag=flag)
+        off, st = plain(0x3800), plain(0x2000)
+        off[:3], st[:3] = 0, 0
+        case(D, V, off, st, flag=1)
+        case(D, V, plain(0), plain(0), flag=1)
+        case(D, V, plain(0), plain(0x2000), flag=0)
+        case(D, V, plain(0x3800), plain(0), flag=0)
+        # the largest coordinate of one entry just below and at 1/4, and an entry of zeros
+        for top_bits, flag in ((0x33FF, 0), (0x3400, 1), (0x0000, 1), (0x0001, 0)):
+            cb = np.full((1 << D, 8), 0x3500, np.uint16)
+            cb[5] = 0
+            cb[5, 3] = top_bits
+            case(D, V, plain(0x3800), plain(0x2000), cb, flag=flag)
+    for _ in range(200):
+        V, D = int(g.choice([2, 3, 4, 8])), 6
+        off = bits(g.choice([-1, 1], (3, 5)) * 2.0 ** g.uniform(-24, 15, (3, 5)))
+        st = bits(2.0 ** g.uniform(-24, 15, (3, 5)))
+        if g.random() < 0.7:   # near the edge
+            st = bits(np.minimum(np.abs(off.view(np.float16).astype(np.float64)) * 4095 / (2 ** V - 1) * 2.0 ** g.uniform(-1, 0.002, (3, 5)), 6e4))
+        off[g.random((3, 5)) < 0.1] = 0
+        case(D, V, off, st)
+    assert host_flag(cases) == want and 0.2 < sum(want) / len(want) < 0.9
 
 
 def test_flag_bounds_the_operand_error():
     """rho * t as two fp16 words (the kernel's rt_split) against the exact product, at the edges of
     what the flag admits: the error stays within 2^-25 of the vector's length in units where the
     group's largest radius is 2^13..2^14, or 1.5 fp32 roundings of the product."""
-    import numpy as np
     f16 = np.float16
     g = np.random.default_rng(5)
     for V in (2, 3, 4, 8):
@@ -122,7 +248,7 @@ def test_flag_bounds_the_operand_error():
             off = (ratio * top * step * 1.001).astype(f16).astype(np.float64) * g.choice([-1, 1], 64)
             cb = np.abs(g.standard_normal((64, 8)))
             cb = (cb / np.linalg.norm(cb, axis=1, keepdims=True)).astype(f16).astype(np.float64)
-            assert split_flag(off, step, cb, V)
+            assert split_flag(bits(off), bits(step), bits(cb), V)
             up = 2.0 ** (13 - np.floor(np.log2(np.abs(off) + top * step)))
             for q in {0, 1, top // 2, top}:
                 rho = ((off + q * step) * up).astype(np.float32).astype(np.float64)
