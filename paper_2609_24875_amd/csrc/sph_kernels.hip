@@ -2108,9 +2108,13 @@ PrefillPlan prefill_plan(const sph_weights* w, int64_t m) {
 // So one range takes it from 24 chunks on (k = 3072); 6144x4096 at 256 rows in 4 ranges is the same error
 // (1.249e-7 against 1.244e-7), 4096x12288 at 66 rows in 11 would be 6% more and keeps three products.
 //
-// It pays by a cost in ns fitted to the launches named at the kernel and at 14 other shapes (within 15%): 4.0 us per
-// chunk and round of workgroups with 16 tiles, 3.2 with 12, 3.2 on the three-product kernel; split-K partials 4 us
-// and 1 us per megabyte.
+// It pays by a cost in ns per chunk and round of workgroups, plus 4 us and 1 us per megabyte of partials for a
+// split: two products 4000 with 16 tiles and 3200 with 12 (the 2^13 codebook with 4 radius bits, which has a third
+// stream to read, 5000 and 4000), three products 3200 with 64 batch rows per workgroup and 2600 with
+// 48. Within 15% of 50 shapes with 128 batch rows per workgroup; 80 to 112 rows take up to a quarter less than it
+// says, so at 65 to 112 rows three products may be kept where two are a little faster. With 3200 for
+// 48 rows too (8, 2) 21429x1920 at 81 rows took 40.6 us on this kernel against 38.6, and with 4000 for the third
+// stream (13, 4) 1703x12672 at 321 rows 74.4 against 70.1.
 PrefillPlan wide_plan(const sph_weights* w, int64_t m, const PrefillPlan& old) {
   PrefillPlan best{};
   if (m <= 64 || !(w->off[SPH_OFF_FLAGS] & SPH_FLAG_RADIUS_SPLIT)) return best;
@@ -2121,7 +2125,7 @@ PrefillPlan wide_plan(const sph_weights* w, int64_t m, const PrefillPlan& old) {
     const int64_t c = (wgs * ks + cus - 1) / cus * ((ng + ks - 1) / ks) * per_chunk;
     return ks > 1 ? c + 4000 + (int64_t)(partial_bytes(w, m, ks) / 1000) : c;
   };
-  int64_t least = cost((int64_t)old.gx * old.gy, old.ks, 3200);
+  int64_t least = cost((int64_t)old.gx * old.gy, old.ks, old.mc == 48 ? 2600 : 3200);
   const double old_err = 0.18 * ng / old.ks + (old.ks > 1 ? 0.104 * old.ks : 0.0);
   for (const int T : {16, 12}) {
     const int64_t gx = (nt + T - 1) / T, gy = (m + PW_MC - 1) / PW_MC;
@@ -2129,7 +2133,7 @@ PrefillPlan wide_plan(const sph_weights* w, int64_t m, const PrefillPlan& old) {
     for (int64_t ks = 1; ks <= most; ++ks) {
       const double err = 1.9 + 0.1 * ng / ks + (ks > 1 ? 0.05 + 0.005 * ng / ks + 0.0075 * ng : 0.0);
       if (err > old_err) continue;
-      const int64_t c = cost(gx * gy, ks, T == 16 ? 4000 : 3200);
+      const int64_t c = cost(gx * gy, ks, kind == SPH_KIND_CB13Q4 ? (T == 16 ? 5000 : 4000) : T == 16 ? 4000 : 3200);
       if (c >= least) continue;
       least = c;
       best.gx = (int)gx;

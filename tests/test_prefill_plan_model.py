@@ -8,6 +8,7 @@ reduce's 16-byte accesses in paper_2609_24875_amd/csrc/sph_kernels.hip (no GPU i
 - every partial output the kernel writes and every 16-byte group the reduce reads or clears lies
   inside the workspace the plan sizes, 16-byte aligned, and the reduce covers each written
   partial exactly once;
+- every row tile and batch row is covered by workgroups none of which is empty, on 16, 32, 48 or 64 batch rows;
 - batches 9..16 go to the prefill kernel exactly from 120 * 2^20 weights.
 """
 from __future__ import annotations
@@ -20,7 +21,7 @@ PF_WAVES, PF_TPW, PF_KS_MAX = 8, 2, 16
 
 
 def prefill_mc(m: int) -> int:
-    return 16 if m <= 16 else 32 if m <= 32 else 64
+    return 16 if m <= 16 else 32 if m <= 32 else 48 if (m + 47) // 48 == (m + 63) // 64 else 64
 
 
 def prefill_plan(n: int, k: int, m: int, cus: int = 256) -> dict:
@@ -47,6 +48,9 @@ def check(n: int, k: int, m: int, cus: int = 256):
     nt, ng, ks = P["nt"], P["ng"], P["ks"]
     assert 1 <= ks <= PF_KS_MAX and ks <= ng
     assert P["gx"] * P["gy"] * ks <= max(cus, P["gx"] * P["gy"])
+    # row tiles and batch rows covered, no workgroup without one
+    assert P["gx"] * PF_WAVES * PF_TPW >= nt > (P["gx"] - 1) * PF_WAVES * PF_TPW
+    assert P["gy"] * P["mc"] >= m > (P["gy"] - 1) * P["mc"]
     # K ranges of blockIdx.z: [nc z / ks, nc (z + 1) / ks)
     bounds = [(ng * z // ks, ng * (z + 1) // ks) for z in range(ks)]
     assert bounds[0][0] == 0 and bounds[-1][1] == ng
@@ -89,8 +93,16 @@ def test_prefill_split_random_shapes():
     for _ in range(200):
         n = rng.randint(1, 60000)
         k = 128 * rng.randint(1, 200)
-        m = rng.choice([9, 12, 16, 17, 24, 32, 33, 64, 65, 128, 256, 1000])
+        m = rng.choice([9, 12, 16, 17, 24, 32, 33, 48, 49, 64, 65, 96, 97, 128, 129, 144, 145, 256, 1000])
         check(n, k, m, cus=rng.choice([256, 304, 80]))
+
+
+def test_batch_rows_per_workgroup():
+    """48 rows exactly where as many workgroups then cover the batch as with 64."""
+    assert [m for m in range(33, 400) if prefill_mc(m) == 48] == [*range(33, 49), *range(65, 97), *range(129, 145)]
+    for m in range(1, 5000):
+        mc = prefill_mc(m)
+        assert (m + mc - 1) // mc == (m + 63) // 64 or m <= 32
 
 
 def test_split_ranges_never_exceed_the_reduce_limit():

@@ -30,7 +30,8 @@ def partial_bytes(n: int, m: int, ks: int) -> int:
     return ks * m * ((n + 15) // 16) * 16 * 4 if ks > 1 else 0
 
 
-def wide_plan(n: int, k: int, m: int, cus: int = 256, flag: bool = True) -> dict | None:
+def wide_plan(n: int, k: int, m: int, cus: int = 256, flag: bool = True, third_stream: bool = False) -> dict | None:
+    """``third_stream``: the 2^13 codebook with 4 radius bits."""
     if m <= 64 or not flag:
         return None
     nt, ng = (n + 15) // 16, k // 128
@@ -40,7 +41,7 @@ def wide_plan(n: int, k: int, m: int, cus: int = 256, flag: bool = True) -> dict
         c = (wgs * ks + cus - 1) // cus * ((ng + ks - 1) // ks) * per_chunk
         return c + 4000 + partial_bytes(n, m, ks) // 1000 if ks > 1 else c
 
-    least = cost(old["gx"] * old["gy"], old["ks"], 3200)
+    least = cost(old["gx"] * old["gy"], old["ks"], 2600 if old["mc"] == 48 else 3200)
     old_err = 0.18 * ng / old["ks"] + (0.104 * old["ks"] if old["ks"] > 1 else 0.0)
     best = None
     for T in (16, 12):
@@ -50,7 +51,7 @@ def wide_plan(n: int, k: int, m: int, cus: int = 256, flag: bool = True) -> dict
             err = 1.9 + 0.1 * ng / ks + (0.05 + 0.005 * ng / ks + 0.0075 * ng if ks > 1 else 0.0)
             if err > old_err:
                 continue
-            c = cost(gx * gy, ks, 4000 if T == 16 else 3200)
+            c = cost(gx * gy, ks, {(16, False): 4000, (12, False): 3200, (16, True): 5000, (12, True): 4000}[T, third_stream])
             if c < least:
                 least = c
                 best = dict(T=T, gx=gx, gy=gy, ks=ks, nt=nt, ng=ng, err=err, old_err=old_err, ws=partial_bytes(n, m, ks))
