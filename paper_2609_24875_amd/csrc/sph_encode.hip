@@ -80,7 +80,11 @@ typedef _Float16 h2v __attribute__((ext_vector_type(2)));
 typedef _Float16 h8v __attribute__((ext_vector_type(8)));
 typedef float f16v __attribute__((ext_vector_type(16)));
 
-// A unit direction as two fp16 words per pair of coordinates, d = hi + lo up to 2^-22 of it.
+// A unit direction times kUp as two fp16 words per pair of coordinates, hi + lo up to 2^-22 of a coordinate or, where
+// fp16 ends, 2^-25 (2^-40 of the unit direction: unscaled it would be 2^-25, which an entry's coordinate of
+// 6e4 made 2e-3 of a score).
+constexpr float kUp = 0x1p15f, kSlack = 1e-5f * kUp;
+
 struct DirWords {
   uint32_t hi[4], lo[4];
 };
@@ -128,8 +132,8 @@ struct Top3 {
 // array) against direction d: one v_mfma_f32_32x32x16_f16 forms c . d_hi + c . d_lo for 32 entries and
 // 32 vectors (K = 16, the lower lanes' operand d_hi, the upper ones' d_lo, the same entry for both),
 // with LO a second one adds c_lo . (d_hi + d_lo). Products are exact and the fp32 sums of up to 32
-// non-negative terms err by less than 2e-6 of the score, d's split by 2^-22 of it (and by 2^-25 a
-// coordinate where fp16 ends). A lane holds 16 of each 32 entries (rows 8 (i / 4) + 4 (lane / 32) + i % 4)
+// non-negative terms err by less than 2e-6 of the score, d's split by 2^-22 of it (and by 2^-25 times the entry a
+// coordinate where fp16 ends, 1e-6 of kUp at most). A lane holds 16 of each 32 entries (rows 8 (i / 4) + 4 (lane / 32) + i % 4)
 // for vector lane % 32 of two blocks of 32, block b = 0 the wave's vectors 0..31. It keeps the three
 // best keys of blocks of GR * 32 entries. The scan is bound by the vector ALU's maxima
 // (a v_max3_i32 per two scores, 4 cycles; 20 instructions per 64 entries and 32 vectors) on top of the
@@ -267,8 +271,8 @@ __device__ __forceinline__ int wave_scan(const uint4* cb, const uint4* cl, int c
 // The entry of [0, cnt) with the largest fp64 cosine (an FMA chain in coordinate order), the lowest
 // index among equals, for the lane's vector. `active` lanes hold a non-zero direction in w; dir(d)
 // gives it in fp64 and entry(e, c) an entry in fp64. Every entry whose fp64 cosine could be the
-// largest scores within `slack` of the best key: twice the score's error (4e-6 of it), the key's
-// cut-off bits (2^-16 of it) and a margin. One survivor needs no fp64 at all; two are compared;
+// largest scores within the slack of the best key: twice the score's error (4e-6 of it and 1e-6 of
+// kUp), the key's cut-off bits (2^-16 of it) and a margin. One survivor needs no fp64 at all; two are compared;
 // more, or more candidate blocks than were kept, go to a scan of all entries by the whole wave. Lanes
 // without a result (non-finite weights) get 0. The LDS holds nblk whole blocks.
 template <int GR, bool LO, class DirF, class EntF>
@@ -278,7 +282,7 @@ __device__ __forceinline__ int nearest_of(const uint4* cb, const uint4* cl, int 
   Top3 p, q;
   scan_entries<GR, LO>(cb, cl, nblk, w, p, q);
   const float best = __builtin_bit_cast(float, max(p.k[0], q.k[0]) & ~kMask);
-  const float thr = best - (1e-5f + 3e-5f * best);
+  const float thr = best - (kSlack + 3e-5f * best);
   const int thr_i = thr < 0.0f ? INT_MIN : fbits(thr);
   int e1 = 0, e2 = 0, n = 0;
   // the candidate blocks: each lane's best first, then (rarely) the others
@@ -386,7 +390,7 @@ __device__ __forceinline__ int nearest_small(const uint4* cb, int cnt, const Dir
   const int p1 = (int)x1, q1 = (int)y1 | 4, p2 = (int)x2, q2 = (int)y2 | 4;   // bit 2: the rows' half
   const int k1 = max(p1, q1), k2 = max(min(p1, q1), max(p2, q2));
   const float best = __builtin_bit_cast(float, k1 & ~mask);
-  const float thr = best - (1e-5f + best * (1e-5f + (float)(mask + 1) * 0x1p-23f));
+  const float thr = best - (kSlack + best * (1e-5f + (float)(mask + 1) * 0x1p-23f));
   const int thr_i = thr < 0.0f ? INT_MIN : fbits(thr);
   int e1 = k1 & mask;
   const bool wide = active && !(k2 < thr_i && e1 < cnt);
@@ -508,7 +512,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(4)))
       d[j] = ldexpf(f[j], ex);
       ss = fmaf(d[j], d[j], ss);
     }
-    const float inv = active ? __builtin_amdgcn_rsqf(ss) : 0.0f;   // ss is in [1/4, 8)
+    const float inv = active ? kUp * __builtin_amdgcn_rsqf(ss) : 0.0f;   // ss is in [1/4, 8)
 #pragma unroll
     for (int j = 0; j < 8; ++j) d[j] *= inv;
     const DirWords w = split_dir(d);
@@ -696,7 +700,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(4)))
   float f[8], most = 0.0f;
 #pragma unroll
   for (int c = 0; c < 8; ++c) {
-    f[c] = (float)d[c];
+    f[c] = kUp * (float)d[c];
     most = fmaxf(most, f[c]);
   }
   const bool active = most > 0.0f;   // a zero vector's cosines are all 0: the first centre

@@ -91,6 +91,40 @@ def test_scales(fmt, scale):
         assert np.array_equal(got, (d @ O.f16_to_f64(cb).T).argmax(axis=1))
 
 
+def entries_above_two(D, g):
+    """Every other entry large (up to fp16's end) where the weights are tiny, so that both kinds compete, the
+    large ones a few fp16 steps from each other."""
+    cb = synth.random_codebook(D, g)
+    far = cb[1::2]
+    far[:] = synth.f16_bits(1e-3 * g.random(far.shape))
+    at = g.integers(3, 6, len(far))
+    far[np.arange(len(far)), at] = 0x7B00 + g.integers(0, 250, len(far))
+    return cb
+
+
+def weights_tiny_there(g, n, k):
+    w = g.standard_normal((n, k)).astype(np.float32)
+    w.reshape(-1, 8)[:, 3:6] *= 10.0 ** g.uniform(-6, -4.3, (n * k // 8, 1))
+    return w
+
+
+@pytest.mark.parametrize("fmt", ["W2_cfg", "W2", "W2_72", "W3_cfg", "W3"])
+def test_entries_above_two(fmt):
+    """Larger than a unit direction's coordinates, and than what the packer takes, but finite: the nearest entry."""
+    D, V = synth.FORMATS[fmt]
+    g = np.random.default_rng(D)
+    cb, w = entries_above_two(D, g), weights_tiny_there(g, 40, 1024)
+    check(fmt, w, cb)
+    # the k-means samples against the same entries as centres
+    ns = 3000
+    u = g.random(ns)
+    _, obj, idx = pkg.kmeans_codebook(D, V, torch.from_numpy(w).to(DEV), torch.from_numpy(u).to(DEV),
+                                      torch.from_numpy(cb.view(np.int16)).to(DEV), 0)
+    d = np.abs(w.astype(np.float64)).reshape(-1, 8)[idx.cpu().numpy()]
+    best = (d / np.linalg.norm(d, axis=1, keepdims=True) @ O.f16_to_f64(cb).T).max(axis=1).sum()
+    assert np.allclose(obj.cpu().numpy(), best, rtol=1e-12)
+
+
 @pytest.mark.parametrize("fmt,ns", [("W2", 5000), ("W3", 5000), ("W3_cfg", 1023), ("W2", 64), ("W3", 70000),
                                     # sums by chunks: a chunk of one sample over, and the most chunks
                                     ("W2_cfg", 32769), ("W3_cfg", 257), ("W2_cfg", 70000)])
