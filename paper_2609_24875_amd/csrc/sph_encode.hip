@@ -77,7 +77,9 @@ __device__ __forceinline__ double decompose(const float* __restrict__ w, int64_t
 // ------------------------------------------------------------------------------------ Eq. 5
 
 typedef _Float16 h2v __attribute__((ext_vector_type(2)));
+typedef _Float16 h4v __attribute__((ext_vector_type(4)));
 typedef _Float16 h8v __attribute__((ext_vector_type(8)));
+typedef float f4v __attribute__((ext_vector_type(4)));
 typedef float f16v __attribute__((ext_vector_type(16)));
 
 // A unit direction times kUp as two fp16 words per pair of coordinates, hi + lo up to 2^-22 of a coordinate or, where
@@ -268,6 +270,69 @@ __device__ __forceinline__ int wave_scan(const uint4* cb, const uint4* cl, int c
   return be < cnt ? be : 0;
 }
 
+// The same for all lanes whose thr is finite, by scoring the entries on the matrix cores once more: cheaper than
+// wave_scan for one lane after the other where many lanes need it (codebooks with equal or nearly equal
+// entries: 1000x1024 with each of 8192 entries four times 1.00 -> 0.35 ms; two k-means iterations with each centre
+// sixteen times 1.57 -> 0.73 ms, 64 centres 0.22 -> 0.12). On 16x16x16 products, whose four scores a lane leave the
+// registers of the first scan as they are (32x32x16 ones cost every W3 encode 1.6%).
+template <bool LO, class EntF>
+__device__ __forceinline__ int rescan(const uint4* cb, const uint4* cl, int cnt, const DirWords& w, const double (&d)[8], float thr,
+                                      EntF entry) {
+  const int lane = threadIdx.x & 63, col = lane & 15, grp = lane >> 4;
+  int own = 0;
+#pragma unroll 1
+  for (int b = 0; b < 4; ++b) {   // vectors 16 b + col
+    const int src = 16 * b + col;
+    const float tv = __shfl(thr, src, 64);
+    if (!__any(tv < INFINITY)) continue;
+    uint32_t x[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const uint32_t h0 = __shfl(w.hi[i], src, 64), h1 = __shfl(w.hi[2 + i], src, 64), l0 = __shfl(w.lo[i], src, 64), l1 = __shfl(w.lo[2 + i], src, 64);
+      x[i] = grp == 0 ? h0 : grp == 1 ? h1 : grp == 2 ? l0 : l1;
+    }
+    const h4v bop = __builtin_bit_cast(h4v, make_uint2(x[0], x[1]));
+    double dv[8], bs = -INFINITY;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) dv[i] = __shfl(d[i], src, 64);
+    int be = INT_MAX;
+#pragma unroll 1
+    for (int e0 = 0; e0 < cnt; e0 += 16) {
+      const int at = 2 * (e0 + col) + (grp & 1);   // four of the entry's coordinates
+      f4v s = __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(h4v, ((const uint2*)cb)[at]), bop, f4v{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
+      if constexpr (LO) s = __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(h4v, ((const uint2*)cl)[at]), bop, s, 0, 0, 0);
+      uint32_t hits = 0;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) hits |= (s[i] >= tv ? 1u : 0u) << i;
+#pragma unroll 1
+      while (__any(hits != 0)) {
+        const int e = e0 + 4 * grp + (hits ? __builtin_ctz(hits) : 0);
+        if (hits && e < cnt) {
+          double c[8];
+          entry(e, c);
+          const double sc = cosine(dv, c);
+          if (sc > bs) {
+            bs = sc;
+            be = e;
+          }
+        }
+        hits &= hits - 1;
+      }
+    }
+#pragma unroll
+    for (int o = 16; o <= 32; o <<= 1) {
+      const double os = __shfl_xor(bs, o, 64);
+      const int oe = __shfl_xor(be, o, 64);
+      if (os > bs || (os == bs && oe < be)) {
+        bs = os;
+        be = oe;
+      }
+    }
+    if (grp == b) own = be < cnt ? be : 0;
+  }
+  return own;
+}
+
 // The entry of [0, cnt) with the largest fp64 cosine (an FMA chain in coordinate order), the lowest
 // index among equals, for the lane's vector. `active` lanes hold a non-zero direction in w; dir(d)
 // gives it in fp64 and entry(e, c) an entry in fp64. Every entry whose fp64 cosine could be the
@@ -336,7 +401,13 @@ __device__ __forceinline__ int nearest_of(const uint4* cb, const uint4* cl, int 
       const double s1 = cosine(d, c1), s2 = cosine(d, c2);
       if (s2 > s1 || (s2 == s1 && e2 < e1)) e1 = e2;
     }
-    for (uint64_t todo = __ballot(wide); todo; todo &= todo - 1) {
+    uint64_t todo = __ballot(wide);
+    if (__builtin_expect(__builtin_popcountll(todo) > 8, 0)) {
+      const int e = rescan<LO>(cb, cl, cnt, w, d, wide ? thr : INFINITY, entry);
+      if (wide) e1 = e;
+      todo = 0;
+    }
+    for (; todo; todo &= todo - 1) {
       const int src = (int)__builtin_ctzll(todo);
       const int e = wave_scan<LO>(cb, cl, cnt, w, d, thr, src, entry);
       if ((int)(threadIdx.x & 63) == src) e1 = e;
@@ -397,7 +468,25 @@ __device__ __forceinline__ int nearest_small(const uint4* cb, int cnt, const Dir
   if (__any(wide)) {
     double d[8];
     dir(d);
-    for (uint64_t todo = __ballot(wide); todo; todo &= todo - 1) {
+    uint64_t todo = __ballot(wide);
+    // equal or nearly equal entries for many lanes: every lane compares them all in fp64 (1000x1024 with each entry
+    // twice, 64 entries 83 -> 14 us, 256 110 -> 41)
+    if (5 * __builtin_popcountll(todo) > cnt) {
+      double bs = -INFINITY;
+      int be = 0;
+      for (int e = 0; e < cnt; ++e) {
+        double c[8];
+        entry(e, c);
+        const double sc = cosine(d, c);
+        if (sc > bs) {
+          bs = sc;
+          be = e;
+        }
+      }
+      if (wide) e1 = be;
+      todo = 0;
+    }
+    for (; todo; todo &= todo - 1) {
       const int src = (int)__builtin_ctzll(todo);
       const int e = wave_scan<false>(cb, nullptr, cnt, w, d, thr, src, entry);
       if (lane == src) e1 = e;
