@@ -1292,7 +1292,7 @@ sph_status sph_encode(const sph_format* fmt, int64_t n, int64_t k, const float* 
   a.gstep = d_group_step;
   const int64_t units = (a.nvec + 63) / 64;
   if (a.ncb <= kSmallEntries) {
-    if (!launch_ok((const void*)k_encode<kSmallEntries, 4>, dim3((unsigned)((units + 3) / 4)), dim3(256), (hipStream_t)stream, a, units))
+    if (!launch_ok((const void*)k_encode<kSmallEntries, kEncodeWaves>, dim3(sph_encode_blocks(units)), dim3(64 * kEncodeWaves), (hipStream_t)stream, a, units))
       return SPH_ERR_HIP;
     return SPH_OK;
   }

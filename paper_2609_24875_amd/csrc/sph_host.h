@@ -19,3 +19,12 @@ void sph_host_pack(const sph_format* fmt, int64_t n, int64_t k, const uint8_t* s
 // product (SPH_FLAG_RADIUS_SPLIT): codes already checked by sph_host_check_codes.
 bool sph_host_radius_split(const sph_format* fmt, int64_t n, int64_t k, const uint16_t* gmin, const uint16_t* gstep,
                            const uint16_t* codebook);
+
+// Workgroups of the encoder's small-codebook kernel: 4 waves of 256 threads take 64 vectors each and go on in steps
+// of the grid, which stays below the 2^32 threads that a launch may have (a matrix may have 2^35 vectors).
+constexpr int kEncodeWaves = 4;
+
+static inline unsigned sph_encode_blocks(int64_t units) {
+  const int64_t b = (units + kEncodeWaves - 1) / kEncodeWaves;
+  return (unsigned)(b < (int64_t(1) << 22) ? b : int64_t(1) << 22);
+}
