@@ -141,8 +141,11 @@ def _stream_handle(stream=None) -> int:
     if stream is not None:
         return int(stream.cuda_stream)
     if torch.cuda.is_initialized():
-        # the current stream's handle without building a Python Stream object for it
-        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        # the current stream's handle without building a Python Stream object for it, where this torch offers that
+        try:
+            return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+        except AttributeError:
+            pass
     return int(torch.cuda.current_stream().cuda_stream)
 
 

@@ -64,3 +64,18 @@ def test_launch_errors(monkeypatch):
     monkeypatch.setattr(torch.cuda, "is_current_stream_capturing", lambda: True)
     with pytest.raises(RuntimeError, match="capturing a graph"):
         B._launch(_library(512, []), "call", _weights(), 1, SimpleNamespace(device="cpu"), (), STREAM)
+
+
+@pytest.mark.parametrize("missing", [None, "_cuda_getCurrentRawStream", "_cuda_getDevice"])
+def test_current_stream_handle(monkeypatch, missing):
+    """The raw lookup where torch has it, the public one where it does not."""
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: True)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: SimpleNamespace(cuda_stream=55))
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda dev: 40 + dev, raising=False)
+    monkeypatch.setattr(torch._C, "_cuda_getDevice", lambda: 3, raising=False)
+    if missing:
+        monkeypatch.delattr(torch._C, missing)
+    assert B._stream_handle() == (55 if missing else 43)
+    assert B._stream_handle(STREAM) == 77
+    monkeypatch.setattr(torch.cuda, "is_initialized", lambda: False)
+    assert B._stream_handle() == 55
