@@ -176,11 +176,11 @@ __global__ __launch_bounds__(kThreads) void k_fq_forward(FqArgs a) {
   for (int t = 0; t < VPT; ++t) {
     const int64_t i = base + t * kThreads + tid;   // whole groups are inside or outside together
     x[t] = i < a.nvec ? a.rho[i] : 0.0f;
-    if (x[t] != x[t]) x[t] = 0.0f;   // softplus_d's value without a number, log 2, is softplus(0)
     if (i < a.nvec) dz[t * kThreads + tid] = (uint32_t)a.dir[i] | ((uint32_t)a.signs[i] << 16);
   }
 #pragma unroll
   for (int t = 0; t < VPT; ++t) {
+    if (x[t] != x[t]) x[t] = 0.0f;   // softplus_d's value without a number, log 2, is softplus(0)
     float lo = x[t], hi = x[t];
     lo = fminf(lo, row_ror<0x128>(lo));
     hi = fmaxf(hi, row_ror<0x128>(hi));
