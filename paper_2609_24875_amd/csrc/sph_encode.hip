@@ -11,7 +11,7 @@
 // Work layout:
 //   Eq. 5 search a wave takes 64 vectors (or samples); the matrix cores score them against all
 //                entries within a known error, and only entries within that error of the best are
-//                compared in fp64 (see scan_entries and nearest_of).
+//                compared in fp64 (see scan_entries, nearest_of and nearest_small).
 //   encoder      16 neighbouring lanes form one 128-weight group; the fp16 codebook sits in LDS.
 //   k-means      squared radii and their running sum (three-pass scan), inverse-CDF sampling by
 //                binary search, then per iteration: assignment (the centre range split over

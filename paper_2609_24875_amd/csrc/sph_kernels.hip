@@ -2101,8 +2101,9 @@ PrefillPlan prefill_plan(const sph_weights* w, int64_t m) {
 // The plan of a batch above 64 on the two-product kernel, where it applies and pays; otherwise
 // wide = 0. It applies to matrices flagged at pack time, and where its rounding error is no larger
 // than the three-product kernel's under plan `old`. Variance of fp32 outputs against fp64, relative to the
-// outputs' and in units of 2^-48, fitted to 119 matrices of W2, W3, W3_cfg and (8, 2) with 4 to 97 chunks
-// and 1 to 16 K ranges, encoded radii and others (within 3% of each in the error itself, C chunks per range):
+// outputs' and in units of 2^-48, fitted to 238 calls of (6, 4), (13, 3), (8, 8) and (8, 2) with 4 to 97 chunks
+// and 1 to 16 K ranges, encoded radii and others (within 6% of each in the error itself, and on the right side of
+// the comparison in all; C chunks per range):
 //   three products  0.18 C + 1.3, and 0.104 per range of a split
 //   two products    0.10 C + 3.2, and 0.05 + 0.005 C + 0.0075 per chunk of all ranges for a split
 // So one range takes it from 24 chunks on (k = 3072); 6144x4096 at 256 rows in 4 ranges is the same error

@@ -2,9 +2,10 @@
 
 Bars: unpacked codes bit-exact; outputs within rel_err <= 2e-3 (max |y - y*| over
 max(|y*|, row RMS of y*)), the tolerance the target states for fp32 accumulation against the
-fp64 oracle. Every path forms exact fp16 products (the signed directions, and on the matrix
-cores the level times the direction split exactly into two fp16 words) and rounds only its fp32
-radius and sums. Each path is also held, output by output, to the a-priori bound its arithmetic
+fp64 oracle. Every path up to batch 64 forms exact fp16 products (the signed directions, and on the
+matrix cores the level times the direction split exactly into two fp16 words) and rounds only its
+fp32 radius and sums; larger batches on large matrices multiply the rounded radius times the direction in two fp16
+words (tests/test_gpu_prefill_wide.py). Each path is also held, output by output, to the a-priori bound its arithmetic
 gives.
 
 Group parameters (Eq. 7) are drawn independently for every group of every row, with negative
