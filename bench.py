@@ -40,9 +40,9 @@ KERNEL_SOURCE = os.path.join(ROOT, "paper_2609_24875_amd", "csrc", "sph_kernels.
 # SHA-256 of the kernel source and compile flags the counters were taken with: any change to
 # the kernels makes the entry stale and `traffic` is reported as null.
 TRAFFIC = {
-    "67117cf4e921a554fe05a4f18909f0c7791f3b968329480c31c31bb3ff178865": {
-        "7168x5120-m1": 11924914, "5120x5120-m1": 8754308,
-        "51200x5120-m1": 82695931, "5120x25600-m1": 41959939},
+    "e48f50c77530a5e7691bbd70c52aacb50ef2920daa449469a291182e2b0cad1e": {
+        "7168x5120-m1": 11903311, "5120x5120-m1": 8739647,
+        "51200x5120-m1": 82678301, "5120x25600-m1": 41945286},
 }
 
 def kernel_source_hash() -> str:

@@ -449,10 +449,10 @@ __global__ __launch_bounds__(kThreads) void k_fq_grad_cb_part(int64_t nv, const 
 // blocks' sums, else in the radius gradient's first ncb * 8 values of the block's stretch, which
 // k_fq_grad_rho fills afterwards.
 //
-// 47 bytes per vector, read and written once and in order. The gather of the lists by centre (below)
+// 47 bytes per vector, read and written once and in order. The gather of the lists by centre (above)
 // moved a 128-byte line into L1 for each 32-byte gradient, each radius and each sign byte: 2.4 GB for
 // 12288x4096, 244 us, and the radius gradient took another 55 us; this pass takes 96
-// us, half vector-ALU work (the cuts and the one-hot words). Additions to
+// us, the vector ALUs busy 73% of it (the cuts and the one-hot words). Additions to
 // the wave's sums in LDS (ds_add_f32) took 260 us, one lane every three cycles.
 constexpr int kPassWaves = 8;
 constexpr float kPassUp = 0x1p24f, kPassDown = 0x1p-40f, kPassMost = 0x1p104f;
