@@ -2,6 +2,7 @@
 // Host side of the library: argument validation and packing of logical SPHQuant codes
 // (Sec. 3.1, Eq. 3-7) into the device layout described in sph_layout.h. Pure C++: no HIP
 // headers, so it also builds and runs with g++ on a machine without a GPU.
+#include <algorithm>
 #include <cmath>
 #include <cstring>
 #include <vector>
@@ -106,14 +107,22 @@ bool sph_host_radius_split(const sph_format* fmt, int64_t n, int64_t k, const ui
   if (fmt->vec_dim != SPH_VEC) return false;
   const int64_t ngrp = n * (k / SPH_GROUP);
   const float top = (float)((1 << fmt->radius_bits) - 1);
-  int64_t one = 0, both = 0;   // groups with only one of the two parameters, or with both
   for (int64_t i = 0; i < ngrp; ++i) {
     const uint16_t oh = gmin[i] & 0x7FFF, sh = gstep[i] & 0x7FFF;
-    one += (oh == 0) != (sh == 0);
-    both += oh != 0 && sh != 0;
     if (oh >= sh || oh == 0) continue;   // an offset of at least the step is above (2^V - 1 <= 255) / 4096 of it
     const float o = f16_value(oh), s = f16_value(sh);
     if (o * 4096.0f < o + top * s) return false;
+  }
+  int64_t one = 0, both = 0;   // groups with only one of the two parameters, or with both
+  for (int64_t a = 0; a < ngrp; a += 4096) {
+    uint16_t x = 0, y = 0;     // up to 4096 each: as wide as the parameters, for the vectoriser
+    for (int64_t i = a; i < std::min(ngrp, a + 4096); ++i) {
+      const uint16_t o = (gmin[i] & 0x7FFF) != 0, s = (gstep[i] & 0x7FFF) != 0;
+      x += o ^ s;
+      y += o & s;
+    }
+    one += x;
+    both += y;
   }
   if (one * 13 > both * 3) return false;
   for (int64_t z = 0; z < (int64_t(1) << fmt->dir_bits); ++z) {
